@@ -40,14 +40,19 @@ struct nnp_handle {
   long param_off[kMaxModels * kMaxS][kLayers] = {};  // flat offset of W for (slot, layer)
   char* dmem = nullptr;
   float* flat = nullptr;
+  bool net = false;            // the fused network takes these widths (net_widths)
+  // weight copies, those that the precision's kernels read (null otherwise)
   float* Wf[kLayers] = {};     // row-major W and W^T (LDS-staged kernels)
   bf16_t* Wb[kLayers] = {};
   float* WTf[kLayers] = {};
-  bf16_t* Wqb[kLayers] = {};   // fragment order, W and W^T (BF16 body kernels)
+  bf16_t* Wqb[kLayers] = {};   // fragment order, W and W^T (fused network, BF16 body kernels)
   bf16_t* WTqb[kLayers] = {};
+  float* Wqf[kLayers] = {};    // fragment order, FP32 (fused network)
+  float* WTqf[kLayers] = {};
   float* bias[kLayers] = {};
   float* WT0cf = nullptr;      // ensembles: member-concatenated W_0^T (dE/dG in one product)
-  bf16_t* WT0cq = nullptr;
+  bf16_t* WT0cq = nullptr;     // ... in fragment order
+  float* WT0cqf = nullptr;
   float* wout = nullptr;
   float* bout = nullptr;
   double* eself = nullptr;
@@ -115,12 +120,12 @@ __global__ void k_copy_status(const uint32_t* __restrict__ src, uint32_t* __rest
 
 enum Stage {
   ST_STAGE = 0, ST_PAIRS, ST_AEV, ST_L1, ST_L2, ST_HEAD, ST_ENERGY, ST_BWD3, ST_BWD2, ST_GRADG,
-  ST_AEVBWD, ST_WGRAD, ST_MID, ST_NET, ST_COUNT
+  ST_AEVBWD, ST_WGRAD, ST_NET, ST_COUNT
 };
 const char* kStageNames[ST_COUNT] = {
     "stage+sort", "neighbors", "aev_fwd", "mlp_layer1", "mlp_layer2", "mlp_layer3_head",
     "energy_sum", "mlp_bwd_layer3", "mlp_bwd_layer2", "mlp_bwd_dEdG", "aev_bwd_forces",
-    "weight_grads", "mlp_mid_fused", "mlp_net_fused"};
+    "weight_grads", "mlp_net_fused"};
 
 hipEvent_t prof_event(nnp_handle* h) {
   if (h->ev_next == h->ev_pool.size()) {
@@ -381,17 +386,12 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
   }
   T* X = at<T>(ws, P.X);
   unsigned long long* kmask = at<unsigned long long>(ws, P.kmask);
-  // BF16 with gradients, one network: layer 1, the fused middle and dE/dG
-  // in one launch per tile (H1 and D1 stay in LDS)
-  const bool net_path = bf && need_bwd && h->n_models == 1 && h->width[1] == 256 &&
-                        h->width[2] == 192 && h->width[3] == 160 && Fp % 256 == 0 &&
-                        Fp <= 2048;
   {
     StageTimer t(h, io.timed, ST_AEV, st);
-    // the whole-network kernel reads each row's own k-steps only; the weight
+    // the fused network reads each row's own k-steps only; the weight
     // gradients and the layer kernels read whole rows
     launch_aev_fwd<T>(dims, P.n, h->C, rec, counts, P.cap, row, X, Fp, h->deterministic, kmask,
-                      net_path && !io.dparams, st);
+                      h->net && !io.dparams, st);
   }
 
   T* H1 = at<T>(ws, P.H1);
@@ -402,8 +402,64 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
   T* D1 = at<T>(ws, P.D1);
   T* G = at<T>(ws, P.G);
   float* erow = at<float>(ws, P.erow);
-  // B operands: row-major W (both precisions) and W^T (FP32), and the BF16
-  // fragment-order copies of W and W^T
+  const int M = h->n_models;
+  const int ldd1 = M * w1;  // D1 row: the members' delta1 side by side
+  const float escale = 1.f / (float)M;
+  const float inv_alpha_l2e = (float)(1.4426950408889634 / h->alpha);
+  bool ok = true;
+  if (h->net) {
+    // every member's whole network in one launch; an ensemble's dE/dG (the
+    // sum over the members) in a second
+    NetArgs na{};
+    na.gt = gt;
+    na.S = S;
+    na.X = X;
+    na.ldx = Fp;
+    na.kmask = kmask;
+    na.W0 = bf ? (const void*)h->Wqb[0] : h->Wqf[0];
+    na.W1 = bf ? (const void*)h->Wqb[1] : h->Wqf[1];
+    na.W2 = bf ? (const void*)h->Wqb[2] : h->Wqf[2];
+    na.W2T = bf ? (const void*)h->WTqb[2] : h->WTqf[2];
+    na.W1T = bf ? (const void*)h->WTqb[1] : h->WTqf[1];
+    na.W0T = bf ? (const void*)h->WTqb[0] : h->WTqf[0];
+    na.b0 = h->bias[0];
+    na.b1 = h->bias[1];
+    na.b2 = h->bias[2];
+    na.wout = h->wout;
+    na.bout = h->bout;
+    na.alpha = h->alpha;
+    na.inv_alpha_l2e = inv_alpha_l2e;
+    na.escale = escale;
+    na.perm = perm;
+    na.mol = mol;
+    na.dLdE = io.dLdE;
+    na.erow = erow;
+    na.erow_stride = P.rows_cap;
+    na.bwd = need_bwd;
+    na.G = io.out3 && M == 1 ? G : nullptr;
+    na.D1 = io.dparams || (io.out3 && M > 1) ? D1 : nullptr;
+    na.ld_d1 = ldd1;
+    if (io.dparams) {
+      na.H1 = H1;
+      na.H2 = H2;
+      na.H3 = H3;
+      na.D3 = D3;
+      na.D2 = D2;
+      na.uprow = at<float>(ws, P.uprow);
+    }
+    {
+      StageTimer t(h, io.timed, ST_NET, st);
+      // (the feature rows may be stored sparse: no other kernel may take over)
+      ok &= launch_mlp_net<T>(h->width, na, P.n, P.rows_cap, M, st);
+    }
+    if (io.out3 && M > 1) {
+      NetGradArgs ga{gt, D1, ldd1, bf ? (const void*)h->WT0cq : h->WT0cqf, kmask, G, Fp};
+      StageTimer t(h, io.timed, ST_GRADG, st);
+      launch_net_grad<T>(ga, P.rows_cap, st);
+    }
+  }
+  // other widths, layer by layer.  B operands: row-major W (both precisions)
+  // and W^T (FP32), and the BF16 fragment-order copies of W and W^T
   const void* W[kLayers];
   const void* WT[kLayers];
   const void* Wq[kLayers];
@@ -414,13 +470,8 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     Wq[l] = bf ? (const void*)h->Wqb[l] : nullptr;
     WTq[l] = bf ? (const void*)h->WTqb[l] : nullptr;
   }
-  const int M = h->n_models;
-  const int ldd1 = M * w1;  // D1 row: the members' delta1 side by side
-  const float escale = 1.f / (float)M;
   const size_t esz = sizeof(T);
-  bool ok = true;
-  bool net_fused = false;  // the whole network ran as one launch (dE/dG included)
-  for (int k = 0; k < M; ++k) {
+  for (int k = 0; k < M && !h->net; ++k) {
     // member k: weight slots k * S .. k * S + S - 1
     const int q0 = k * S;
     float* erow_k = erow + (size_t)k * P.rows_cap;
@@ -441,51 +492,10 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     for (int l = 0; l < kLayers - 1; ++l) bias_k[l] = h->bias[l] + (size_t)q0 * h->width[l + 1];
     const float* wout_k = h->wout + (size_t)q0 * w3;
     const float* bout_k = h->bout + q0;
-    if (net_path) {
-      MidArgs ma{};
-      ma.gt = gt;
-      ma.W1 = static_cast<const bf16_t*>(Wqk[1]);
-      ma.W2 = static_cast<const bf16_t*>(Wqk[2]);
-      ma.W2T = static_cast<const bf16_t*>(WTqk[2]);
-      ma.W1T = static_cast<const bf16_t*>(WTqk[1]);
-      ma.b1 = bias_k[1];
-      ma.b2 = bias_k[2];
-      ma.wout = wout_k;
-      ma.bout = bout_k;
-      ma.erow = erow_k;
-      ma.D1 = io.dparams ? reinterpret_cast<bf16_t*>(D1k) : nullptr;  // the weight gradients' copy
-      ma.ld_d1 = ldd1;
-      ma.escale = escale;
-      if (io.dparams) {
-        ma.H2 = reinterpret_cast<bf16_t*>(H2);
-        ma.H3 = reinterpret_cast<bf16_t*>(H3);
-        ma.D3 = reinterpret_cast<bf16_t*>(D3);
-        ma.D2 = reinterpret_cast<bf16_t*>(D2);
-        ma.uprow = at<float>(ws, P.uprow);
-      }
-      ma.perm = perm;
-      ma.mol = mol;
-      ma.dLdE = io.dLdE;
-      ma.alpha = h->alpha;
-      ma.inv_alpha_l2e = (float)(1.4426950408889634 / h->alpha);
-      ma.X = reinterpret_cast<const bf16_t*>(X);
-      ma.ldx = Fp;
-      ma.W0 = static_cast<const bf16_t*>(Wqk[0]);
-      ma.b0 = bias_k[0];
-      ma.H1out = reinterpret_cast<bf16_t*>(H1);
-      ma.W0T = static_cast<const bf16_t*>(WTq[0]);
-      ma.G = io.out3 ? reinterpret_cast<bf16_t*>(G) : nullptr;
-      ma.kmask = kmask;
-      StageTimer t(h, io.timed, ST_NET, st);
-      // (the feature rows may be stored sparse: no other kernel may take over)
-      ok &= launch_mlp_net(h->width, ma, P.rows_cap, st);
-      net_fused = true;
-      continue;
-    }
     GemmArgs g{};
     g.gt = gt;
     g.alpha = h->alpha;
-    g.inv_alpha_l2e = (float)(1.4426950408889634 / h->alpha);
+    g.inv_alpha_l2e = inv_alpha_l2e;
     g.escale = escale;
     // layer 1: H1 = CELU(X W0^T + b0)
     g.A = X; g.lda = Fp; g.B = Wk[0]; g.Bq = Wqk[0]; g.sB = (long)w1 * Fp; g.ldb = Fp;
@@ -496,77 +506,41 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
       ok &= launch_gemm<T>(EPI_CELU, g, P.rows_cap, st);
     }
     g.kmask_k = nullptr;
-    // BF16 with gradients: one fused launch for layer 2, the energy head and the
-    // adjoint of layers 3 and 2 (intermediates stay in LDS)
-    bool fused = false;
-    if (bf && need_bwd) {
-      MidArgs ma{};
-      ma.gt = gt;
-      ma.H1 = reinterpret_cast<const bf16_t*>(H1);
-      ma.W1 = static_cast<const bf16_t*>(Wqk[1]);
-      ma.W2 = static_cast<const bf16_t*>(Wqk[2]);
-      ma.W2T = static_cast<const bf16_t*>(WTqk[2]);
-      ma.W1T = static_cast<const bf16_t*>(WTqk[1]);
-      ma.b1 = bias_k[1];
-      ma.b2 = bias_k[2];
-      ma.wout = wout_k;
-      ma.bout = bout_k;
-      ma.erow = erow_k;
-      ma.D1 = reinterpret_cast<bf16_t*>(D1k);
-      ma.ld_d1 = ldd1;
-      ma.escale = escale;
-      if (io.dparams) {
-        ma.H2 = reinterpret_cast<bf16_t*>(H2);
-        ma.H3 = reinterpret_cast<bf16_t*>(H3);
-        ma.D3 = reinterpret_cast<bf16_t*>(D3);
-        ma.D2 = reinterpret_cast<bf16_t*>(D2);
-        ma.uprow = at<float>(ws, P.uprow);
-      }
-      ma.perm = perm;
-      ma.mol = mol;
-      ma.dLdE = io.dLdE;
-      ma.alpha = h->alpha;
-      ma.inv_alpha_l2e = g.inv_alpha_l2e;
-      StageTimer t(h, io.timed, ST_MID, st);
-      fused = launch_mlp_mid(h->width, ma, P.rows_cap, st);
+    // layer 2: H2 = CELU(H1 W1^T + b1)
+    g.A = H1; g.lda = w1; g.B = Wk[1]; g.Bq = Wqk[1]; g.sB = (long)w2 * w1; g.ldb = w1;
+    g.bias = bias_k[1]; g.sBias = w2; g.N = w2; g.K = w1; g.C = H2; g.ldc = w2;
+    {
+      StageTimer t(h, io.timed, ST_L2, st);
+      ok &= launch_gemm<T>(EPI_CELU, g, P.rows_cap, st);
     }
-    if (!fused) {
-      // layer 2: H2 = CELU(H1 W1^T + b1)
-      g.A = H1; g.lda = w1; g.B = Wk[1]; g.Bq = Wqk[1]; g.sB = (long)w2 * w1; g.ldb = w1;
-      g.bias = bias_k[1]; g.sBias = w2; g.N = w2; g.K = w1; g.C = H2; g.ldc = w2;
+    // layer 3 + output: E_i, delta3
+    g.A = H2; g.lda = w2; g.B = Wk[2]; g.Bq = nullptr; g.sB = (long)w3 * w2; g.ldb = w2;
+    g.bias = bias_k[2]; g.sBias = w3; g.N = w3; g.K = w2;
+    g.C = need_bwd ? (void*)D3 : nullptr; g.ldc = w3;
+    g.w_out = wout_k; g.sWout = w3; g.b_out = bout_k; g.erow = erow_k;
+    g.H3 = io.dparams ? (void*)H3 : nullptr; g.ldh3 = w3;
+    g.perm = perm; g.mol = mol; g.dLdE = io.dLdE;
+    g.uprow = io.dparams ? at<float>(ws, P.uprow) : nullptr;
+    {
+      StageTimer t(h, io.timed, ST_HEAD, st);
+      ok &= launch_gemm<T>(EPI_HEAD, g, P.rows_cap, st);
+    }
+    g.H3 = nullptr;
+    g.uprow = nullptr;
+    if (need_bwd) {
+      // delta2 = (delta3 W2) * CELU'(z2)
+      g.A = D3; g.lda = w3; g.B = WTk[2]; g.Bq = WTqk[2]; g.sB = (long)w2 * w3; g.ldb = w3;
+      g.bias = nullptr; g.N = w2; g.K = w3; g.C = D2; g.ldc = w2; g.H = H2; g.ldh = w2;
       {
-        StageTimer t(h, io.timed, ST_L2, st);
-        ok &= launch_gemm<T>(EPI_CELU, g, P.rows_cap, st);
+        StageTimer t(h, io.timed, ST_BWD3, st);
+        ok &= launch_gemm<T>(EPI_BWD, g, P.rows_cap, st);
       }
-      // layer 3 + output: E_i, delta3
-      g.A = H2; g.lda = w2; g.B = Wk[2]; g.Bq = nullptr; g.sB = (long)w3 * w2; g.ldb = w2;
-      g.bias = bias_k[2]; g.sBias = w3; g.N = w3; g.K = w2;
-      g.C = need_bwd ? (void*)D3 : nullptr; g.ldc = w3;
-      g.w_out = wout_k; g.sWout = w3; g.b_out = bout_k; g.erow = erow_k;
-      g.H3 = io.dparams ? (void*)H3 : nullptr; g.ldh3 = w3;
-      g.perm = perm; g.mol = mol; g.dLdE = io.dLdE;
-      g.uprow = io.dparams ? at<float>(ws, P.uprow) : nullptr;
+      // delta1 = (delta2 W1) * CELU'(z1)
+      g.A = D2; g.lda = w2; g.B = WTk[1]; g.Bq = WTqk[1]; g.sB = (long)w1 * w2; g.ldb = w2;
+      g.N = w1; g.K = w2; g.C = D1k; g.ldc = ldd1; g.H = H1; g.ldh = w1;
       {
-        StageTimer t(h, io.timed, ST_HEAD, st);
-        ok &= launch_gemm<T>(EPI_HEAD, g, P.rows_cap, st);
-      }
-      g.H3 = nullptr;
-      g.uprow = nullptr;
-      if (need_bwd) {
-        // delta2 = (delta3 W2) * CELU'(z2)
-        g.A = D3; g.lda = w3; g.B = WTk[2]; g.Bq = WTqk[2]; g.sB = (long)w2 * w3; g.ldb = w3;
-        g.bias = nullptr; g.N = w2; g.K = w3; g.C = D2; g.ldc = w2; g.H = H2; g.ldh = w2;
-        {
-          StageTimer t(h, io.timed, ST_BWD3, st);
-          ok &= launch_gemm<T>(EPI_BWD, g, P.rows_cap, st);
-        }
-        // delta1 = (delta2 W1) * CELU'(z1)
-        g.A = D2; g.lda = w2; g.B = WTk[1]; g.Bq = WTqk[1]; g.sB = (long)w1 * w2; g.ldb = w2;
-        g.N = w1; g.K = w2; g.C = D1k; g.ldc = ldd1; g.H = H1; g.ldh = w1;
-        {
-          StageTimer t(h, io.timed, ST_BWD2, st);
-          ok &= launch_gemm<T>(EPI_BWD, g, P.rows_cap, st);
-        }
+        StageTimer t(h, io.timed, ST_BWD2, st);
+        ok &= launch_gemm<T>(EPI_BWD, g, P.rows_cap, st);
       }
     }
   }  // members
@@ -585,7 +559,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     GemmArgs g{};
     g.gt = gt;
     g.alpha = h->alpha;
-    g.inv_alpha_l2e = (float)(1.4426950408889634 / h->alpha);
+    g.inv_alpha_l2e = inv_alpha_l2e;
     const bool cat = M > 1;
     g.A = D1; g.lda = ldd1;
     g.B = cat ? (bf ? nullptr : (const void*)h->WT0cf) : WT[0];
@@ -593,7 +567,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     g.sB = (long)Fp * ldd1; g.ldb = ldd1;
     g.N = Fp; g.K = ldd1; g.C = G; g.ldc = Fp; g.H = nullptr;
     g.kmask_n = kmask;  // the adjoint reads a row's own k-steps of dE/dG only
-    if (!net_fused) {
+    if (!h->net) {
       StageTimer t(h, io.timed, ST_GRADG, st);
       ok &= launch_gemm<T>(EPI_OUT, g, P.rows_cap, st);
     }
@@ -761,21 +735,25 @@ nnp_status nnp_create_ensemble(const nnp_aev_params* aev, const nnp_mlp_params* 
     return a;
   };
   const size_t o_flat = take(o * 4);
-  size_t o_wf[kLayers], o_wb[kLayers], o_wtf[kLayers], o_wqb[kLayers], o_wtqb[kLayers],
-      o_b[kLayers];
+  // the copies of W and W^T that the handle's kernels read: fragment order
+  // (the fused network; BF16 layer kernels, whose head also reads W
+  // row-major), or row-major (FP32 layer kernels)
+  h->net = net_widths(h->width, h->Fp);
+  const bool bf = precision == NNP_MLP_BF16;
+  const bool frag = bf || h->net, rows = !h->net;
+  const size_t ew = bf ? 2 : 4;
+  size_t o_w[kLayers], o_wt[kLayers], o_wq[kLayers], o_wtq[kLayers], o_b[kLayers];
   for (int l = 0; l < kLayers - 1; ++l) {
     const size_t inp = l == 0 ? h->Fp : h->width[l];
     const size_t el = (size_t)Q * h->width[l + 1] * inp;
-    o_wf[l] = take(el * 4);
-    o_wb[l] = take(el * 2);
-    o_wtf[l] = take(el * 4);
-    o_wqb[l] = take(el * 2);
-    o_wtqb[l] = take(el * 2);
+    o_w[l] = take(rows ? el * ew : 0);
+    o_wt[l] = take(rows && !bf ? el * ew : 0);
+    o_wq[l] = take(frag ? el * ew : 0);
+    o_wtq[l] = take(frag ? el * ew : 0);
     o_b[l] = take((size_t)Q * h->width[l + 1] * 4);
   }
   const size_t cat_el = n_models > 1 ? (size_t)S * h->Fp * n_models * h->width[1] : 0;
-  const size_t o_wt0cf = take(cat_el * 4);
-  const size_t o_wt0cq = take(cat_el * 2);
+  const size_t o_wt0c = take(cat_el * ew);
   const size_t o_wout = take((size_t)Q * h->width[3] * 4);
   const size_t o_bout = take((size_t)Q * 4);
   const size_t o_eself = take(kMaxS * 8);
@@ -787,16 +765,23 @@ nnp_status nnp_create_ensemble(const nnp_aev_params* aev, const nnp_mlp_params* 
   }
   h->flat = reinterpret_cast<float*>(h->dmem + o_flat);
   for (int l = 0; l < kLayers - 1; ++l) {
-    h->Wf[l] = reinterpret_cast<float*>(h->dmem + o_wf[l]);
-    h->Wb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_wb[l]);
-    h->WTf[l] = reinterpret_cast<float*>(h->dmem + o_wtf[l]);
-    h->Wqb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_wqb[l]);
-    h->WTqb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_wtqb[l]);
+    if (bf) {
+      if (rows) h->Wb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_w[l]);
+      h->Wqb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_wq[l]);
+      h->WTqb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_wtq[l]);
+    } else if (rows) {
+      h->Wf[l] = reinterpret_cast<float*>(h->dmem + o_w[l]);
+      h->WTf[l] = reinterpret_cast<float*>(h->dmem + o_wt[l]);
+    } else {
+      h->Wqf[l] = reinterpret_cast<float*>(h->dmem + o_wq[l]);
+      h->WTqf[l] = reinterpret_cast<float*>(h->dmem + o_wtq[l]);
+    }
     h->bias[l] = reinterpret_cast<float*>(h->dmem + o_b[l]);
   }
   if (n_models > 1) {
-    h->WT0cf = reinterpret_cast<float*>(h->dmem + o_wt0cf);
-    h->WT0cq = reinterpret_cast<bf16_t*>(h->dmem + o_wt0cq);
+    if (bf) h->WT0cq = reinterpret_cast<bf16_t*>(h->dmem + o_wt0c);
+    else if (rows) h->WT0cf = reinterpret_cast<float*>(h->dmem + o_wt0c);
+    else h->WT0cqf = reinterpret_cast<float*>(h->dmem + o_wt0c);
   }
   h->wout = reinterpret_cast<float*>(h->dmem + o_wout);
   h->bout = reinterpret_cast<float*>(h->dmem + o_bout);
@@ -860,6 +845,7 @@ nnp_status nnp_set_params_device(nnp_handle* h, const float* params_dev, void* s
   p.n_models = h->n_models;
   p.WT0cf = h->WT0cf;
   p.WT0cq = h->WT0cq;
+  p.WT0cqf = h->WT0cqf;
   for (int l = 0; l <= kLayers; ++l) p.width[l] = h->width[l];
   p.width[0] = h->F;
   p.Fp = h->Fp;
@@ -871,6 +857,8 @@ nnp_status nnp_set_params_device(nnp_handle* h, const float* params_dev, void* s
     p.WTf[l] = h->WTf[l];
     p.Wqb[l] = h->Wqb[l];
     p.WTqb[l] = h->WTqb[l];
+    p.Wqf[l] = h->Wqf[l];
+    p.WTqf[l] = h->WTqf[l];
     p.bias[l] = h->bias[l];
   }
   p.wout = h->wout;

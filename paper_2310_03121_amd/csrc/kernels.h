@@ -44,43 +44,58 @@ struct GemmArgs {
   const unsigned long long* kmask_n = nullptr;
 };
 
-struct MidArgs {
+// The fused network (mlp_net.h).  Weights in fragment order, weight slot
+// member * S + element; T is the operand type of the launch.
+struct NetArgs {
   const GroupTable* gt;
-  const bf16_t* H1;               // [rows][W1]
-  const bf16_t* W1;               // [S][W2][W1], fragment order
-  const bf16_t* W2;               // [S][W3][W2], fragment order
-  const bf16_t* W2T;              // [S][W2][W3], fragment order
-  const bf16_t* W1T;              // [S][W1][W2], fragment order
-  const float* b1;                // [S][W2]
-  const float* b2;                // [S][W3]
-  const float* wout;              // [S][W3]
-  const float* bout;              // [S]
-  float* erow;                    // [atoms] atomic energies, input atom order
-  bf16_t* D1;                     // [rows][ld_d1], columns [0, W1)
-  bf16_t* H2;                     // optional [rows][W2]
-  bf16_t* H3;                     // optional [rows][W3]
-  bf16_t* D3;                     // optional [rows][W3]
-  bf16_t* D2;                     // optional [rows][W2]
-  float* uprow;                   // optional [rows]
-  const int* perm;
-  const int* mol;
-  const double* dLdE;
+  int S;
+  const void* X;                  // [rows][ldx] feature rows (T)
+  int ldx;                        // row stride of X and G, layer 1's K (a multiple of 32)
+  const unsigned long long* kmask;  // [rows]: the k-steps (32 columns of X) that may be
+                                    // nonzero; X is read, and G written, only there
+  const void* W0;                 // [slots][W1][ldx]
+  const void* W1;                 // [slots][W2][W1]
+  const void* W2;                 // [slots][W3][W2]
+  const void* W2T;                // [slots][W2][W3]
+  const void* W1T;                // [slots][W1][W2]
+  const void* W0T;                // [slots][ldx][W1]
+  const float* b0;                // [slots][W1]
+  const float* b1;                // [slots][W2]
+  const float* b2;                // [slots][W3]
+  const float* wout;              // [slots][W3]
+  const float* bout;              // [slots]
   float alpha;
-  float inv_alpha_l2e;
-  float escale = 1.f;             // factor on the upstream gradient (1 / ensemble size)
-  int ld_d1 = 0;                  // row stride of D1 (0: W1)
-  // the whole network per tile (k_mlp_net): layer 1 from X, dE/dG into G
-  const bf16_t* X = nullptr;      // [rows][ldx] feature rows
-  int ldx = 0;                    // row stride of X and G, layer 1's K (a multiple of 256)
-  const bf16_t* W0 = nullptr;     // [S][W1][ldx], fragment order
-  const float* b0 = nullptr;      // [S][W1]
-  bf16_t* H1out = nullptr;        // [rows][W1]: H1, stored when D1 is (the weight gradients)
-  const bf16_t* W0T = nullptr;    // [S][ldx][W1], fragment order
-  bf16_t* G = nullptr;            // [rows][ldx] dE/dG, or null (no forces)
-  // optional [rows]: per row, the k-steps (32 columns of X) that may be
-  // nonzero (launch_aev_fwd's kmask); X is read, and G written, only there.
-  // Null: every k-step (ldx <= 2048 either way).
-  const unsigned long long* kmask = nullptr;
+  float inv_alpha_l2e;            // log2(e) / alpha
+  float escale;                   // factor on the upstream gradient (1 / ensemble size)
+  const int* perm;                // sorted row -> atom
+  const int* mol;                 // atom -> molecule
+  const double* dLdE;             // per-molecule upstream gradient, or null for ones
+  float* erow;                    // [members][erow_stride] atomic energies, input atom order
+  long erow_stride;
+  bool bwd;                       // gradients wanted (D1, and G when set)
+  void* G;                        // [rows][ldx] dE/dG, or null
+  void* D1;                       // optional [rows][ld_d1], member k at columns k * W1
+  int ld_d1;
+  // the weight gradients' operands, all or none ([rows][width]; D1 too)
+  void* H1;
+  void* H2;
+  void* H3;
+  void* D3;
+  void* D2;
+  float* uprow;                   // [rows] upstream gradient of each row
+};
+
+// dE/dG of an ensemble: G = D1 Wc over the members' delta1 side by side
+// (lda = K = members * W1), Wc the member-concatenated W_0^T in fragment order
+// [S][ldx][K].  Each row is written on its own k-steps.
+struct NetGradArgs {
+  const GroupTable* gt;
+  const void* D1;
+  int K;
+  const void* Wc;
+  const unsigned long long* kmask;
+  void* G;
+  int ldx;
 };
 
 // Weight slots: member k of an ensemble, element s -> slot k * S + s.
@@ -89,16 +104,22 @@ struct PackArgs {
   long off[kMaxModels * kMaxS * kLayers];  // flat offset of W for (slot, layer)
   int S;                  // elements (slot = member * S + element)
   int n_models;
-  float* WT0cf;           // ensembles: [S][F_pad][M * width1] member-concatenated W_0^T
-  bf16_t* WT0cq;          // the same in MFMA fragment order (N = F_pad, K = M * width1)
+  // ensembles: [S][F_pad][M * width1] member-concatenated W_0^T, row-major
+  // (FP32) or in MFMA fragment order (N = F_pad, K = M * width1)
+  float* WT0cf;
+  bf16_t* WT0cq;
+  float* WT0cqf;
   int width[kLayers + 1];
   int Fp;
   int r0, a0;             // layer 1: inputs from r0 on sit at columns from a0 on
+  // null: not wanted
   float* Wf[kLayers];     // W [slots][out][in_pad], row-major
   bf16_t* Wb[kLayers];
-  float* WTf[kLayers];    // W^T [S][in_pad][out], row-major
+  float* WTf[kLayers];    // W^T [slots][in_pad][out], row-major
   bf16_t* Wqb[kLayers];   // W in MFMA fragment order (N = out, K = in_pad)
   bf16_t* WTqb[kLayers];  // W^T in MFMA fragment order (N = in_pad, K = out)
+  float* Wqf[kLayers];
+  float* WTqf[kLayers];
   float* bias[kLayers];
   float* wout;
   float* bout;
@@ -211,12 +232,20 @@ void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
                       const long* param_off_dev, hipStream_t st);
 void launch_pack(const PackArgs& p, int slots, hipStream_t st);
 
-// mlp_mid.hip
-bool launch_mlp_mid(const int* width, const MidArgs& a, int rows_cap, hipStream_t st);
-// Layer 1, the fused middle and dE/dG in one launch (one workgroup per
-// 128-row tile; H1 and D1 stay in LDS).  Widths 1008-256-192-160 with a
-// padded feature count that is a multiple of 256; returns false otherwise.
-bool launch_mlp_net(const int* width, const MidArgs& a, int rows_cap, hipStream_t st);
+// mlp_net_*.hip: the whole network of a row tile in one workgroup, every
+// member of an ensemble in one launch (then launch_net_grad for dE/dG).
+// Hidden widths 256-192-160 and 160-128-96, feature rows of at most 2,048
+// columns; n_rows: atoms (the tile size follows from it).
+inline bool net_widths(const int* width, int ldx) {
+  return ldx % 32 == 0 && ldx <= 2048 &&
+         ((width[1] == 256 && width[2] == 192 && width[3] == 160) ||
+          (width[1] == 160 && width[2] == 128 && width[3] == 96));
+}
+template <typename T>
+bool launch_mlp_net(const int* width, const NetArgs& a, int n_rows, int rows_cap, int members,
+                    hipStream_t st);
+template <typename T>
+void launch_net_grad(const NetGradArgs& a, int rows_cap, hipStream_t st);
 
 // md.hip
 void launch_vv_kick_drift(const int* dims, int n_cap, double* x, double* v, const float* F,

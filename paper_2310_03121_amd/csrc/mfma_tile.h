@@ -10,10 +10,12 @@
 // of C: lane l has row l % 16 and columns 4 * (l / 16) + {0, 1, 2, 3} of each
 // 16 x 16 tile, so epilogues store 4-column vectors.
 //
-// Fragment of a k-step (16 bytes per lane, BF16): lane l holds row l % 16 of
-// its 16-row slice, elements [8 * (l / 16), +8) of the k-step's 32 (one
-// v_mfma_f32_16x16x32_bf16).  A is read that way from row-major LDS; B is
-// pre-packed so that the 64 lanes' fragments are contiguous.
+// Fragment of a k-step (16 bytes per lane): lane l holds row l % 16 of its
+// 16-row slice, for BF16 elements [8 * (l / 16), +8) of the k-step's 32 (one
+// v_mfma_f32_16x16x32_bf16), for FP32 elements [4 * (l / 16), +4) of 16 (four
+// v_mfma_f32_16x16x4f32, component c feeding the c-th).  A is read that way
+// from row-major LDS; B is pre-packed so that the 64 lanes' fragments are
+// contiguous.
 #pragma once
 #include "kernels.h"
 
@@ -36,6 +38,18 @@ template <> struct Frag<bf16_t> {
   __device__ __forceinline__ static void mma(const uint4& b, const uint4& a, f32x4_t& acc) {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b),
                                                   __builtin_bit_cast(bf16x8_t, a), acc, 0, 0, 0);
+  }
+};
+
+template <> struct Frag<float> {
+  static constexpr int KS = 16;
+  static constexpr int EL = 4;
+  __device__ __forceinline__ static void mma(const uint4& b, const uint4& a, f32x4_t& acc) {
+    const float4 vb = __builtin_bit_cast(float4, b), va = __builtin_bit_cast(float4, a);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vb.x, va.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vb.y, va.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vb.z, va.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vb.w, va.w, acc, 0, 0, 0);
   }
 };
 
@@ -136,56 +150,6 @@ struct BRingQ {
   __device__ __forceinline__ void next_pass(const T*, int, int) {}  // one pass only
 };
 
-// A ring for a product whose four 16-column tiles come in two pairs at
-// arbitrary places: tiles (2 c0, 2 c0 + 1, 2 c1, 2 c1 + 1) of B (K dense,
-// ns = K / KS steps, a multiple of P).  Steps from ns on read the next
-// pass's pair of pairs, as BRing does.
-template <typename T, int P>
-struct BRingPair {
-  static constexpr int FE = 64 * Frag<T>::EL;
-  uint4 r[P][4];
-  const T* b0;
-  const T* b1;   // this pass
-  const T* n0;
-  const T* n1;   // the next one
-  size_t tile;
-  int ns;
-  __device__ __forceinline__ const T* at(const T* B, int c, int lane) const {
-    return B + (size_t)(2 * c) * tile + lane * Frag<T>::EL;
-  }
-  __device__ __forceinline__ void init(const T* B, int K, int lane, int c0, int c1, int d0,
-                                       int d1) {
-    ns = K / Frag<T>::KS;
-    tile = (size_t)ns * FE;
-    b0 = at(B, c0, lane);
-    b1 = at(B, c1, lane);
-    n0 = at(B, d0, lane);
-    n1 = at(B, d1, lane);
-  }
-  __device__ __forceinline__ void next_pass(const T* B, int d0, int d1, int lane) {
-    b0 = n0;
-    b1 = n1;
-    n0 = at(B, d0, lane);
-    n1 = at(B, d1, lane);
-  }
-  template <int U>
-  __device__ __forceinline__ void load(int s) {
-    const T* p0 = s < ns ? b0 + (size_t)s * FE : n0 + (size_t)(s - ns) * FE;
-    const T* p1 = s < ns ? b1 + (size_t)s * FE : n1 + (size_t)(s - ns) * FE;
-    r[U][0] = *reinterpret_cast<const uint4*>(p0);
-    r[U][1] = *reinterpret_cast<const uint4*>(p0 + tile);
-    r[U][2] = *reinterpret_cast<const uint4*>(p1);
-    r[U][3] = *reinterpret_cast<const uint4*>(p1 + tile);
-  }
-  template <int U = 0>
-  __device__ __forceinline__ void prologue() {
-    if constexpr (U < P) {
-      load<U>(U);
-      prologue<U + 1>();
-    }
-  }
-};
-
 template <int TM>
 __device__ __forceinline__ void load_a(const unsigned char* arow, int astride16, uint4 (&fa)[TM]) {
 #pragma unroll
@@ -229,9 +193,9 @@ __device__ __forceinline__ void kgroup(const unsigned char* ap, int astride16, R
 // All NS k-steps of a product with compile-time K, fully unrolled: slot
 // refills stop at the last step, so no load is wasted.  The two A fragment
 // sets alternate by step parity.
-template <typename T, int TM, int TN, int P, int NS, int S = 0>
+template <typename T, int TM, int TN, int P, int NS, int S = 0, typename Ring>
 __device__ __forceinline__ void ksteps_ct(const unsigned char* a0, int astride16,
-                                          BRing<T, TN, P>& br, f32x4_t (&acc)[TM][TN],
+                                          Ring& br, f32x4_t (&acc)[TM][TN],
                                           uint4 (&fe)[TM], uint4 (&fo)[TM]) {
   if constexpr (S < NS) {
     constexpr int SB = Frag<T>::KS * sizeof(T);

@@ -1231,11 +1231,12 @@ template void launch_wgrad_net<bf16_t>(const GroupTable*, int, int, int, const W
 // ------------------------------------------------------------ weight packing
 //
 // From the flat parameter vector (per species, per layer: W row-major
-// out x in, then b) to: W_l [S][out][in_pad] row-major (float and bf16) and
+// out x in, then b) to the copies that the handle's kernels read (the others
+// are null): W_l [S][out][in_pad] row-major (float or bf16) and
 // W_l^T [S][in_pad][out] row-major (float), the LDS-staged kernels' operands;
-// W_l and W_l^T in MFMA fragment order (bf16), the register-streamed
-// kernels' operands; biases [S][out], output weights [S][w3] and output
-// biases [S].  One thread per (species, layer, out, in_pad).
+// W_l and W_l^T in MFMA fragment order (bf16 or float), the fused network's
+// and the register-streamed kernels' operands; biases [S][out], output
+// weights [S][w3] and output biases [S].  One thread per (species, layer, out, in_pad).
 //
 // Fragment order of a [N][K] operand: 16-row tiles, then k-steps of KS, then
 // the 64 lanes of the wave, then the EL elements of a lane; lane l of k-step
@@ -1263,18 +1264,25 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs p) {
     const bool on = pi < in && (l != 0 || i < p.r0 || i >= p.a0);
     const float v = on ? src[(size_t)o * in + pi] : 0.f;
     const size_t ws = (size_t)s * out * inp;
-    p.Wf[l][ws + (size_t)o * inp + i] = v;
-    p.Wb[l][ws + (size_t)o * inp + i] = f2bf(v);
-    p.WTf[l][ws + (size_t)i * out + o] = v;
-    p.Wqb[l][ws + frag_off<bf16_t>(o, i, inp)] = f2bf(v);
-    p.WTqb[l][ws + frag_off<bf16_t>(i, o, out)] = f2bf(v);
+    if (p.Wf[l]) p.Wf[l][ws + (size_t)o * inp + i] = v;
+    if (p.Wb[l]) p.Wb[l][ws + (size_t)o * inp + i] = f2bf(v);
+    if (p.WTf[l]) p.WTf[l][ws + (size_t)i * out + o] = v;
+    if (p.Wqb[l]) {
+      p.Wqb[l][ws + frag_off<bf16_t>(o, i, inp)] = f2bf(v);
+      p.WTqb[l][ws + frag_off<bf16_t>(i, o, out)] = f2bf(v);
+    }
+    if (p.Wqf[l]) {
+      p.Wqf[l][ws + frag_off<float>(o, i, inp)] = v;
+      p.WTqf[l][ws + frag_off<float>(i, o, out)] = v;
+    }
     if (i == 0) p.bias[l][(size_t)s * out + o] = src[(size_t)out * in + o];
     if (l == 0 && p.n_models > 1) {
       // member k's W_0^T as columns [k out, (k + 1) out) of one K = M out operand
       const int k = s / p.S, e = s % p.S, KM = p.n_models * out;
       const size_t wc = (size_t)e * inp * KM;
-      p.WT0cf[wc + (size_t)i * KM + (size_t)k * out + o] = v;
-      p.WT0cq[wc + frag_off<bf16_t>(i, k * out + o, KM)] = f2bf(v);
+      if (p.WT0cf) p.WT0cf[wc + (size_t)i * KM + (size_t)k * out + o] = v;
+      if (p.WT0cq) p.WT0cq[wc + frag_off<bf16_t>(i, k * out + o, KM)] = f2bf(v);
+      if (p.WT0cqf) p.WT0cqf[wc + frag_off<float>(i, k * out + o, KM)] = v;
     }
   } else {
     if (t >= in) return;

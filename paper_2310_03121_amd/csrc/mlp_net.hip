@@ -1,0 +1,181 @@
+// Dispatch of the fused network by operand type and hidden widths, and dE/dG
+// of ensembles.
+#include "mlp_net.h"
+
+namespace nnp {
+
+void launch_net_bf16_7(const NetArgs&, int, int, int, hipStream_t);
+void launch_net_bf16_4(const NetArgs&, int, int, int, hipStream_t);
+void launch_net_fp32_7(const NetArgs&, int, int, int, hipStream_t);
+void launch_net_fp32_4(const NetArgs&, int, int, int, hipStream_t);
+
+template <typename T>
+bool launch_mlp_net(const int* width, const NetArgs& a, int n_rows, int rows_cap, int members,
+                    hipStream_t st) {
+  if (!net_widths(width, a.ldx) || !a.X || !a.kmask) return false;
+  if (a.H1 && !(a.H2 && a.H3 && a.D3 && a.D2 && a.D1 && a.uprow)) return false;
+  const bool seven = width[1] == 256;
+  if constexpr (sizeof(T) == 2)
+    (seven ? launch_net_bf16_7 : launch_net_bf16_4)(a, n_rows, rows_cap, members, st);
+  else
+    (seven ? launch_net_fp32_7 : launch_net_fp32_4)(a, n_rows, rows_cap, members, st);
+  return true;
+}
+template bool launch_mlp_net<bf16_t>(const int*, const NetArgs&, int, int, int, hipStream_t);
+template bool launch_mlp_net<float>(const int*, const NetArgs&, int, int, int, hipStream_t);
+
+// ------------------------------------------------------- dE/dG of an ensemble
+//
+// One workgroup per 64-row tile and group of 4 UN active k-steps of the
+// tile's rows (32 columns of G each, UN per wave): the members' delta1 stream
+// through two LDS chunk buffers, the weights through the register ring.  The
+// members are summed inside the FP32 accumulator, in member order.
+template <typename T, int UN, int P>
+struct GradRing {
+  static constexpr int FB = 64 * 16;
+  uint4 r[P][2 * UN];
+  const unsigned char* base[UN];
+  unsigned lane16, tile;
+  int ns;
+  __device__ __forceinline__ void init(const T* B, int K, int lane, const int (&q)[UN]) {
+    ns = K / Frag<T>::KS;
+    tile = (unsigned)ns * FB;
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      base[u] = reinterpret_cast<const unsigned char*>(B) + (size_t)(2 * q[u]) * tile;
+    lane16 = (unsigned)lane * 16;
+  }
+  template <int U>
+  __device__ __forceinline__ void load(int s) {
+    const unsigned at = (unsigned)(s < ns ? s : ns - 1) * FB;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      r[U][2 * u] = *reinterpret_cast<const uint4*>(base[u] + at + lane16);
+      r[U][2 * u + 1] = *reinterpret_cast<const uint4*>(base[u] + (at + tile) + lane16);
+    }
+  }
+  template <int U = 0>
+  __device__ __forceinline__ void prologue() {
+    if constexpr (U < P) {
+      load<U>(U);
+      prologue<U + 1>();
+    }
+  }
+};
+
+template <typename T, int UN>
+__global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
+  constexpr int BM = 64, NTH = 256, ES = sizeof(T), TM = BM / 16;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BM * kNetChunkStride];
+  __shared__ unsigned long long rmask[BM];
+  const GroupTable* gt = a.gt;
+  const int nt = gt->total_rows / BM;
+  if ((int)blockIdx.x >= nt) return;
+  const int row0 = xcd_tile(blockIdx.x, nt) * BM;
+  const int s = tile_species(gt, row0);
+  const int row_end = gt->pstart[s] + gt->cnt[s];
+  if (row0 >= row_end) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rl = lane & 15, cq = (lane >> 4) * 4;
+  const int K = a.K, ldx = a.ldx;
+  const int nks = ldx / 32;
+  const unsigned long long all = nks >= 64 ? ~0ull : (1ull << nks) - 1ull;
+  const unsigned long long m = row0 + lane < row_end ? a.kmask[row0 + lane] & all : 0ull;
+  if (tid < BM) rmask[tid] = m;
+  unsigned lo = (unsigned)m, hi = (unsigned)(m >> 32);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    lo |= __shfl_xor(lo, d, 64);
+    hi |= __shfl_xor(hi, d, 64);
+  }
+  const unsigned long long U = ((unsigned long long)__builtin_amdgcn_readfirstlane(hi) << 32) |
+                               (unsigned)__builtin_amdgcn_readfirstlane(lo);
+  const int nact = __popcll(U);
+  const int p0 = (int)blockIdx.y * 4 * UN;
+  if (p0 >= nact) return;  // block-uniform
+  const int qlist = nth_set_bit(U, lane);
+  int q[UN];
+#pragma unroll
+  for (int u = 0; u < UN; ++u) {
+    const int p = p0 + wv * UN + u;
+    q[u] = __builtin_amdgcn_readlane(qlist, p < nact ? p : nact - 1);
+  }
+
+  const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(static_cast<const T*>(a.D1) + (size_t)row0 * K), (short)0,
+      (row_end - row0) * K * ES, kBufferRsrcWord3);
+  constexpr int RPV = NTH / 16, NVA = BM / RPV;
+  auto aload = [&](int c, uint4 (&ra)[NVA]) __attribute__((always_inline)) {
+    const int col = c * (kNetChunk / ES) + (tid & 15) * (16 / ES);
+#pragma unroll
+    for (int v = 0; v < NVA; ++v) {
+      const int r = (tid >> 4) + RPV * v;
+      const unsigned off = col < K ? (unsigned)((r * K + col) * ES) : kOutOfRange;
+      const u32x4_t val = __builtin_amdgcn_raw_buffer_load_b128(arsrc, off, 0, 0);
+      ra[v] = make_uint4(val[0], val[1], val[2], val[3]);
+    }
+  };
+  auto astore = [&](int buf, const uint4 (&ra)[NVA]) __attribute__((always_inline)) {
+    unsigned char* base = smem + buf * BM * kNetChunkStride;
+#pragma unroll
+    for (int v = 0; v < NVA; ++v)
+      *reinterpret_cast<uint4*>(base + ((tid >> 4) + RPV * v) * kNetChunkStride + (tid & 15) * 16) =
+          ra[v];
+  };
+  GradRing<T, UN, 4> br;
+  br.init(static_cast<const T*>(a.Wc) + (size_t)s * ldx * K, K, lane, q);
+  br.prologue();
+  uint4 ra0[NVA], ra1[NVA];
+  const int nu = (K * ES + kNetChunk - 1) / kNetChunk;
+  aload(0, ra0);
+  aload(1 < nu ? 1 : 0, ra1);
+  f32x4_t acc[TM][2 * UN];
+  zero_acc(acc);
+  astore(0, ra0);
+  __syncthreads();
+  const int arow = rl * kNetChunkStride + (lane >> 4) * 16;
+  auto unit = [&](int u, uint4 (&r_next2)[NVA], const uint4 (&r_next1)[NVA])
+                  __attribute__((always_inline)) {
+    aload(u + 2 < nu ? u + 2 : nu - 1, r_next2);
+    kgroup<T, TM, 2 * UN, 4>(smem + (u & 1) * BM * kNetChunkStride + arow, 16 * kNetChunkStride, br,
+                             u * 4, acc);
+    astore((u + 1) & 1, r_next1);
+    __syncthreads();
+  };
+  for (int u = 0; u < nu; u += 2) {
+    unit(u, ra0, ra1);
+    if (u + 1 < nu) unit(u + 1, ra1, ra0);
+  }
+#pragma unroll
+  for (int u = 0; u < UN; ++u) {
+    if (p0 + wv * UN + u >= nact) break;  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int r = i * 16 + rl;
+      if (row0 + r < row_end && ((rmask[r] >> q[u]) & 1ull)) {
+        T* g = static_cast<T*>(a.G) + (size_t)(row0 + r) * ldx + q[u] * 32 + cq;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const f32x4_t v = acc[i][2 * u + j];
+          Store<T>::put4(g + j * 16, make_float4(v[0], v[1], v[2], v[3]));
+        }
+      }
+    }
+  }
+}
+
+template <typename T>
+void launch_net_grad(const NetGradArgs& a, int rows_cap, hipStream_t st) {
+  const int tiles = rows_cap / 64, nks = a.ldx / 32;
+  // two k-steps per wave where the tiles alone fill the GPU (the deltas are
+  // read once per eight k-steps then), else one
+  if (tiles >= 256)
+    hipLaunchKernelGGL((k_net_grad<T, 2>), dim3(tiles, (nks + 7) / 8), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_net_grad<T, 1>), dim3(tiles, (nks + 3) / 4), dim3(256), 0, st, a);
+}
+template void launch_net_grad<bf16_t>(const NetGradArgs&, int, hipStream_t);
+template void launch_net_grad<float>(const NetGradArgs&, int, hipStream_t);
+
+}  // namespace nnp

@@ -1,0 +1,10 @@
+// BF16 networks of hidden widths 160-128-96.
+#include "mlp_net.h"
+
+namespace nnp {
+
+void launch_net_bf16_4(const NetArgs& a, int n_rows, int rows_cap, int members, hipStream_t st) {
+  launch_net_w<bf16_t, 160, 128, 96>(a, n_rows, rows_cap, members, st);
+}
+
+}  // namespace nnp
