@@ -27,14 +27,16 @@
 // is resident at once (two workgroups of 80 KB LDS per CU), and each of its
 // products is short, so the time is the sum of the products' latencies and of
 // the epilogues' vector work.  Hence: the next product's weight fragments are
-// requested before an epilogue (BF16: all of them), biases, upstream
-// gradients and row indices before the products that need them, CELU has no
-// branch, and conversions to BF16 are packed.  Measured per evaluation,
-// BF16 batch: 42.3 -> 39.0 us; FP32 batch, which ran one GEMM per layer with
+// requested between the tiles of an epilogue (BF16: all of them; in one burst
+// before it they queue for 1.6 us behind each other, 64 bytes per clock and
+// CU, and the epilogue's arithmetic waits), biases, upstream gradients and
+// row indices before the products that need them, CELU has no branch, and
+// conversions to BF16 are packed.  Measured per evaluation,
+// BF16 batch: 42.3 -> 37.7 us; FP32 batch, which ran one GEMM per layer with
 // activations through HBM: 342 -> 233 us (the matrix rate a large FP32
 // product reaches, 154 TFLOP/s, allows about 180); one 24-atom molecule in
 // FP32: 108 -> 20 us; an eight-network ensemble, which ran two launches per
-// member: 603 -> 298 us on the batch, 403 -> 33 us on one 53-atom molecule.
+// member: 603 -> 279 us on the batch, 403 -> 33 us on one 53-atom molecule.
 //
 // Every row's result is independent of the tile it sits in: the sums over K
 // run in the same order for every tile size, and the energy's sum over the
@@ -91,12 +93,22 @@ struct NetRing {
       r[U][j] = *reinterpret_cast<const uint4*>(p + (size_t)(jj * tile) + lane16);
     }
   }
-  template <int NS, int U = 0>
-  __device__ __forceinline__ void prologue() {
-    if constexpr (U < P && U < NS) {
-      load<U>(U);
-      prologue<NS, U + 1>();
-    }
+  // fragment f of the first min(P, NS) steps (f a constant after unrolling):
+  // the epilogue before the product asks for a few after each of its tiles
+  __device__ __forceinline__ void fetch(int f) {
+    const int u = f / TN, j = f % TN;
+    const unsigned jj = EVEN ? (unsigned)j : (unsigned)(j < jl ? j : jl);
+    const unsigned char* p = base + (unsigned)u * FB;
+    r[u][j] = *reinterpret_cast<const uint4*>(p + (size_t)(jj * tile) + lane16);
+  }
+  // epilogue tile t of NE (0 .. NE - 1) asks for its share
+  template <int NS, int NE>
+  __device__ __forceinline__ void fetch_share(int t) {
+    constexpr int NF = (P < NS ? P : NS) * TN, PER = (NF + NE - 1) / NE;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (t * PER + q < NF) fetch(t * PER + q);
+    __builtin_amdgcn_sched_barrier(0);
   }
 };
 
@@ -354,21 +366,22 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     }
     br1.init(static_cast<const T*>(a.W1) + (size_t)slot * W2 * W1, (wv % C2::WN) * C2::TN, C2::NT,
              W1, lane);
-    br1.template prologue<W1 / KS>();
 #pragma unroll
     for (int i = 0; i < C1::TM; ++i) {
       const int r = wm * C1::TM * 16 + i * 16 + rl;
 #pragma unroll
       for (int j = 0; j < C1::TN; ++j) {
         const int ct = wn * C1::TN + j;
-        if (!C1::even && ct >= C1::NT) break;  // wave-uniform
-        const int c = ct * 16 + cq;
-        const float4 h = make_float4(net_celu(acc[i][j][0] + b[j].x, alpha, ial2e),
-                                     net_celu(acc[i][j][1] + b[j].y, alpha, ial2e),
-                                     net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
-                                     net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
-        LdsV<T>::put(X1 + r * S1 + c * ES, h);
-        if (STORE) Store<T>::put4(static_cast<T*>(a.H1) + (size_t)(row0 + r) * W1 + c, h);
+        if (C1::even || ct < C1::NT) {  // wave-uniform
+          const int c = ct * 16 + cq;
+          const float4 h = make_float4(net_celu(acc[i][j][0] + b[j].x, alpha, ial2e),
+                                       net_celu(acc[i][j][1] + b[j].y, alpha, ial2e),
+                                       net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
+                                       net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
+          LdsV<T>::put(X1 + r * S1 + c * ES, h);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.H1) + (size_t)(row0 + r) * W1 + c, h);
+        }
+        br1.template fetch_share<W1 / KS, C1::TM * C1::TN>(i * C1::TN + j);
       }
     }
   }
@@ -391,21 +404,22 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
                                               16 * S1, br1, acc, fe, fo);
     br2.init(static_cast<const T*>(a.W2) + (size_t)slot * W3 * W2, (wv % C3::WN) * C3::TN, C3::NT,
              W2, lane);
-    br2.template prologue<W2 / KS>();
 #pragma unroll
     for (int i = 0; i < C2::TM; ++i) {
       const int r = wm * C2::TM * 16 + i * 16 + rl;
 #pragma unroll
       for (int j = 0; j < C2::TN; ++j) {
         const int ct = wn * C2::TN + j;
-        if (!C2::even && ct >= C2::NT) break;
-        const int c = ct * 16 + cq;
-        const float4 h = make_float4(net_celu(acc[i][j][0] + b[j].x, alpha, ial2e),
-                                     net_celu(acc[i][j][1] + b[j].y, alpha, ial2e),
-                                     net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
-                                     net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
-        LdsV<T>::put(X2 + r * S2 + c * ES, h);
-        if (STORE) Store<T>::put4(static_cast<T*>(a.H2) + (size_t)(row0 + r) * W2 + c, h);
+        if (C2::even || ct < C2::NT) {  // wave-uniform
+          const int c = ct * 16 + cq;
+          const float4 h = make_float4(net_celu(acc[i][j][0] + b[j].x, alpha, ial2e),
+                                       net_celu(acc[i][j][1] + b[j].y, alpha, ial2e),
+                                       net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
+                                       net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
+          LdsV<T>::put(X2 + r * S2 + c * ES, h);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.H2) + (size_t)(row0 + r) * W2 + c, h);
+        }
+        br2.template fetch_share<W2 / KS, C2::TM * C2::TN>(i * C2::TN + j);
       }
     }
   }
@@ -427,11 +441,9 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     uint4 fe[C3::TM], fo[C3::TM];
     ksteps_ct<T, C3::TM, C3::TN, P2, W2 / KS>(X2 + (wm * C3::TM * 16 + rl) * S2 + (lane >> 4) * 16,
                                               16 * S2, br2, acc, fe, fo);
-    if (BWD) {
+    if (BWD)
       br3.init(static_cast<const T*>(a.W2T) + (size_t)slot * W2 * W3, (wv % C2::WN) * C2::TN,
                C2::NT, W3, lane);
-      br3.template prologue<W3 / KS>();
-    }
 #pragma unroll
     for (int i = 0; i < C3::TM; ++i) {
       const int r = wm * C3::TM * 16 + i * 16 + rl;
@@ -439,31 +451,33 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int j = 0; j < C3::TN; ++j) {
         const int ct = wn * C3::TN + j;
-        if (!C3::even && ct >= C3::NT) break;
-        const int c = ct * 16 + cq;
-        const float bb[4] = {b[j].x, b[j].y, b[j].z, b[j].w};
-        const float ww[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
-        float h[4], d[4];
+        if (C3::even || ct < C3::NT) {  // wave-uniform
+          const int c = ct * 16 + cq;
+          const float bb[4] = {b[j].x, b[j].y, b[j].z, b[j].w};
+          const float ww[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+          float h[4], d[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float z = acc[i][j][e] + bb[e];
-          const float ex = __builtin_amdgcn_exp2f(fminf(z, 0.f) * ial2e);
-          const float neg = alpha * (ex - 1.f);
-          h[e] = z > 0.f ? z : neg;
-          d[e] = up[i] * ww[e] * (z > 0.f ? 1.f : ex);
-          float& sum = ep[HEAD ? e : 0];
-          if (!C3::spread) sum = __builtin_fmaf(ww[e], h[e], sum);
+          for (int e = 0; e < 4; ++e) {
+            const float z = acc[i][j][e] + bb[e];
+            const float ex = __builtin_amdgcn_exp2f(fminf(z, 0.f) * ial2e);
+            const float neg = alpha * (ex - 1.f);
+            h[e] = z > 0.f ? z : neg;
+            d[e] = up[i] * ww[e] * (z > 0.f ? 1.f : ex);
+            float& sum = ep[HEAD ? e : 0];
+            if (!C3::spread) sum = __builtin_fmaf(ww[e], h[e], sum);
+          }
+          const float4 h4 = make_float4(h[0], h[1], h[2], h[3]);
+          const float4 d4 = make_float4(d[0], d[1], d[2], d[3]);
+          if (BWD) LdsV<T>::put(D3s + r * S3 + c * ES, d4);
+          if (C3::spread)
+            *reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(epart) + r * LL::SH + c * 4) =
+                h4;
+          if (STORE) {
+            Store<T>::put4(static_cast<T*>(a.H3) + (size_t)(row0 + r) * W3 + c, h4);
+            Store<T>::put4(static_cast<T*>(a.D3) + (size_t)(row0 + r) * W3 + c, d4);
+          }
         }
-        const float4 h4 = make_float4(h[0], h[1], h[2], h[3]);
-        const float4 d4 = make_float4(d[0], d[1], d[2], d[3]);
-        if (BWD) LdsV<T>::put(D3s + r * S3 + c * ES, d4);
-        if (C3::spread)
-          *reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(epart) + r * LL::SH + c * 4) =
-              h4;
-        if (STORE) {
-          Store<T>::put4(static_cast<T*>(a.H3) + (size_t)(row0 + r) * W3 + c, h4);
-          Store<T>::put4(static_cast<T*>(a.D3) + (size_t)(row0 + r) * W3 + c, d4);
-        }
+        if (BWD) br3.template fetch_share<W3 / KS, C3::TM * C3::TN>(i * C3::TN + j);
       }
       if (STORE && wn == 0 && lane < 16) a.uprow[row0 + r] = row0 + r < row_end ? up[i] : 0.f;
       if constexpr (!C3::spread) {
@@ -526,21 +540,22 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
         D3s + (wm * C2::TM * 16 + rl) * S3 + (lane >> 4) * 16, 16 * S3, br3, acc, fe, fo);
     br4.init(static_cast<const T*>(a.W1T) + (size_t)slot * W1 * W2, (wv % C1::WN) * C1::TN, C1::NT,
              W2, lane);
-    br4.template prologue<W2 / KS>();
 #pragma unroll
     for (int i = 0; i < C2::TM; ++i) {
       const int r = wm * C2::TM * 16 + i * 16 + rl;
 #pragma unroll
       for (int j = 0; j < C2::TN; ++j) {
         const int ct = wn * C2::TN + j;
-        if (!C2::even && ct >= C2::NT) break;
-        const int c = ct * 16 + cq;
-        const float4 h = LdsV<T>::get(X2 + r * S2 + c * ES);
-        const float4 d =
-            make_float4(acc[i][j][0] * celu_slope(h.x, ia), acc[i][j][1] * celu_slope(h.y, ia),
-                        acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
-        LdsV<T>::put(X2 + r * S2 + c * ES, d);
-        if (STORE) Store<T>::put4(static_cast<T*>(a.D2) + (size_t)(row0 + r) * W2 + c, d);
+        if (C2::even || ct < C2::NT) {  // wave-uniform
+          const int c = ct * 16 + cq;
+          const float4 h = LdsV<T>::get(X2 + r * S2 + c * ES);
+          const float4 d =
+              make_float4(acc[i][j][0] * celu_slope(h.x, ia), acc[i][j][1] * celu_slope(h.y, ia),
+                          acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
+          LdsV<T>::put(X2 + r * S2 + c * ES, d);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.D2) + (size_t)(row0 + r) * W2 + c, d);
+        }
+        br4.template fetch_share<W2 / KS, C2::TM * C2::TN>(i * C2::TN + j);
       }
     }
   }
@@ -563,25 +578,24 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     uint4 fe[C1::TM], fo[C1::TM];
     ksteps_ct<T, C1::TM, C1::TN, P2, W2 / KS>(X2 + (wm * C1::TM * 16 + rl) * S2 + (lane >> 4) * 16,
                                               16 * S2, br4, acc, fe, fo);
-    if (a.G && wv < nact) {
-      br5.init(W0T, 2 * qat(wv), K / 16, W1, lane);
-      br5.template prologue<W1 / KS>();
-    }
+    if (a.G) br5.init(W0T, 2 * qat(wv), K / 16, W1, lane);
 #pragma unroll
     for (int i = 0; i < C1::TM; ++i) {
       const int r = wm * C1::TM * 16 + i * 16 + rl;
 #pragma unroll
       for (int j = 0; j < C1::TN; ++j) {
         const int ct = wn * C1::TN + j;
-        if (!C1::even && ct >= C1::NT) break;
-        const int c = ct * 16 + cq;
-        const float4 h = LdsV<T>::get(X1 + r * S1 + c * ES);
-        const float4 d =
-            make_float4(acc[i][j][0] * celu_slope(h.x, ia), acc[i][j][1] * celu_slope(h.y, ia),
-                        acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
-        LdsV<T>::put(X1 + r * S1 + c * ES, d);
-        if (STORE || a.D1)
-          Store<T>::put4(static_cast<T*>(a.D1) + (size_t)(row0 + r) * a.ld_d1 + member * W1 + c, d);
+        if (C1::even || ct < C1::NT) {  // wave-uniform
+          const int c = ct * 16 + cq;
+          const float4 h = LdsV<T>::get(X1 + r * S1 + c * ES);
+          const float4 d =
+              make_float4(acc[i][j][0] * celu_slope(h.x, ia), acc[i][j][1] * celu_slope(h.y, ia),
+                          acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
+          LdsV<T>::put(X1 + r * S1 + c * ES, d);
+          if (STORE || a.D1)
+            Store<T>::put4(static_cast<T*>(a.D1) + (size_t)(row0 + r) * a.ld_d1 + member * W1 + c, d);
+        }
+        if (a.G) br5.template fetch_share<W1 / KS, C1::TM * C1::TN>(i * C1::TN + j);
       }
     }
   }
@@ -596,10 +610,8 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     uint4 fe[GM], fo[GM];
     ksteps_ct<T, GM, 2, P1, W1 / KS>(X1 + rl * S1 + (lane >> 4) * 16, 16 * S1,
                                      br5, acc, fe, fo);
-    if (p + GN < nact) {
-      br5.init(W0T, 2 * qat(p + GN), K / 16, W1, lane);
-      br5.template prologue<W1 / KS>();
-    }
+    br5.init(W0T, 2 * qat(p + GN), K / 16, W1, lane);
+    if (p + GN < nact) br5.template fetch_share<W1 / KS, 1>(0);
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
       const int r = i * 16 + rl;
