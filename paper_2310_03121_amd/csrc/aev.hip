@@ -20,11 +20,10 @@
 // cos(theta - theta_z) = kappa c cos(theta_z) + sqrt(1 - kappa^2 c^2) sin(theta_z)
 // for theta = acos(kappa c); (1 + cos)/2 raised to zeta is exp2(zeta log2(.)).
 //
-// The adjoint recomputes the same terms, contracts them with g = dE/dG
-// (read from the network backward pass, only the blocks the atom touches),
-// accumulates dE/d(displacement) per neighbor slot in LDS, then scatters: one
-// atomic add per neighbor and component for the neighbors, and one
-// wave-reduced add for the centre atom.
+// The adjoint recomputes the same terms and contracts them with g = dE/dG
+// (read from the network backward pass, only the blocks the atom touches).
+// Its radial part is pulled from both sides of a pair, so only the angular
+// neighbors are scattered to.
 #include "kernels.h"
 #include "energy_sum.h"
 
@@ -392,15 +391,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
   }
 }
 
-// Atoms per workgroup of the molecule adjoint.
+// Atoms and waves per workgroup of the molecule adjoint.
 constexpr int kMolBlock = 64;
+constexpr int kMolWaves = 8;
 
-// LDS per wave (adjoint): per neighbor float4 (dx, dy, dz, r), float4
-// (fc_rad, fc_ang, dfc_rad, dfc_ang), float4 accumulated dE/d(displacement),
-// int species.  The dE/dG row is read from global memory where a term needs
-// it (an atom touches only the blocks of the species around it).  Pairs are
-// decoded per lane here: with eight lanes per pair the chunked table of the
-// forward pass measured no gain.
+// LDS per wave (deterministic adjoint): per neighbor float4 (dx, dy, dz, r),
+// float4 (fc_rad, fc_ang, dfc_rad, dfc_ang), float4 accumulated
+// dE/d(displacement), int species.
 constexpr int kBwdBytesPerNbr = 16 + 16 + 16 + 4;
 
 // Sixteen consecutive dE/dG values (one radial species block) as floats.
@@ -482,42 +479,18 @@ __device__ __forceinline__ void adjoint_setup(int slot, const float4 q, bool ang
 }
 
 // The radial and angular passes of one atom (nr neighbors, the first na
-// angular, set up in nd, nf, nsp): dE/d(displacement) of every neighbor
-// entry into grad (the radial pass stores, the angular pass adds).  The
-// angular pass takes one of three forms (Mode):
-//   kAngPairLanes: one lane per pair, 64 pairs per pass (long lists: the
-//     pair's shared terms are computed once, not in eight lanes), and one
-//     lane per neighbor entry in the radial pass;
-//   kAngShiftLanes: eight lanes per pair (one per angle shift), eight pairs
-//     per pass, fewer registers (the fallback of the four-atom kernels);
-//   kAngShiftLanesOrdered: the same, adding the pass's eight pairs' terms one
-//     pair after the other instead of with LDS atomics, so that every
-//     entry's sum has a fixed order (deterministic mode).
-constexpr int kAngPairLanes = 0, kAngShiftLanes = 1, kAngShiftLanesOrdered = 2;
-template <typename GT, int Mode>
-__device__ __forceinline__ void adjoint_passes(int nr, int na, const AevConst& C,
-                                               const GT* __restrict__ grow, const float4* nd,
-                                               const float4* nf, float4* grad, const int* nsp) {
+// angular, set up in nd, nf, nsp): dE/d(displacement) of every neighbor entry
+// into grad (the radial pass stores, the angular pass adds), in an order that
+// depends on the atom's own list only (deterministic mode): eight lanes per
+// angular pair (one per angle shift), eight pairs per pass, whose terms are
+// added one pair after the other.
+template <typename GT>
+__device__ __forceinline__ void adjoint_passes_ordered(int nr, int na, const AevConst& C,
+                                                       const GT* __restrict__ grow,
+                                                       const float4* nd, const float4* nf,
+                                                       float4* grad, const int* nsp) {
   const int lane = lane_id();
   const int S = C.S;
-  if constexpr (Mode == kAngPairLanes) {
-    // ---- radial: one lane per neighbor entry, its 16 shifts against the 16
-    // dE/dG values of its species block (two vector loads)
-    for (int e = lane; e < nr; e += kWave) {
-      const float4 v = nd[e];
-      const float4 f = nf[e];
-      float gv[16];
-      Load16<GT>::get(grow + nsp[e] * kNR, gv);
-      float acc = 0.f;
-#pragma unroll
-      for (int m = 0; m < kNR; ++m) {
-        const float u = v.w - C.shf_r[m];
-        acc += gv[m] * fast_exp2(-C.eta_r_l2e * u * u) * (f.z - C.eta_r2 * u * f.x);
-      }
-      const float sc = C.cR * acc * fast_rcp(v.w);
-      grad[e] = make_float4(v.x * sc, v.y * sc, v.z * sc, 0.f);
-    }
-  } else
   // ---- radial: dE/dr_ij per neighbor, reduced over the 16 shift lanes
   {
     const int gq = lane >> 4, m = lane & 15;
@@ -541,95 +514,6 @@ __device__ __forceinline__ void adjoint_passes(int nr, int na, const AevConst& C
     }
   }
   wave_lds_sync();
-
-  if constexpr (Mode == kAngPairLanes) {
-    // ---- angular: one lane per unordered pair (j, k), 64 pairs per pass.
-    // What the pair's 32 terms share (cosine, sine, the four distance
-    // Gaussians) is computed once; the lane walks the eight angle shifts and
-    // contracts each with the pair block's dE/dG values (one vector load).
-    const int T = na * (na - 1) / 2;
-    const GT* gang = grow + C.A0;
-    for (int t0 = 0; t0 < T; t0 += kWave) {
-      // lanes past the last pair recompute it and add nothing
-      const int t = t0 + lane;
-      const bool valid = t < T;
-      int ej, ek;
-      decode_pair(valid ? t : T - 1, na, ej, ek);
-      const float4 vj = nd[ej], vk = nd[ek];
-      const float4 cj = nf[ej], ck = nf[ek];
-      Block32<GT> gb;
-      gb.load(gang + pair_block(nsp[ej], nsp[ek], S) * 32);
-      const float fj = cj.y, fk = ck.y, dfj = cj.w, dfk = ck.w;
-      const float rj = fast_rcp(vj.w), rk = fast_rcp(vk.w);
-      const float cs = (vj.x * vk.x + vj.y * vk.y + vj.z * vk.z) * (rj * rk);
-      const float kc = C.kappa * cs;
-      const float sn = fast_sqrt(fmaxf(1.f - kc * kc, 1e-12f));
-      const float isn = fast_rcp(sn);
-      const float dbar = 0.5f * (vj.w + vk.w);
-      float e2[kNA], ue2[kNA];
-#pragma unroll
-      for (int a = 0; a < kNA; ++a) {
-        const float u = dbar - C.shf_a[a];
-        e2[a] = fast_exp2(-C.eta_a_l2e * u * u);
-        ue2[a] = u * e2[a];
-      }
-      float X0 = 0.f, X1 = 0.f, Xc = 0.f;
-#pragma unroll
-      for (int z = 0; z < kNZ; ++z) {
-        const float cz = C.lane_tab[kNR + z], sz = C.lane_tab[kNR + kNZ + z];
-        float A0 = 0.f, A1 = 0.f;
-#pragma unroll
-        for (int a = 0; a < kNA; ++a) {
-          A0 += gb.at(a * kNZ + z) * e2[a];
-          A1 -= gb.at(a * kNZ + z) * ue2[a];
-        }
-        const float base_ = 0.5f + 0.5f * (kc * cz + sn * sz);
-        const float pw = fast_exp2(C.zeta * fast_log2(base_));
-        const float df1 = C.zeta * pw * fast_rcp(base_) * (C.kappa * (cz - kc * sz * isn));
-        X0 += 2.f * pw * A0;
-        X1 += 2.f * pw * A1;
-        Xc += df1 * A0;
-      }
-      X1 *= C.eta_a;
-      const float fcc = fj * fk;
-      const float dEdc = Xc * fcc;
-      const float dEdj = X1 * fcc + X0 * dfj * fk;
-      const float dEdk = X1 * fcc + X0 * fj * dfk;
-      const float aj = (dEdj - dEdc * cs * rj) * rj;
-      const float ak = (dEdk - dEdc * cs * rk) * rk;
-      const float bb = dEdc * rj * rk;
-      // Entry j's terms: the pass's pairs of row j are consecutive lanes, so
-      // a segmented sum over that run leaves the row's total in its last lane,
-      // which adds it alone (LDS atomics on one address from up to 16 lanes
-      // would serialize).  Lanes past the last pair lie after it.
-      float sx = aj * vj.x + bb * vk.x, sy = aj * vj.y + bb * vk.y, sz = aj * vj.z + bb * vk.z;
-      const int rs = (ej * (2 * na - ej - 1)) >> 1;  // the row's first pair
-      const int s_lane = (rs > t0 ? rs : t0) - t0;
-      const int re = rs + na - 2 - ej;               // and its last
-      const int e_lane = (re < t0 + kWave - 1 ? re : t0 + kWave - 1) - t0;
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const float ox = __shfl_up(sx, d, kWave), oy = __shfl_up(sy, d, kWave),
-                    oz = __shfl_up(sz, d, kWave);
-        if (lane - d >= s_lane) {
-          sx += ox;
-          sy += oy;
-          sz += oz;
-        }
-      }
-      if (lane == e_lane) {
-        atomicAdd(&grad[ej].x, sx);
-        atomicAdd(&grad[ej].y, sy);
-        atomicAdd(&grad[ej].z, sz);
-      }
-      // entry k's terms: at most one per row, so few lanes share an entry
-      if (valid) {
-        atomicAdd(&grad[ek].x, ak * vk.x + bb * vj.x);
-        atomicAdd(&grad[ek].y, ak * vk.y + bb * vj.y);
-        atomicAdd(&grad[ek].z, ak * vk.z + bb * vj.z);
-      }
-    }
-  } else
   // ---- angular: lanes (t, z), eight unordered pairs per pass
   {
     const int tz = lane & 7, tg = lane >> 3;
@@ -679,29 +563,20 @@ __device__ __forceinline__ void adjoint_passes(int nr, int na, const AevConst& C
         const float aj = (dEdj - dEdc * cs * rj) * rj;
         const float ak = (dEdk - dEdc * cs * rk) * rk;
         const float bb = dEdc * rj * rk;
-        if constexpr (Mode == kAngShiftLanes) {
-          atomicAdd(&grad[ej].x, aj * vj.x + bb * vk.x);
-          atomicAdd(&grad[ej].y, aj * vj.y + bb * vk.y);
-          atomicAdd(&grad[ej].z, aj * vj.z + bb * vk.z);
-          atomicAdd(&grad[ek].x, ak * vk.x + bb * vj.x);
-          atomicAdd(&grad[ek].y, ak * vk.y + bb * vj.y);
-          atomicAdd(&grad[ek].z, ak * vk.z + bb * vj.z);
-        } else {
-          for (int q = 0; q < 8; ++q) {
-            if (tg == q) {
-              float4 a = grad[ej];
-              a.x += aj * vj.x + bb * vk.x;
-              a.y += aj * vj.y + bb * vk.y;
-              a.z += aj * vj.z + bb * vk.z;
-              grad[ej] = a;
-              float4 b = grad[ek];
-              b.x += ak * vk.x + bb * vj.x;
-              b.y += ak * vk.y + bb * vj.y;
-              b.z += ak * vk.z + bb * vj.z;
-              grad[ek] = b;
-            }
-            wave_lds_sync();
+        for (int q = 0; q < 8; ++q) {
+          if (tg == q) {
+            float4 a = grad[ej];
+            a.x += aj * vj.x + bb * vk.x;
+            a.y += aj * vj.y + bb * vk.y;
+            a.z += aj * vj.z + bb * vk.z;
+            grad[ej] = a;
+            float4 b = grad[ek];
+            b.x += ak * vk.x + bb * vj.x;
+            b.y += ak * vk.y + bb * vj.y;
+            b.z += ak * vk.z + bb * vj.z;
+            grad[ek] = b;
           }
+          wave_lds_sync();
         }
       }
     }
@@ -709,225 +584,551 @@ __device__ __forceinline__ void adjoint_passes(int nr, int na, const AevConst& C
   wave_lds_sync();
 }
 
-// The adjoint of atoms i0 .. i0 + 3, by one wave: dE/d(displacement) of every
-// neighbor entry into the wave's LDS region (max(64, cap) entries of nd, nf,
-// grad, nsp), then put(j, x, y, z) adds -sign * dE/dv to neighbor j and
-// +sign * the sum to the centre atom.
+// One unordered pair of angular neighbors (j, k) of an atom, in one lane: the
+// derivative of the pair's 32 terms, contracted with the pair block's dE/dG
+// values gb.at(8 a + z), as dE/dv_j = aj v_j + bb v_k and dE/dv_k = ak v_k +
+// bb v_j.  What the terms share (cosine, sine, the four distance Gaussians) is computed once;
+// base^(zeta - 1) serves the value (times base) and the derivative, so an
+// angle shift costs one logarithm and one exponential.
+template <typename Blk>
+__device__ __forceinline__ void adjoint_pair(const AevConst& C, const Blk& gb, const float4 vj,
+                                             const float4 vk, float fj, float dfj, float fk,
+                                             float dfk, float& aj, float& ak, float& bb) {
+  const float rj = fast_rcp(vj.w), rk = fast_rcp(vk.w);
+  const float cs = (vj.x * vk.x + vj.y * vk.y + vj.z * vk.z) * (rj * rk);
+  const float kc = C.kappa * cs;
+  const float sn = fast_sqrt(fmaxf(1.f - kc * kc, 1e-12f));
+  const float kci = kc * fast_rcp(sn);
+  const float dbar = 0.5f * (vj.w + vk.w);
+  float e2[kNA], ue2[kNA];
+#pragma unroll
+  for (int a = 0; a < kNA; ++a) {
+    const float u = dbar - C.shf_a[a];
+    e2[a] = fast_exp2(-C.eta_a_l2e * u * u);
+    ue2[a] = u * e2[a];
+  }
+  const float zm1 = C.zeta - 1.f;
+  float X0 = 0.f, X1 = 0.f, Xc = 0.f;
+#pragma unroll
+  for (int z = 0; z < kNZ; ++z) {
+    float A0 = 0.f, A1 = 0.f;
+#pragma unroll
+    for (int a = 0; a < kNA; ++a) {
+      A0 += gb.at(a * kNZ + z) * e2[a];
+      A1 += gb.at(a * kNZ + z) * ue2[a];
+    }
+    const float base_ = 0.5f + 0.5f * (kc * C.cos_z[z] + sn * C.sin_z[z]);
+    const float q = fast_exp2(zm1 * fast_log2(base_));
+    const float qa = q * A0;
+    X0 += qa * base_;
+    X1 += (q * base_) * A1;
+    Xc += qa * (C.cos_z[z] - kci * C.sin_z[z]);
+  }
+  X0 *= 2.f;
+  X1 *= -2.f * C.eta_a;
+  Xc *= C.zeta * C.kappa;
+  const float fcc = fj * fk;
+  const float dEdc = Xc * fcc;
+  const float dEdj = X1 * fcc + X0 * dfj * fk;
+  const float dEdk = X1 * fcc + X0 * fj * dfk;
+  aj = (dEdj - dEdc * cs * rj) * rj;
+  ak = (dEdk - dEdc * cs * rk) * rk;
+  bb = dEdc * rj * rk;
+}
+
+// dE/dG values of an angular pair block staged in LDS as floats.
+struct BlockLds {
+  const float* p;
+  __device__ __forceinline__ float at(int k) const { return p[k]; }
+};
+
+constexpr int kAdjEnt = 64;        // angular entries in LDS
+constexpr int kAdjPairs = 192;     // pairs whose results the LDS holds at a time
+constexpr int kAdjBlk = 6;         // staged pair blocks: three elements among the neighbors
+constexpr int kAdjBlkStride = 36;  // floats (neighboring blocks start four banks apart)
+
+// LDS of one wave of the adjoint, one atom at a time.
+struct AdjLds {
+  float4 nd[kAdjEnt];              // displacement, distance
+  float2 nf[kAdjEnt];              // angular cutoff value and derivative
+  int nj[kAdjEnt];                 // neighbor atom
+  int nsp[kAdjEnt];                // element, or its rank among the neighbors' elements
+  float tab[3][kAdjPairs];         // pair results, then the entries' vectors
+  float gb[kAdjBlk * kAdjBlkStride];
+};
+
+// The radial derivative of one neighbor entry at displacement v, pulled: the
+// derivative of E_i and E_j with respect to their distance is one sum over
+// the 16 shifts of (dE_i/dG_i[s_j] + dE_j/dG_j[s_i]) times the term's
+// derivative, so an atom adds both to its own force and writes to no
+// neighbor.  Lists are symmetric (the predicate sees the negated
+// displacement, the same distance), so every pair comes up from both sides.
+// (PULL = false: dE_i's part alone, for the caller to scatter.)
+template <typename GT, bool PULL = true>
+__device__ __forceinline__ float radial_pull(const AevConst& C, const GT* __restrict__ gi,
+                                             const GT* __restrict__ gj, float r) {
+  float gv[16], gw[16];
+  Load16<GT>::get(gi, gv);
+  if constexpr (PULL) Load16<GT>::get(gj, gw);
+  float dfr;
+  const float fr = cutoff_val(r, C.inv_rc_r, dfr, C.pi_2rc_r);
+  float acc = 0.f;
+#pragma unroll
+  for (int m = 0; m < kNR; ++m) {
+    const float u = r - C.shf_r[m];
+    const float gm = PULL ? gv[m] + gw[m] : gv[m];
+    acc += gm * fast_exp2(-C.eta_r_l2e * u * u) * (dfr - C.eta_r2 * u * fr);
+  }
+  return C.cR * acc * fast_rcp(r);
+}
+
+// The adjoint of one atom by one wave; put(j, c, x) adds x to component c of
+// atom j.  (23,001-atom water box, BF16: 148 -> 73 us against scattering every
+// entry and adding the pairs by lane scans and LDS atomics, 4,500 atoms in
+// FP32 38 -> 24 us; it is bound by vector instructions, about 1,250 per atom,
+// 50 us at the full issue rate.)
 //
-// Quad waves (every atom with at most 16 neighbors) are built for latency:
-// the adjoint waits on its gathers of dE/dG, so it issues as few dependent
-// rounds of them as it can.  Lane (g, e) of group g sets up neighbor e of atom
-// i0 + g and computes that neighbor's whole radial derivative (its 16 shifts
-// against the 16 dE/dG values of its species block, two vector loads), so the
-// radial part of all four atoms is one round; the angular pairs of the four
-// atoms form one list that passes of eight pairs (eight lanes each) walk; the
-// scatter and the centre sums (16-lane reductions) again take all four atoms
-// at once.  Other waves take their atoms one at a time over the whole wave.
-template <typename GT, int Q, typename Put>
-__device__ __forceinline__ void adjoint_atoms(int i0, int n, const AevConst& C,
+// Radial part: pulled, one lane per entry.  Angular part: one lane per
+// unordered pair of angular neighbors.  A pair leaves three numbers in LDS
+// (aj, ak and bb of adjoint_pair), which the lanes of the entries then
+// collect, several lanes per entry.  (LDS atomics, at two clocks per lane,
+// took three quarters of the time of a version that added the pairs' results
+// with them.)  The pair blocks of dE/dG that the neighbors' elements select
+// are staged in LDS.  Only angular entries are scattered, component by
+// component in consecutive lanes: a global atomic addition costs by the
+// 64-byte line it goes to (one lane per entry with three additions in turn
+// costs three times as much).  The LDS holds 64 angular entries and 192
+// pairs; further pairs come in turn, and an atom with more than 64 angular
+// neighbors scatters every pair's results directly.
+template <typename GT, bool PULL, typename Put>
+__device__ __forceinline__ void adjoint_one(int i, int n, const AevConst& C, int si,
+                                            const float4* __restrict__ rec,
+                                            const int* __restrict__ nbr, int nr, int na, int cap,
+                                            const int* __restrict__ row_of,
+                                            const GT* __restrict__ grow, const GT* __restrict__ g,
+                                            int ldg, float sign, AdjLds& L, Put&& put) {
+  const int lane = lane_id();
+  const int S = C.S;
+  const size_t at0 = (size_t)i * cap;
+  const int pairs = (na * (na - 1)) >> 1;
+  const bool fits = na <= kAdjEnt;
+  const GT* gang = grow + C.A0;
+  float cx = 0.f, cy = 0.f, cz = 0.f;  // the lane's part of the centre's sum
+  unsigned elems = 0;                   // elements among the angular neighbors
+  for (int e = lane; e < nr; e += kWave) {
+    const float4 v = rec[at0 + e];
+    const int j = clampi(nbr[at0 + e], n);
+    const int sp = species_of(v);
+    const float r = fast_sqrt(dist2(v.x, v.y, v.z));
+    const float sc = radial_pull<GT, PULL>(
+        C, grow + sp * kNR, PULL ? g + (size_t)row_of[j] * ldg + si * kNR : nullptr, r);
+    if (!PULL) {
+      put(j, 0, -sign * v.x * sc);
+      put(j, 1, -sign * v.y * sc);
+      put(j, 2, -sign * v.z * sc);
+    }
+    cx += v.x * sc;
+    cy += v.y * sc;
+    cz += v.z * sc;
+    if (e < na && fits) {
+      float dfa;
+      const float fa = cutoff_val(r, C.inv_rc_a, dfa, C.pi_2rc_a);
+      L.nd[e] = make_float4(v.x, v.y, v.z, r);
+      L.nf[e] = make_float2(fa, dfa);
+      L.nj[e] = j;
+      L.nsp[e] = sp;
+      elems = 1u << sp;  // (angular entries are in the first 64)
+    }
+  }
+  if (fits && pairs > 0) {
+    // the blocks of the neighbors' elements: slot of ranks (a, b >= a) is
+    // pair_block(a, b, ne)
+    elems = wave_or(elems);
+    const int ne = __popc(elems), nb = (ne * (ne + 1)) >> 1;
+    const bool staged = nb <= kAdjBlk;
+    const int np = staged ? ne : S;
+    if (staged) {
+      if (lane < na) L.nsp[lane] = __popc(elems & ((1u << L.nsp[lane]) - 1u));
+      constexpr int EP = 16 / sizeof(GT), VB = 32 / EP;  // elements per 16 bytes, pieces per block
+      if (lane < nb * VB) {
+        const int slot = lane / VB, piece = lane % VB;
+        int a = 0;
+        while (a + 1 < ne && slot >= ((a + 1) * (2 * ne - a)) >> 1) ++a;
+        const int b = slot - ((a * (2 * ne - a + 1)) >> 1) + a;
+        const int blk = pair_block(nth_bit(elems, a), nth_bit(elems, b), S);
+        const uint4 u = *reinterpret_cast<const uint4*>(gang + blk * 32 + piece * EP);
+        float* d = L.gb + slot * kAdjBlkStride + piece * EP;
+        if constexpr (sizeof(GT) == 4) {
+          *reinterpret_cast<uint4*>(d) = u;
+        } else {
+          const unsigned w[4] = {u.x, u.y, u.z, u.w};
+          float f[8];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            f[2 * k] = __uint_as_float(w[k] << 16);
+            f[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
+          }
+          reinterpret_cast<float4*>(d)[0] = make_float4(f[0], f[1], f[2], f[3]);
+          reinterpret_cast<float4*>(d)[1] = make_float4(f[4], f[5], f[6], f[7]);
+        }
+      }
+    }
+    wave_lds_sync();
+    // this lane's entry when results are collected: entry e, every nsub-th
+    // partner from sub on
+    const int nsub = kWave / na;
+    const int sub = (int)(((float)lane + 0.5f) * fast_rcp((float)na));
+    const int e = lane - sub * na;
+    float gx = 0.f, gy = 0.f, gz = 0.f, ga = 0.f;
+    for (int c0 = 0; c0 < pairs; c0 += kAdjPairs) {
+      const int cn = pairs - c0 < kAdjPairs ? pairs - c0 : kAdjPairs;
+      for (int k = lane; k < cn; k += kWave) {
+        int ej, ek;
+        decode_pair(c0 + k, na, ej, ek);
+        const int blk = pair_block(L.nsp[ej], L.nsp[ek], np);
+        const float2 cj = L.nf[ej], ck = L.nf[ek];
+        float aj, ak, bb;
+        if (staged) {
+          const BlockLds gb{L.gb + blk * kAdjBlkStride};
+          adjoint_pair(C, gb, L.nd[ej], L.nd[ek], cj.x, cj.y, ck.x, ck.y, aj, ak, bb);
+        } else {
+          Block32<GT> gb;
+          gb.load(gang + blk * 32);
+          adjoint_pair(C, gb, L.nd[ej], L.nd[ek], cj.x, cj.y, ck.x, ck.y, aj, ak, bb);
+        }
+        L.tab[0][k] = aj;
+        L.tab[1][k] = ak;
+        L.tab[2][k] = bb;
+      }
+      wave_lds_sync();
+      if (sub < nsub) {
+        for (int p = sub; p < na; p += nsub) {
+          const int lo = p < e ? p : e, hi = p < e ? e : p;
+          const int t = ((lo * (2 * na - lo - 1)) >> 1) + hi - lo - 1 - c0;
+          if (p != e && t >= 0 && t < cn) {
+            const float4 v = L.nd[p];
+            const float bb = L.tab[2][t];
+            ga += L.tab[p < e ? 1 : 0][t];
+            gx += bb * v.x;
+            gy += bb * v.y;
+            gz += bb * v.z;
+          }
+        }
+      }
+      wave_lds_sync();
+    }
+    // the entry's sum over its lanes, and the scatter
+    for (int s = 1; s < nsub; ++s) {
+      const int from = e + s * na;
+      const float ox = __shfl(gx, from, kWave), oy = __shfl(gy, from, kWave),
+                  oz = __shfl(gz, from, kWave), oa = __shfl(ga, from, kWave);
+      if (sub == 0) {
+        gx += ox;
+        gy += oy;
+        gz += oz;
+        ga += oa;
+      }
+    }
+    if (lane < na) {
+      const float4 v = L.nd[lane];
+      gx += ga * v.x;
+      gy += ga * v.y;
+      gz += ga * v.z;
+      L.tab[0][lane] = gx;
+      L.tab[1][lane] = gy;
+      L.tab[2][lane] = gz;
+      cx += gx;
+      cy += gy;
+      cz += gz;
+    }
+    wave_lds_sync();
+    for (int t = lane; t < 3 * na; t += kWave) {
+      const int q = (t * 21846) >> 16, c = t - 3 * q;  // t / 3
+      put(L.nj[q], c, -sign * L.tab[c][q]);
+    }
+  } else if (!fits) {
+    for (int t = lane; t < pairs; t += kWave) {
+      int ej, ek;
+      decode_pair(t, na, ej, ek);
+      float4 vj = rec[at0 + ej], vk = rec[at0 + ek];
+      Block32<GT> gb;
+      gb.load(gang + pair_block(species_of(vj), species_of(vk), S) * 32);
+      vj.w = fast_sqrt(dist2(vj.x, vj.y, vj.z));
+      vk.w = fast_sqrt(dist2(vk.x, vk.y, vk.z));
+      float dj, dk;
+      const float fj = cutoff_val(vj.w, C.inv_rc_a, dj, C.pi_2rc_a);
+      const float fk = cutoff_val(vk.w, C.inv_rc_a, dk, C.pi_2rc_a);
+      float aj, ak, bb;
+      adjoint_pair(C, gb, vj, vk, fj, dj, fk, dk, aj, ak, bb);
+      const float gj[3] = {aj * vj.x + bb * vk.x, aj * vj.y + bb * vk.y, aj * vj.z + bb * vk.z};
+      const float gk[3] = {ak * vk.x + bb * vj.x, ak * vk.y + bb * vj.y, ak * vk.z + bb * vj.z};
+      const int jj = clampi(nbr[at0 + ej], n), jk = clampi(nbr[at0 + ek], n);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        put(jj, c, -sign * gj[c]);
+        put(jk, c, -sign * gk[c]);
+      }
+      cx += gj[0] + gk[0];
+      cy += gj[1] + gk[1];
+      cz += gj[2] + gk[2];
+    }
+  }
+  cx = wave_sum_rows(cx);
+  cy = wave_sum_rows(cy);
+  cz = wave_sum_rows(cz);
+  if (lane < 3) put(i, lane, sign * (lane == 0 ? cx : (lane == 1 ? cy : cz)));
+}
+
+// The adjoint of atoms i0 .. i0 + 4 H - 1 by one wave, for short lists
+// (molecules): lane (g, l) of H rounds takes entries l, l + 16, ... of atom
+// i0 + 4 h + g, so the atom's sums are sums over 16 lanes; the pairs of
+// angular neighbors of all atoms form one list, one lane per pair, whose
+// results go through LDS as in adjoint_one.  Needs at most 16 angular
+// neighbors per atom; returns false (nothing done) otherwise.  (32,768-atom
+// batch 18.8 -> 15.3 us, 77,163 atoms of mixed molecules 73.5 -> 39.4 us against
+// eight lanes per pair, lists of at most 16 entries and LDS atomics: mixed
+// molecules have longer lists now and then, which took the slow path.)
+template <int H>
+struct QuadLds {
+  float4 nd[64 * H];
+  float2 nf[64 * H];
+  int nsp[64 * H];
+  float tab[3][kAdjPairs];
+};
+
+template <typename GT, int H, bool PULL, typename Put>
+__device__ __forceinline__ bool adjoint_quads(int i0, int n, const AevConst& C,
+                                              const float4* __restrict__ xyzs,
                                               const float4* __restrict__ rec,
                                               const int* __restrict__ nbr,
                                               const int2* __restrict__ counts, int cap,
                                               const int* __restrict__ row_of,
                                               const GT* __restrict__ g, int ldg, float sign,
-                                              float4* nd, float4* nf, float4* grad, int* nsp,
-                                              Put&& put) {
+                                              QuadLds<H>& L, Put&& put) {
+  constexpr int Q = 4 * H;
   const int lane = lane_id();
-  // records, neighbor indices and counts of all four atoms are first-level
-  // loads; group gq (lanes 16 gq .. 16 gq + 15) holds atom i0 + gq
-  const int gq = Q > 1 ? lane >> 4 : 0, l = lane & 15;
-  const int ig = i0 + gq;
-  const bool gin = ig < n;
-  const size_t gbase = (size_t)(gin ? ig : i0) * cap + l;
-  const float4 q0 = gin ? rec[gbase] : make_float4(0.f, 0.f, 0.f, 0.f);
-  const int2 cn = gin ? counts[ig] : make_int2(0, 0);
-  const int nr_g = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
-  const int na_g = cn.y < 0 ? 0 : (cn.y > nr_g ? nr_g : cn.y);
-  const bool quad = Q > 1 && __ballot(nr_g > kQuadNbr) == 0;
   const int S = C.S;
-  if (quad) {
-    const int row_g = gin ? row_of[ig] : 0;
-    // ---- setup and radial derivative, one lane per neighbor entry
-    if (l < nr_g) {
-      const float r = fast_sqrt(dist2(q0.x, q0.y, q0.z));
-      float dfr, dfa = 0.f;
-      const float fr = cutoff_val(r, C.inv_rc_r, dfr, C.pi_2rc_r);
-      const float fa = l < na_g ? cutoff_val(r, C.inv_rc_a, dfa, C.pi_2rc_a) : 0.f;
-      const int sp = species_of(q0);
-      const int slot = kQuadNbr * gq + l;
-      nd[slot] = make_float4(q0.x, q0.y, q0.z, r);
-      nf[slot] = make_float4(fr, fa, dfr, dfa);
-      nsp[slot] = sp;
-      float gv[16];
-      Load16<GT>::get(g + (size_t)row_g * ldg + sp * kNR, gv);
-      float acc = 0.f;
+  const int gq = lane >> 4, l = lane & 15;
+  int nr[H], na[H], row[H], si[H], jn[H];
+  float4 v0[H];
+  bool wide = false;
 #pragma unroll
-      for (int m = 0; m < kNR; ++m) {
-        const float u = r - C.shf_r[m];
-        acc += gv[m] * fast_exp2(-C.eta_r_l2e * u * u) * (dfr - C.eta_r2 * u * fr);
+  for (int h = 0; h < H; ++h) {
+    const int i = i0 + 4 * h + gq;
+    const bool in = i < n;
+    const int2 cn = in ? counts[i] : make_int2(0, 0);
+    v0[h] = in ? rec[(size_t)i * cap + l] : make_float4(0.f, 0.f, 0.f, 0.f);
+    jn[h] = in ? nbr[(size_t)i * cap + l] : 0;
+    row[h] = in ? row_of[i] : 0;
+    si[h] = in ? species_of(xyzs[i]) : 0;
+    nr[h] = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
+    na[h] = cn.y < 0 ? 0 : (cn.y > nr[h] ? nr[h] : cn.y);
+    wide |= na[h] > kQuadNbr;
+  }
+  if (__ballot(wide)) return false;
+  float cen[H][3];
+  float gx[H], gy[H], gz[H], ga[H];  // the lane's angular entry
+#pragma unroll
+  for (int h = 0; h < H; ++h) gx[h] = gy[h] = gz[h] = ga[h] = 0.f;
+  int P[Q + 1];  // the atoms' first pairs in the list (uniform)
+  P[0] = 0;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    cen[h][0] = cen[h][1] = cen[h][2] = 0.f;
+    const size_t at = (size_t)(i0 + 4 * h + gq) * cap;
+    for (int e = l; __ballot(e < nr[h]) != 0; e += kQuadNbr) {
+      if (e < nr[h]) {
+        const bool first = e < kQuadNbr;
+        const float4 v = first ? v0[h] : rec[at + e];
+        const int j = clampi(first ? jn[h] : nbr[at + e], n);
+        const int sp = species_of(v);
+        const float r = fast_sqrt(dist2(v.x, v.y, v.z));
+        const float sc = radial_pull<GT, PULL>(
+            C, g + (size_t)row[h] * ldg + sp * kNR,
+            PULL ? g + (size_t)row_of[j] * ldg + si[h] * kNR : nullptr, r);
+        if (!PULL) {
+          if (e < na[h]) {  // (with the angular part)
+            gx[h] = v.x * sc;
+            gy[h] = v.y * sc;
+            gz[h] = v.z * sc;
+          } else {
+            put(j, 0, -sign * v.x * sc);
+            put(j, 1, -sign * v.y * sc);
+            put(j, 2, -sign * v.z * sc);
+          }
+        }
+        if (PULL || e >= na[h]) {
+          cen[h][0] += v.x * sc;
+          cen[h][1] += v.y * sc;
+          cen[h][2] += v.z * sc;
+        }
+        if (e < na[h]) {
+          float dfa;
+          const float fa = cutoff_val(r, C.inv_rc_a, dfa, C.pi_2rc_a);
+          const int slot = 64 * h + lane;
+          L.nd[slot] = make_float4(v.x, v.y, v.z, r);
+          L.nf[slot] = make_float2(fa, dfa);
+          L.nsp[slot] = sp;
+        }
       }
-      const float sc = C.cR * acc * fast_rcp(r);
-      grad[slot] = make_float4(q0.x * sc, q0.y * sc, q0.z * sc, 0.f);
     }
-    wave_lds_sync();
-    // ---- angular: the four atoms' pair lists as one list (pairs of atom a
-    // from offset P_a), eight pairs per pass, lanes (pair tg, angle shift tz)
-    const int na0 = __builtin_amdgcn_readlane(na_g, 0);
-    const int na1 = __builtin_amdgcn_readlane(na_g, 16);
-    const int na2 = __builtin_amdgcn_readlane(na_g, 32);
-    const int na3 = __builtin_amdgcn_readlane(na_g, 48);
-    const int P1 = na0 * (na0 - 1) / 2;
-    const int P2 = P1 + na1 * (na1 - 1) / 2;
-    const int P3 = P2 + na2 * (na2 - 1) / 2;
-    const int Ttot = P3 + na3 * (na3 - 1) / 2;
-    const int r0 = __builtin_amdgcn_readlane(row_g, 0);
-    const int r1 = __builtin_amdgcn_readlane(row_g, 16);
-    const int r2 = __builtin_amdgcn_readlane(row_g, 32);
-    const int r3 = __builtin_amdgcn_readlane(row_g, 48);
-    const int tz = lane & 7, tg = lane >> 3;
-    const float cz = C.lane_tab[kNR + tz], sz = C.lane_tab[kNR + kNZ + tz];
-    const float ra0 = C.shf_a[0], ra1 = C.shf_a[1], ra2 = C.shf_a[2], ra3 = C.shf_a[3];
-    for (int t0 = 0; t0 < Ttot; t0 += 8) {
-      // lanes past the last pair recompute it and contribute zero
-      const int pt = t0 + tg;
-      const bool valid = pt < Ttot;
-      const int pc = valid ? pt : Ttot - 1;
-      const int a = (pc >= P1) + (pc >= P2) + (pc >= P3);
-      const int pa = a == 0 ? 0 : (a == 1 ? P1 : (a == 2 ? P2 : P3));
-      const int na = a == 0 ? na0 : (a == 1 ? na1 : (a == 2 ? na2 : na3));
-      const int ra = a == 0 ? r0 : (a == 1 ? r1 : (a == 2 ? r2 : r3));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = __builtin_amdgcn_readlane(na[h], 16 * q);
+      P[4 * h + q + 1] = P[4 * h + q] + ((k * (k - 1)) >> 1);
+    }
+  }
+  wave_lds_sync();
+  const int pairs = P[Q];
+  for (int c0 = 0; c0 < pairs; c0 += kAdjPairs) {
+    const int cn = pairs - c0 < kAdjPairs ? pairs - c0 : kAdjPairs;
+    for (int k = lane; k < cn; k += kWave) {
+      const int idx = c0 + k;
+      int a = 0, start = 0, ka = __builtin_amdgcn_readlane(na[0], 0),
+          ra = __builtin_amdgcn_readlane(row[0], 0);
+#pragma unroll
+      for (int q = 1; q < Q; ++q) {
+        const bool past = idx >= P[q];
+        a = past ? q : a;
+        start = past ? P[q] : start;
+        ka = past ? __builtin_amdgcn_readlane(na[q >> 2], 16 * (q & 3)) : ka;
+        ra = past ? __builtin_amdgcn_readlane(row[q >> 2], 16 * (q & 3)) : ra;
+      }
       int ej, ek;
-      decode_pair(pc - pa, na, ej, ek);
+      decode_pair(idx - start, ka, ej, ek);
       ej += kQuadNbr * a;
       ek += kQuadNbr * a;
-      const float4 vj = nd[ej], vk = nd[ek];
-      const float4 cj = nf[ej], ck = nf[ek];
-      const float fj = cj.y, fk = ck.y, dfj = cj.w, dfk = ck.w;
-      const GT* gb = g + (size_t)ra * ldg + C.A0 + tz + pair_block(nsp[ej], nsp[ek], S) * 32;
-      const float g0 = Store<GT>::get(gb), g1 = Store<GT>::get(gb + 8),
-                  g2 = Store<GT>::get(gb + 16), g3 = Store<GT>::get(gb + 24);
-      const float rj = fast_rcp(vj.w), rk = fast_rcp(vk.w);
-      const float cs = (vj.x * vk.x + vj.y * vk.y + vj.z * vk.z) * (rj * rk);
-      const float kc = C.kappa * cs;
-      const float sn = fast_sqrt(fmaxf(1.f - kc * kc, 1e-12f));
-      const float base_ = 0.5f + 0.5f * (kc * cz + sn * sz);
-      const float pw = fast_exp2(C.zeta * fast_log2(base_));
-      const float f1 = 2.f * pw;
-      const float df1 = C.zeta * pw * fast_rcp(base_) * (C.kappa * (cz - kc * sz * fast_rcp(sn)));
-      const float dbar = 0.5f * (vj.w + vk.w);
-      float u, e2, A0 = 0.f, A1 = 0.f;
-      u = dbar - ra0; e2 = fast_exp2(-C.eta_a_l2e * u * u); A0 += g0 * e2; A1 -= g0 * u * e2;
-      u = dbar - ra1; e2 = fast_exp2(-C.eta_a_l2e * u * u); A0 += g1 * e2; A1 -= g1 * u * e2;
-      u = dbar - ra2; e2 = fast_exp2(-C.eta_a_l2e * u * u); A0 += g2 * e2; A1 -= g2 * u * e2;
-      u = dbar - ra3; e2 = fast_exp2(-C.eta_a_l2e * u * u); A0 += g3 * e2; A1 -= g3 * u * e2;
-      float X0 = valid ? f1 * A0 : 0.f;
-      float X1 = valid ? f1 * A1 * C.eta_a : 0.f;
-      float Xc = valid ? df1 * A0 : 0.f;
-      X0 = group8_sum(X0);
-      X1 = group8_sum(X1);
-      Xc = group8_sum(Xc);
-      if (valid && tz == 0) {
-        const float fcc = fj * fk;
-        const float dEdc = Xc * fcc;
-        const float dEdj = X1 * fcc + X0 * dfj * fk;
-        const float dEdk = X1 * fcc + X0 * fj * dfk;
-        const float aj = (dEdj - dEdc * cs * rj) * rj;
-        const float ak = (dEdk - dEdc * cs * rk) * rk;
-        const float bb = dEdc * rj * rk;
-        atomicAdd(&grad[ej].x, aj * vj.x + bb * vk.x);
-        atomicAdd(&grad[ej].y, aj * vj.y + bb * vk.y);
-        atomicAdd(&grad[ej].z, aj * vj.z + bb * vk.z);
-        atomicAdd(&grad[ek].x, ak * vk.x + bb * vj.x);
-        atomicAdd(&grad[ek].y, ak * vk.y + bb * vj.y);
-        atomicAdd(&grad[ek].z, ak * vk.z + bb * vj.z);
+      Block32<GT> gb;
+      gb.load(g + (size_t)ra * ldg + C.A0 + pair_block(L.nsp[ej], L.nsp[ek], S) * 32);
+      const float2 cj = L.nf[ej], ck = L.nf[ek];
+      float aj, ak, bb;
+      adjoint_pair(C, gb, L.nd[ej], L.nd[ek], cj.x, cj.y, ck.x, ck.y, aj, ak, bb);
+      L.tab[0][k] = aj;
+      L.tab[1][k] = ak;
+      L.tab[2][k] = bb;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int base = 64 * h + 16 * gq;
+      const int t0 = (gq == 0 ? P[4 * h] : (gq == 1 ? P[4 * h + 1]
+                                                    : (gq == 2 ? P[4 * h + 2] : P[4 * h + 3]))) - c0;
+      if (l < na[h]) {
+        for (int p = 0; p < na[h]; ++p) {
+          const int lo = p < l ? p : l, hi = p < l ? l : p;
+          const int t = ((lo * (2 * na[h] - lo - 1)) >> 1) + hi - lo - 1 + t0;
+          if (p != l && t >= 0 && t < cn) {
+            const float4 v = L.nd[base + p];
+            const float bb = L.tab[2][t];
+            ga[h] += L.tab[p < l ? 1 : 0][t];
+            gx[h] += bb * v.x;
+            gy[h] += bb * v.y;
+            gz[h] += bb * v.z;
+          }
+        }
       }
     }
     wave_lds_sync();
-    // ---- scatter of all four atoms: neighbors get -sign * dE/dv, each
-    // centre +sign * its group's sum
-    float4 gv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (l < nr_g) {
-      gv = grad[kQuadNbr * gq + l];
-      put(clampi(nbr[gbase], n), -sign * gv.x, -sign * gv.y, -sign * gv.z);
-    }
-    const float sx = group16_sum(gv.x), sy = group16_sum(gv.y), sz2 = group16_sum(gv.z);
-    if (gin && l == 0) put(ig, sign * sx, sign * sy, sign * sz2);
-    return;
   }
-  for (int a = 0; a < Q; ++a) {
-    const int i = i0 + a;
-    if (i >= n) break;  // wave-uniform
-    const int nr = __builtin_amdgcn_readlane(nr_g, kQuadNbr * a);
-    const int na = __builtin_amdgcn_readlane(na_g, kQuadNbr * a);
-    const GT* grow = g + (size_t)row_of[i] * ldg;
-    // this atom alone over the whole wave
-    const float4* arec = rec + (size_t)i * cap;
-    const int* arow = nbr + (size_t)i * cap;
-    // the scatter's first two rounds of neighbor indices, loaded now so that
-    // their latency hides behind the passes
-    const int j0 = lane < nr ? arow[lane] : 0;
-    const int j1 = lane + kWave < nr ? arow[lane + kWave] : 0;
-    for (int e = lane; e < nr; e += kWave) adjoint_setup(e, arec[e], e < na, C, nd, nf, nsp);
-    wave_lds_sync();
-    adjoint_passes<GT, Q == 1 ? kAngPairLanes : kAngShiftLanes>(nr, na, C, grow, nd, nf, grad,
-                                                                nsp);
-    float sx = 0.f, sy = 0.f, sz = 0.f;
-    for (int e = lane; e < nr; e += kWave) {
-      const float4 gv = grad[e];
-      const int j = e < kWave ? j0 : (e < 2 * kWave ? j1 : arow[e]);
-      put(clampi(j, n), -sign * gv.x, -sign * gv.y, -sign * gv.z);
-      sx += gv.x;
-      sy += gv.y;
-      sz += gv.z;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    if (l < na[h]) {
+      gx[h] += ga[h] * v0[h].x;
+      gy[h] += ga[h] * v0[h].y;
+      gz[h] += ga[h] * v0[h].z;
+      const int j = clampi(jn[h], n);
+      put(j, 0, -sign * gx[h]);
+      put(j, 1, -sign * gy[h]);
+      put(j, 2, -sign * gz[h]);
     }
-    sx = wave_sum_rows(sx);
-    sy = wave_sum_rows(sy);
-    sz = wave_sum_rows(sz);
-    if (lane == 0) put(i, sign * sx, sign * sy, sign * sz);
-    wave_lds_sync();  // the next atom reuses the region
+    const float x = group16_sum(cen[h][0] + gx[h]), y = group16_sum(cen[h][1] + gy[h]),
+                z = group16_sum(cen[h][2] + gz[h]);
+    const int i = i0 + 4 * h + gq;
+    if (i < n && l < 3) put(i, l, sign * (l == 0 ? x : (l == 1 ? y : z)));
   }
+  return true;
 }
 
-// Adjoint: g (rows of type GT, stride ldg) -> scatter into out (float32 [n][3]).
+// Adjoint: g (rows of type GT, stride ldg) -> added into out (float32 [n][3]).
 // sign = +1 writes forces (-dE/dr); sign = -1 writes the gradient dE/dr.
 // With gidx, atom i's force goes to row gidx[i] of out ([n_total][3]; rows
 // outside [0, n_total) are skipped; staging reports them).  Blocks from
 // nb_adj on sum the molecular energies (one block per molecule), which need
 // only the atomic energies of the forward pass: they fill the tail of the
 // scatter instead of a launch of their own.
-template <typename GT, int Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 1 ? 6 : 4, 8))) void k_aev_bwd(
-    const int* __restrict__ dims, AevConst C,
-                                                 const float4* __restrict__ rec,
-                                                 const int* __restrict__ nbr,
-                                                 const int2* __restrict__ counts, int cap,
-                                                 const int* __restrict__ row_of,
-                                                 const GT* __restrict__ g, int ldg,
-                                                 float* __restrict__ out, float sign,
-                                                 const int* __restrict__ gidx, int n_total,
-                                                 int nb_adj, EnergyArgs EA) {
-  extern __shared__ float4 lds4[];
+template <typename GT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_aev_bwd(
+    const int* __restrict__ dims, AevConst C, const float4* __restrict__ xyzs,
+    const float4* __restrict__ rec, const int* __restrict__ nbr, const int2* __restrict__ counts,
+    int cap, const int* __restrict__ row_of, const GT* __restrict__ g, int ldg,
+    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total, int nb_adj,
+    EnergyArgs EA) {
+  __shared__ AdjLds lds[4];
   if ((int)blockIdx.x >= nb_adj) {  // block-uniform: the molecular energy sums
     energy_block((int)blockIdx.x - nb_adj, dims, EA);
     return;
   }
   const int n = dims[0];
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int i0 = ((int)blockIdx.x * 4 + w) * Q;
+  const int i = (int)blockIdx.x * 4 + w;
+  if (i >= n) return;
+  const int2 cn = counts[i];
+  const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
+  const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
+  adjoint_one<GT, true>(i, n, C, species_of(xyzs[i]), rec, nbr, nr, na, cap, row_of,
+                        g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w],
+                        [&](int j, int c, float x) {
+                          if (gidx) {
+                            j = gidx[j];
+                            if (j < 0 || j >= n_total) return;
+                          }
+                          unsafeAtomicAdd(out + 3 * (size_t)j + c, x);
+                        });
+}
+
+// Small systems (few waves, so the chain of dependent loads is the time): four
+// atoms per wave on short lists, every entry scattered to global memory
+// (pulling the radial part would put two more loads in the chain).  1,645
+// atoms: 28.7 -> 9.0 us, 24 atoms in FP32: 11.5 -> 5.6 us, against 64-atom
+// workgroups with windows.
+template <typename GT>
+__global__ __launch_bounds__(256) void k_aev_bwd_small(
+    const int* __restrict__ dims, AevConst C, const float4* __restrict__ xyzs,
+    const float4* __restrict__ rec, const int* __restrict__ nbr, const int2* __restrict__ counts,
+    int cap, const int* __restrict__ row_of, const GT* __restrict__ g, int ldg,
+    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total, int nb_adj,
+    EnergyArgs EA) {
+  __shared__ union {
+    QuadLds<1> quad;
+    AdjLds one;
+  } lds[4];
+  if ((int)blockIdx.x >= nb_adj) {  // block-uniform: the molecular energy sums
+    energy_block((int)blockIdx.x - nb_adj, dims, EA);
+    return;
+  }
+  const int n = dims[0];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int i0 = ((int)blockIdx.x * 4 + w) * 4;
   if (i0 >= n) return;
-  const int reg = aev_region(cap);
-  float4* nd = lds4 + (size_t)w * reg * 3;
-  int* nsp = reinterpret_cast<int*>(lds4 + (size_t)4 * reg * 3) + w * reg;
-  adjoint_atoms<GT, Q>(i0, n, C, rec, nbr, counts, cap, row_of, g, ldg, sign, nd, nd + reg,
-                    nd + 2 * reg, nsp, [&](int j, float x, float y, float z) {
-                      if (gidx) {
-                        j = gidx[j];
-                        if (j < 0 || j >= n_total) return;
-                      }
-                      unsafeAtomicAdd(out + 3 * j, x);
-                      unsafeAtomicAdd(out + 3 * j + 1, y);
-                      unsafeAtomicAdd(out + 3 * j + 2, z);
-                    });
+  auto put = [&](int j, int c, float x) {
+    if (gidx) {
+      j = gidx[j];
+      if (j < 0 || j >= n_total) return;
+    }
+    unsafeAtomicAdd(out + 3 * (size_t)j + c, x);
+  };
+  if (adjoint_quads<GT, 1, false>(i0, n, C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, sign,
+                                  lds[w].quad, put))
+    return;
+  for (int a = 0; a < 4 && i0 + a < n; ++a) {
+    const int i = i0 + a;
+    const int2 cn = counts[i];
+    const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
+    const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
+    adjoint_one<GT, false>(i, n, C, 0, rec, nbr, nr, na, cap, row_of,
+                           g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w].one, put);
+    wave_lds_sync();  // the next atom reuses the LDS
+  }
 }
 
 // Deterministic adjoint (gather mode): one atom per wave, as above, but the
@@ -963,13 +1164,12 @@ __global__ __launch_bounds__(256) void k_aev_bwd_det(const int* __restrict__ dim
   const float4* arec = rec + (size_t)i * cap;
   for (int e = lane; e < nr; e += kWave) adjoint_setup(e, arec[e], e < na, C, nd, nf, nsp);
   wave_lds_sync();
-  adjoint_passes<GT, kAngShiftLanesOrdered>(nr, na, C, g + (size_t)row_of[i] * ldg, nd, nf, grad,
-                                            nsp);
+  adjoint_passes_ordered<GT>(nr, na, C, g + (size_t)row_of[i] * ldg, nd, nf, grad, nsp);
   for (int e = lane; e < nr; e += kWave) pgrad[(size_t)i * cap + e] = grad[e];
 }
 
 // Molecules (no box, no index map): a workgroup owns the kMolBlock atoms
-// [b * kMolBlock, (b + 1) * kMolBlock), its waves taking them in turn, and
+// [b * kMolBlock, (b + 1) * kMolBlock), eight per wave, and
 // adds every force into an LDS window over the atoms [b - 1, b + 2) *
 // kMolBlock, which holds all neighbors of its atoms for molecules of up to
 // kMolBlock + 1 atoms (neighbors outside it, in larger molecules, are added
@@ -978,49 +1178,48 @@ __global__ __launch_bounds__(256) void k_aev_bwd_det(const int* __restrict__ dim
 // atoms (nothing else adds to it; staging zeroed the output), else with one
 // atomic add per component.  This replaces the contended per-entry global
 // atomics of the per-atom kernel (about nine adds per atom on the same lines).
-template <typename GT, int Q>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_aev_bwd_mol(const int* __restrict__ dims, AevConst C,
-                                                      const float4* __restrict__ rec,
-                                                      const int* __restrict__ nbr,
-                                                      const int2* __restrict__ counts, int cap,
-                                                      const int* __restrict__ row_of,
-                                                      const GT* __restrict__ g, int ldg,
-                                                      float* __restrict__ out, float sign,
-                                                      const int2* __restrict__ mrange,
-                                                      int nb_adj, EnergyArgs EA) {
-  extern __shared__ float4 lds4[];
+template <typename GT>
+__global__ __launch_bounds__(64 * kMolWaves) __attribute__((amdgpu_waves_per_eu(4, 8))) void
+k_aev_bwd_mol(const int* __restrict__ dims, AevConst C, const float4* __restrict__ xyzs,
+              const float4* __restrict__ rec, const int* __restrict__ nbr,
+              const int2* __restrict__ counts, int cap, const int* __restrict__ row_of,
+              const GT* __restrict__ g, int ldg, float* __restrict__ out, float sign,
+              const int2* __restrict__ mrange, int nb_adj, EnergyArgs EA) {
+  constexpr int kWin = 3 * kMolBlock;
+  __shared__ union {
+    QuadLds<2> quad;
+    AdjLds one;
+  } lds[kMolWaves];
+  __shared__ float win[3 * kWin];
   if ((int)blockIdx.x >= nb_adj) {  // block-uniform: the molecular energy sums
     energy_block((int)blockIdx.x - nb_adj, dims, EA);
     return;
   }
-  constexpr int kWin = 3 * kMolBlock;
   const int n = dims[0];
-  const int nw = (int)blockDim.x >> 6, w = (int)threadIdx.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int base = (int)blockIdx.x * kMolBlock, w0 = base - kMolBlock;
-  const int reg = aev_region(cap);
-  float4* nd = lds4 + (size_t)w * reg * 3;
-  int* nsp = reinterpret_cast<int*>(lds4 + (size_t)nw * reg * 3) + w * reg;
-  float* win = reinterpret_cast<float*>(reinterpret_cast<int*>(lds4 + (size_t)nw * reg * 3) +
-                                        (size_t)nw * reg);
   for (int t = threadIdx.x; t < 3 * kWin; t += blockDim.x) win[t] = 0.f;
   __syncthreads();
-  for (int a = Q * w; a < kMolBlock; a += Q * nw) {
-    const int i0 = base + a;
-    if (i0 >= n) break;  // wave-uniform
-    adjoint_atoms<GT, Q>(i0, n, C, rec, nbr, counts, cap, row_of, g, ldg, sign, nd, nd + reg,
-                      nd + 2 * reg, nsp, [&](int j, float x, float y, float z) {
-                        const int t = j - w0;
-                        if (t >= 0 && t < kWin) {
-                          atomicAdd(win + 3 * t, x);
-                          atomicAdd(win + 3 * t + 1, y);
-                          atomicAdd(win + 3 * t + 2, z);
-                        } else {
-                          unsafeAtomicAdd(out + 3 * j, x);
-                          unsafeAtomicAdd(out + 3 * j + 1, y);
-                          unsafeAtomicAdd(out + 3 * j + 2, z);
-                        }
-                      });
-    wave_lds_sync();  // the next atoms reuse this wave's region
+  auto put = [&](int j, int c, float x) {
+    const int t = j - w0;
+    if (t >= 0 && t < kWin)
+      atomicAdd(win + 3 * t + c, x);
+    else
+      unsafeAtomicAdd(out + 3 * (size_t)j + c, x);
+  };
+  static_assert(kMolBlock == 8 * kMolWaves, "eight atoms per wave");
+  const int i0 = base + 8 * w;
+  if (i0 < n && !adjoint_quads<GT, 2, true>(i0, n, C, xyzs, rec, nbr, counts, cap, row_of, g, ldg,
+                                            sign, lds[w].quad, put)) {
+    for (int a = 0; a < 8 && i0 + a < n; ++a) {
+      const int i = i0 + a;
+      const int2 cn = counts[i];
+      const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
+      const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
+      adjoint_one<GT, true>(i, n, C, species_of(xyzs[i]), rec, nbr, nr, na, cap, row_of,
+                            g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w].one, put);
+      wave_lds_sync();  // the next atom reuses the LDS
+    }
   }
   __syncthreads();
   for (int t = threadIdx.x; t < kWin; t += blockDim.x) {
@@ -1080,39 +1279,9 @@ template void launch_aev_fwd<bf16_t>(const int*, int, const AevConst&, const flo
                                      const int2*, int, const int*, bf16_t*, int, bool,
                                      unsigned long long*, bool, hipStream_t);
 
-template <typename GT, int Q>
-static void launch_aev_bwd_q(const int* dims, int n_cap, const AevConst& C, const float4* rec,
-                             const int* nbr, const int2* counts, int cap, const int* row_of,
-                             const GT* g, int ldg, float* out, float sign, const int* gidx,
-                             int n_total, const int2* mrange, const EnergyArgs* energy,
-                             int nmol_cap, hipStream_t st) {
-  const int nb_e = energy && energy->E && nmol_cap > 0 ? nmol_cap : 0;
-  const EnergyArgs ea = nb_e ? *energy : EnergyArgs{};
-  if (mrange && !gidx) {
-    // waves per workgroup: 8 while two workgroups fit a CU's LDS, else 4
-    const int nw = cap <= 128 ? 8 : 4;
-    const int nb_adj = n_cap > 0 ? (n_cap + kMolBlock - 1) / kMolBlock : 0;
-    if (nb_adj + nb_e == 0) return;
-    const size_t lds =
-        (size_t)nw * aev_region(cap) * kBwdBytesPerNbr + (size_t)3 * kMolBlock * 3 * 4;
-    static const bool attr = (ensure_lds(k_aev_bwd_mol<GT, Q>), true);
-    (void)attr;
-    hipLaunchKernelGGL((k_aev_bwd_mol<GT, Q>), dim3(nb_adj + nb_e), dim3(64 * nw), lds, st, dims,
-                       C, rec, nbr, counts, cap, row_of, g, ldg, out, sign, mrange, nb_adj, ea);
-    return;
-  }
-  const int nb_adj = n_cap > 0 ? (n_cap + 4 * Q - 1) / (4 * Q) : 0;
-  if (nb_adj + nb_e == 0) return;
-  const size_t lds = (size_t)4 * aev_region(cap) * kBwdBytesPerNbr;
-  static const bool attr = (ensure_lds(k_aev_bwd<GT, Q>), true);
-  (void)attr;
-  hipLaunchKernelGGL((k_aev_bwd<GT, Q>), dim3(nb_adj + nb_e), dim3(256), lds, st, dims, C, rec,
-                     nbr, counts, cap, row_of, g, ldg, out, sign, gidx, n_total, nb_adj, ea);
-}
-
 template <typename GT>
-void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4* rec,
-                    const int* nbr, const int2* counts, int cap, const int* row_of, const GT* g,
+void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4* xyzs,
+                    const float4* rec, const int* nbr, const int2* counts, int cap, const int* row_of, const GT* g,
                     int ldg, float* out, float sign, const int* gidx, int n_total,
                     const int2* mrange, const EnergyArgs* energy, int nmol_cap, float4* pgrad,
                     hipStream_t st) {
@@ -1128,18 +1297,33 @@ void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4*
                        rec, counts, cap, row_of, g, ldg, pgrad, nb_adj, ea);
     return;
   }
-  if (aev_quads(cap))
-    launch_aev_bwd_q<GT, 4>(dims, n_cap, C, rec, nbr, counts, cap, row_of, g, ldg, out, sign,
-                            gidx, n_total, mrange, energy, nmol_cap, st);
+  const int nb_e = energy && energy->E && nmol_cap > 0 ? nmol_cap : 0;
+  const EnergyArgs ea = nb_e ? *energy : EnergyArgs{};
+  // Molecules: above 10,000 atoms workgroups with LDS windows, below it four
+  // atoms per wave and direct additions.  Measured, whole evaluation of
+  // 64-atom molecules, seven elements, BF16 (us, direct / window): 1,024 atoms
+  // 36.3 / 41.2, 8,192: 52.0 / 52.5, 12,288: 70.7 / 66.4, 32,768: 126 / 105.
+  // Boxes (long lists) and large subsets: one atom per wave.
+  const bool mol = mrange != nullptr;
+  const bool window = mol && !gidx && n_cap > 10000;
+  const bool small = mol && n_cap <= 10000;
+  const int per_block = window ? kMolBlock : (small ? 16 : 4);
+  const int nb_adj = n_cap > 0 ? (n_cap + per_block - 1) / per_block : 0;
+  if (nb_adj + nb_e == 0) return;
+  if (window)
+    hipLaunchKernelGGL((k_aev_bwd_mol<GT>), dim3(nb_adj + nb_e), dim3(64 * kMolWaves), 0, st, dims,
+                       C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, out, sign, mrange, nb_adj,
+                       ea);
   else
-    launch_aev_bwd_q<GT, 1>(dims, n_cap, C, rec, nbr, counts, cap, row_of, g, ldg, out, sign,
-                            gidx, n_total, mrange, energy, nmol_cap, st);
+    hipLaunchKernelGGL(small ? k_aev_bwd_small<GT> : k_aev_bwd<GT>, dim3(nb_adj + nb_e), dim3(256),
+                       0, st, dims, C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, out, sign,
+                       gidx, n_total, nb_adj, ea);
 }
-template void launch_aev_bwd<float>(const int*, int, const AevConst&, const float4*, const int*,
+template void launch_aev_bwd<float>(const int*, int, const AevConst&, const float4*, const float4*, const int*,
                                     const int2*, int, const int*, const float*, int, float*, float,
                                     const int*, int, const int2*, const EnergyArgs*, int, float4*,
                                     hipStream_t);
-template void launch_aev_bwd<bf16_t>(const int*, int, const AevConst&, const float4*, const int*,
+template void launch_aev_bwd<bf16_t>(const int*, int, const AevConst&, const float4*, const float4*, const int*,
                                      const int2*, int, const int*, const bf16_t*, int, float*,
                                      float, const int*, int, const int2*, const EnergyArgs*, int,
                                      float4*, hipStream_t);

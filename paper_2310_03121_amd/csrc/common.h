@@ -104,6 +104,22 @@ __device__ __forceinline__ float wave_sum_rows(float v) {
          __int_as_float(__builtin_amdgcn_readlane(b, 63));
 }
 
+// Bitwise or over the wave (all lanes active), uniform.
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+  v |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+  v |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+  v |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+  v |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+  return (unsigned)(__builtin_amdgcn_readlane((int)v, 15) | __builtin_amdgcn_readlane((int)v, 31) |
+                    __builtin_amdgcn_readlane((int)v, 47) | __builtin_amdgcn_readlane((int)v, 63));
+}
+
+// The k-th set bit of m (k < popcount(m)).
+__device__ __forceinline__ int nth_bit(unsigned m, int k) {
+  for (; k > 0; --k) m &= m - 1u;
+  return __ffs((int)m) - 1;
+}
+
 // Butterfly sums over groups of 8 and 16 consecutive lanes by DPP (all
 // lanes active), the same pairing as exchanges at lane distance 1, 2, 4 (and
 // 8): swaps inside quads, then the half-row and row mirrors, which pair each
