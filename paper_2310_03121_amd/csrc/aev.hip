@@ -97,15 +97,11 @@ __device__ __forceinline__ int pair_block(int p, int q, int S) {
   return lo * S - lo * (lo - 1) / 2 + (hi - lo);
 }
 
-// Angular pairs are decoded in chunks of 64, one pair per lane, into a
-// per-wave LDS table that the passes then read.
+// LDS per wave (forward): per neighbor float4 (dx, dy, dz, r), float2 (fc_rad,
+// species bits) and fc_ang; a table of 64 angular pairs (eight angle-shift
+// weights, four distance Gaussians and the block of each).  The feature row is
+// accumulated in registers and stored block by block, so no LDS row is needed.
 constexpr int kPairChunk = 64;
-
-// LDS per wave (forward): per neighbor float4 (dx, dy, dz, r), float2
-// (fc_rad, fc_ang), int species; a 64-entry table of angular pairs (eight
-// angle-shift weights, four distance Gaussians and the block of each).  The
-// feature row is accumulated in registers and stored block by block, so no
-// LDS row is needed.
 constexpr int kFwdBytesPerNbr = 16 + 8 + 4;
 constexpr int kFwdPairBytes = 32 + 16 + 4;
 
@@ -120,26 +116,59 @@ __device__ __forceinline__ aev_f32x4 mfma4(float a, float b, aev_f32x4 acc) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
 }
 
-// The angular pair t of atom-local list prefix [0, na), one per lane: the
-// factors of its 32 terms, computed once instead of in each of the 16 lanes
-// of its pass, written to table slot `slot`: the angle-shift weights
+// Four atoms per wave.  When the lists of a wave's four atoms, each rounded up
+// to whole passes, fit 64 entries ("quad" waves), the per-neighbor setup
+// (distances, cutoffs, species) runs for all four at once, one 16-lane group
+// per atom, and the pairs of angular neighbors of all four share one table
+// while they fit it; the radial and angular passes, which fill the wave with
+// (neighbor, shift) and (pair, shift) lanes, run atom by atom.  Other waves
+// take their atoms one at a time with all 64 lanes.  Either way a wave's LDS
+// region holds max(64, capacity) neighbor entries.
+//
+// Quads pay off where lists are short and waves are many; elsewhere a wave
+// per atom keeps four times as many waves in flight to hide the latency of the
+// per-atom passes.  Measured (us, one atom / four atoms per wave): molecules,
+// 1,024 atoms 5.5 / 13.1, 8,192: 10.1 / 15.0, 16,384: 16.6 / 17.8, 32,768: 28.2
+// / 20.1 to 28.3 (by how crowded the molecule is); so molecules of more than
+// 16,384 atoms take quads, boxes (about 55 neighbors) and smaller calls one
+// atom.
+constexpr int kQuadNbr = 16;   // lanes per atom of a quad wave
+constexpr int kQuadAtoms = 16384;
+
+__host__ __device__ constexpr int aev_region(int cap) { return cap > 64 ? cap : 64; }
+
+struct FwdLds {
+  float4* nd;   // displacement, distance
+  float2* fs;   // radial cutoff value, species
+  float* fa;    // angular cutoff value
+  float* pw;    // [kPairChunk][8]
+  float* pg;    // [kPairChunk][4]: distance shifts 0, 2, 1, 3
+  int* pblk;    // [kPairChunk]: block, -1 past the last pair
+};
+
+// The angular pair t of the na angular neighbors at entry `base`, to table
+// slot `slot`: the factors of its 32 terms, computed once instead of in each of
+// the 16 lanes of its pass: the angle-shift weights
 // w[z] = 2 ((1 + cos(theta - theta_z)) / 2)^zeta fc_j fc_k and the distance
 // Gaussians g[a] = exp(-eta_A ((r_j + r_k) / 2 - R_a)^2); term (a, z) = w[z] g[a].
-__device__ __forceinline__ void pair_geometry(int t, int na, const AevConst& C, const float4* nd,
-                                              const float2* nf, const int* nsp, float* pw,
-                                              float* pg, int* pblk, int slot) {
+// Returns the pair's block; not `valid`: the same terms with block -1, whose
+// one-hot row is zero.
+__device__ __forceinline__ int pair_geometry(int t, int na, bool valid, const AevConst& C,
+                                             const FwdLds& L, int base, int slot) {
   int a, b;
   decode_pair(t, na, a, b);
-  const float4 vj = nd[a], vk = nd[b];
+  a += base;
+  b += base;
+  const float4 vj = L.nd[a], vk = L.nd[b];
   const float cs = (vj.x * vk.x + vj.y * vk.y + vj.z * vk.z) * fast_rcp(vj.w * vk.w);
   const float kc = C.kappa * cs;
   const float sn = fast_sqrt(fmaxf(1.f - kc * kc, 0.f));
   const float dbar = 0.5f * (vj.w + vk.w);
-  const float fcc = nf[a].y * nf[b].y;
+  const float fcc = L.fa[a] * L.fa[b];
   float w[kNZ];
 #pragma unroll
   for (int z = 0; z < kNZ; ++z) {
-    const float base_ = 0.5f + 0.5f * (kc * C.lane_tab[kNR + z] + sn * C.lane_tab[kNR + kNZ + z]);
+    const float base_ = 0.5f + 0.5f * (kc * C.cos_z[z] + sn * C.sin_z[z]);
     w[z] = 2.f * fast_exp2(C.zeta * fast_log2(base_)) * fcc;
   }
   float g[kNA];
@@ -148,42 +177,69 @@ __device__ __forceinline__ void pair_geometry(int t, int na, const AevConst& C, 
     const float u = dbar - C.shf_a[q];
     g[q] = fast_exp2(-C.eta_a_l2e * u * u);
   }
-  reinterpret_cast<float4*>(pw)[2 * slot] = make_float4(w[0], w[1], w[2], w[3]);
-  reinterpret_cast<float4*>(pw)[2 * slot + 1] = make_float4(w[4], w[5], w[6], w[7]);
-  reinterpret_cast<float4*>(pg)[slot] = make_float4(g[0], g[1], g[2], g[3]);
-  pblk[slot] = pair_block(nsp[a], nsp[b], C.S);
+  reinterpret_cast<float4*>(L.pw)[2 * slot] = make_float4(w[0], w[1], w[2], w[3]);
+  reinterpret_cast<float4*>(L.pw)[2 * slot + 1] = make_float4(w[4], w[5], w[6], w[7]);
+  reinterpret_cast<float4*>(L.pg)[slot] = make_float4(g[0], g[2], g[1], g[3]);
+  const int blk = valid ? pair_block(__float_as_int(L.fs[a].y), __float_as_int(L.fs[b].y), C.S) : -1;
+  L.pblk[slot] = blk;
+  return blk;
 }
 
-// Four atoms per wave.  When each of a wave's four atoms has at most 16
-// neighbors ("quad" waves), the per-neighbor setup (distances, cutoffs,
-// species; in the adjoint also the force scatter and the centre-atom sum)
-// runs for all four at once, one 16-lane group per atom, and the pairs of
-// angular neighbors of all four share one table; the radial and angular
-// passes, which fill the wave with (neighbor, shift) and (pair, shift) lanes,
-// run atom by atom.  Other waves take their atoms one at a time with all 64
-// lanes.  Either way a wave's LDS region holds max(64, capacity) neighbor
-// entries: four 16-entry slots, or one atom's list.
-//
-// Quads pay off only where lists are short; where they are long, a wave per
-// atom keeps four times as many waves in flight to hide the latency of the
-// per-atom passes.  The launchers take the neighbor capacity as the hint:
-// Q = 4 atoms per wave up to a capacity of 64 (molecules), else Q = 1
-// (liquid-density boxes need more than 64).
-constexpr int kQuadNbr = 16;   // longest list of a quad wave (lanes per atom)
+// The k-steps (32 feature columns) holding a block an atom touches, from the
+// elements among its neighbors (bits 0-7 of `seen`), among its angular
+// neighbors (8-15), and those at least twice among these (16-23): the radial
+// blocks of the first, the angular blocks of the pairs of the second (a pair
+// (x, x) needs two).  Every other feature is zero, and the adjoint reads no
+// dE/dG column outside them.  For four atoms at once, one per 16 lanes (`seen`
+// the same in all of them): lane 7 of each group returns its atom's.
+__device__ __forceinline__ unsigned long long row_ksteps(unsigned seen, const AevConst& C) {
+  const int S = C.S, x = lane_id() & 15;
+  const unsigned rp = seen & 255u, ap = (seen >> 8) & 255u, ad = (seen >> 16) & 255u;
+  // lane x: element x's row of the angular triangle, blocks (x, x + k), which
+  // starts at block x S - x (x - 1) / 2
+  const unsigned row = (((ap >> x) & ~1u) | ((ad >> x) & 1u)) & ((1u << (S - x > 0 ? S - x : 0)) - 1u);
+  const unsigned long long bm =
+      (ap >> x) & 1u ? (unsigned long long)row << (x * S - ((x * (x - 1)) >> 1)) : 0ull;
+  int lo = (int)(unsigned)bm, hi = (int)(unsigned)(bm >> 32);
+  lo |= __builtin_amdgcn_update_dpp(0, lo, 0x111, 0xf, 0xf, true);
+  hi |= __builtin_amdgcn_update_dpp(0, hi, 0x111, 0xf, 0xf, true);
+  lo |= __builtin_amdgcn_update_dpp(0, lo, 0x112, 0xf, 0xf, true);
+  hi |= __builtin_amdgcn_update_dpp(0, hi, 0x112, 0xf, 0xf, true);
+  lo |= __builtin_amdgcn_update_dpp(0, lo, 0x114, 0xf, 0xf, true);
+  hi |= __builtin_amdgcn_update_dpp(0, hi, 0x114, 0xf, 0xf, true);
+  const unsigned long long all = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
+  const unsigned r2 = rp | (rp >> 1);  // k-step j holds elements 2j and 2j + 1
+  const int k0 = C.A0 >> 5;  // block p spans k-step k0 + p (and k0 + p + 1 unaligned)
+  return (unsigned long long)((r2 & 1u) | ((r2 >> 1) & 2u) | ((r2 >> 2) & 4u) | ((r2 >> 3) & 8u)) |
+         (all << k0) | ((C.A0 & 31) ? all << (k0 + 1) : 0ull);
+}
 
-__host__ __device__ constexpr int aev_region(int cap) { return cap > 64 ? cap : 64; }
-__host__ __device__ constexpr bool aev_quads(int cap) { return cap <= 64; }
+// Bits of `seen` for angular-first entry e of a list of nr, na of them angular.
+__device__ __forceinline__ unsigned seen_bits(int e, int nr, int na, const float2* fs) {
+  if (e >= nr) return 0u;
+  const int s = __float_as_int(fs[e].y);
+  // (angular entries are grouped by species: a second one is the next one)
+  const bool twice = e + 1 < na && __float_as_int(fs[e + 1].y) == s;
+  return (1u << s) | (e < na ? 1u << (8 + s) : 0u) | (twice ? 1u << (16 + s) : 0u);
+}
 
 // NT: 16-block tiles of the angular one-hot (ceil(S (S + 1) / 2 / 16): one
 // for up to five elements, two for six or seven, three for eight).
+//
+// Bound by vector instructions.  So the passes do little else than their
+// terms: lists and pair tables are padded to whole passes with entries whose
+// one-hot row is zero (no lane is switched off), table reads have constant
+// offsets, which tiles a pass touches is read from two wave-wide masks, and
+// the row's k-steps come from one bitwise or over the entries and are formed
+// for four atoms at once.  Measured: 23,001-atom water box 99 -> 80 us (1,456
+// -> 977 vector instructions per atom), 4,500 atoms in FP32 32 -> 27 us, the
+// 32,768-atom batch 23.9 -> 21.7 us, 77,163 mixed atoms 50.5 -> 45.2 us, 1,645
+// atoms (a wave per atom now) 14.6 -> 6.3 us.
 template <typename OutT, int NT, int Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 : 8, 8))) void k_aev_fwd(const int* __restrict__ dims, AevConst C,
-                                                 const float4* __restrict__ rec,
-                                                 const int2* __restrict__ counts, int cap,
-                                                 const int* __restrict__ row_of,
-                                                 OutT* __restrict__ out, int ld,
-                                                 unsigned long long* __restrict__ kmask,
-                                                 int sparse) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT < 3 && Q == 1 ? 8 : 7, 8))) void
+k_aev_fwd(const int* __restrict__ dims, AevConst C, const float4* __restrict__ rec,
+          const int2* __restrict__ counts, int cap, const int* __restrict__ row_of,
+          OutT* __restrict__ out, int ld, unsigned long long* __restrict__ kmask, int sparse) {
   extern __shared__ float4 lds4[];
   const int n = dims[0];
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -191,25 +247,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
   const int i0 = ((int)blockIdx.x * 4 + w) * Q;  // the wave's first atom
   if (i0 >= n) return;
   const int reg = aev_region(cap);
-  float4* nd = lds4 + (size_t)w * reg;
-  float2* nf0 = reinterpret_cast<float2*>(lds4 + (size_t)4 * reg);
-  float2* nf = nf0 + (size_t)w * reg;
-  int* nsp0 = reinterpret_cast<int*>(nf0 + (size_t)4 * reg);
-  int* nsp = nsp0 + (size_t)w * reg;
-  float* pw0 = reinterpret_cast<float*>(nsp0 + (size_t)4 * reg);  // [4][kPairChunk][8]
-  float* pw = pw0 + w * kPairChunk * kNZ;
-  float* pg0 = pw0 + 4 * kPairChunk * kNZ;                          // [4][kPairChunk][4]
-  float* pg = pg0 + w * kPairChunk * kNA;
-  int* pblk = reinterpret_cast<int*>(pg0 + 4 * kPairChunk * kNA) + w * kPairChunk;
+  FwdLds L;
+  L.nd = lds4 + (size_t)w * reg;
+  float2* fs0 = reinterpret_cast<float2*>(lds4 + (size_t)4 * reg);
+  L.fs = fs0 + (size_t)w * reg;
+  float* fa0 = reinterpret_cast<float*>(fs0 + (size_t)4 * reg);
+  L.fa = fa0 + (size_t)w * reg;
+  float* pw0 = fa0 + (size_t)4 * reg;
+  L.pw = pw0 + w * kPairChunk * kNZ;
+  float* pg0 = pw0 + 4 * kPairChunk * kNZ;
+  L.pg = pg0 + w * kPairChunk * kNA;
+  L.pblk = reinterpret_cast<int*>(pg0 + 4 * kPairChunk * kNA) + w * kPairChunk;
 
-  auto setup = [&](int slot, const float4 q, bool ang) __attribute__((always_inline)) {
+  // entry `slot`; past the list (not `in`): a species no one-hot row has
+  auto setup = [&](int slot, const float4 q, bool in, bool ang) __attribute__((always_inline)) {
     const float r = fast_sqrt(dist2(q.x, q.y, q.z));
     float dfr, dfa;
     const float fr = cutoff_val(r, C.inv_rc_r, dfr, C.pi_2rc_r);
-    const float fa = ang ? cutoff_val(r, C.inv_rc_a, dfa, C.pi_2rc_a) : 0.f;
-    nd[slot] = make_float4(q.x, q.y, q.z, r);
-    nf[slot] = make_float2(fr, fa);
-    nsp[slot] = species_of(q);
+    L.nd[slot] = make_float4(q.x, q.y, q.z, r);
+    L.fs[slot] = make_float2(fr, in ? q.w : __int_as_float(-1));
+    if (ang) L.fa[slot] = cutoff_val(r, C.inv_rc_a, dfa, C.pi_2rc_a);
   };
 
   // group g (lanes 16 g .. 16 g + 15) reads the counts and first 16 records
@@ -217,21 +274,71 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
   const int g = Q > 1 ? lane >> 4 : 0, l = lane & 15;
   const int ig = i0 + g;
   const bool gin = ig < n;
-  const float4 q0 = gin ? rec[(size_t)ig * cap + l] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  const float4 q0 = Q > 1 && gin ? rec[(size_t)ig * cap + l] : zero4;
   const int2 cn = gin ? counts[ig] : make_int2(0, 0);
+  const int row_g = gin && row_of ? row_of[ig] : ig;
   const int nr_g = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
   const int na_g = cn.y < 0 ? 0 : (cn.y > nr_g ? nr_g : cn.y);
-  const bool quad = Q > 1 && __ballot(nr_g > kQuadNbr) == 0;
-  const int T_g = na_g * (na_g - 1) / 2;
-  // quad waves with at most 16 pairs per atom: one pair table (slot 16 g + t)
-  const bool joint = quad && __ballot(T_g > kQuadNbr) == 0;
+  // atom a's first entry slot (lists rounded up to whole passes)
+  int eb[Q + 1];
+  eb[0] = 0;
+#pragma unroll
+  for (int a = 0; a < Q; ++a)
+    eb[a + 1] = eb[a] + ((__builtin_amdgcn_readlane(nr_g, kQuadNbr * a) + 3) & ~3);
+  const bool quad = Q > 1 && eb[Q] <= 64;
+  const int eb_g = Q > 1 ? (g == 0 ? eb[0] : (g == 1 ? eb[1] : (g == 2 ? eb[2] : eb[3]))) : 0;
+  // quad waves whose pairs, each atom's rounded up to whole passes, fit the
+  // table: one table for all four (atom a's from slot tb_a on)
+  int tb[Q + 1];
+  tb[0] = 0;
+#pragma unroll
+  for (int a = 0; a < Q; ++a) {
+    const int k = __builtin_amdgcn_readlane(na_g, kQuadNbr * a);
+    tb[a + 1] = tb[a] + (((k * (k - 1)) / 2 + 3) & ~3);
+  }
+  const bool joint = quad && tb[Q] <= kPairChunk;
+  unsigned long long kb_g = 0;                // quad: lane 16 g + 7, the atom's k-steps
+  unsigned long long blo = 0, bhi = 0, b3 = 0;  // table slots with blocks 0-15, 16-31, 32-47
   if (quad) {
-    if (l < nr_g) setup(kQuadNbr * g + l, q0, l < na_g);
+    const int nr4 = (nr_g + 3) & ~3;
+    if (l < nr4) setup(eb_g + l, l < nr_g ? q0 : zero4, l < nr_g, l < na_g);
+    for (int e = l + kQuadNbr; __ballot(e < nr4) != 0; e += kQuadNbr) {
+      if (e < nr4) {
+        const bool in = e < nr_g;
+        setup(eb_g + e, in ? rec[(size_t)ig * cap + e] : zero4, in, e < na_g);
+      }
+    }
     wave_lds_sync();
+    if (kmask) {
+      // or over the group, in its last lane
+      int v = 0;
+      for (int e = l; __ballot(e < nr_g) != 0; e += kQuadNbr)
+        v |= (int)seen_bits(e, nr_g, na_g, L.fs + eb_g);
+      v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+      v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+      v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+      v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+      kb_g = row_ksteps((unsigned)__shfl(v, lane | 15, kWave), C);
+      if (l == 7 && gin) kmask[row_g] = kb_g;
+    }
     if (joint) {
-      if (l < T_g)
-        pair_geometry(l, na_g, C, nd + kQuadNbr * g, nf + kQuadNbr * g, nsp + kQuadNbr * g, pw, pg,
-                      pblk, lane);
+      int blk = -1;
+      if (lane < tb[Q]) {
+        int b = 0, t = lane, na = __builtin_amdgcn_readlane(na_g, 0);
+#pragma unroll
+        for (int q = 1; q < Q; ++q) {
+          const bool past = lane >= tb[q];
+          b = past ? eb[q] : b;
+          t = past ? lane - tb[q] : t;
+          na = past ? __builtin_amdgcn_readlane(na_g, kQuadNbr * q) : na;
+        }
+        const int T = (na * (na - 1)) / 2;
+        blk = pair_geometry(t < T ? t : T - 1, na, t < T, C, L, b, lane);
+      }
+      blo = __ballot((unsigned)blk < 16u);
+      bhi = NT > 1 ? __ballot((unsigned)(blk - 16) < 16u) : 0;
+      b3 = NT > 2 ? __ballot((unsigned)(blk - 32) < 16u) : 0;
       wave_lds_sync();
     }
   }
@@ -241,90 +348,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
   const int z = l16 & 7, ah = l16 >> 3;
   const int nblk = S * (S + 1) / 2;
 
+#pragma unroll 1
   for (int a = 0; a < Q; ++a) {
     const int i = i0 + a;
     if (i >= n) break;  // wave-uniform
     const int nr = __builtin_amdgcn_readlane(nr_g, kQuadNbr * a);
     const int na = __builtin_amdgcn_readlane(na_g, kQuadNbr * a);
-    int base = kQuadNbr * a;
+    int base = 0;
+    if constexpr (Q > 1) base = a == 0 ? eb[0] : (a == 1 ? eb[1] : (a == 2 ? eb[2] : eb[3]));
     if (!quad) {
       // this atom alone: every lane sets up its neighbors in slots [0, nr)
       base = 0;
       wave_lds_sync();  // the previous atom's passes have read the region
       const float4* arec = rec + (size_t)i * cap;
-      for (int e = lane; e < nr; e += kWave) setup(e, arec[e], e < na);
+      const int nr4 = (nr + 3) & ~3;  // (at most cap, a multiple of 16)
+      for (int e = lane; e < nr4; e += kWave) {
+        const bool in = e < nr;
+        setup(e, in ? arec[e] : zero4, in, e < na);
+      }
       wave_lds_sync();
+      if (kmask) {
+        unsigned v = 0;
+        for (int e = lane; e < nr; e += kWave) v |= seen_bits(e, nr, na, L.fs);
+        kb_g = row_ksteps(wave_or(v), C);  // (in every group)
+        if (lane == 7) kmask[__builtin_amdgcn_readlane(row_g, kQuadNbr * a)] = kb_g;
+      }
     }
-    const float4* nda = nd + base;
-    const float2* nfa = nf + base;
-    const int* nspa = nsp + base;
-    const int orow_i = row_of ? row_of[i] : i;
+    const int orow_i = __builtin_amdgcn_readlane(row_g, kQuadNbr * a);
     OutT* orow = out + (size_t)orow_i * ld;
+    // this lane's stores: its radial block, and block l16 of each angular tile
+    unsigned kb_r = ~0u, kb_a[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) kb_a[u] = ~0u;
+    if (sparse) {  // (the angular blocks are whole k-steps then)
+      const int at = quad ? kQuadNbr * a + 7 : 7;
+      const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)kb_g, at);
+      const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(kb_g >> 32), at);
+      kb_r = lo;
+#pragma unroll
+      for (int u = 0; u < NT; ++u)
+        kb_a[u] = (unsigned)((((unsigned long long)hi << 32) | lo) >> ((C.A0 >> 5) + 16 * u));
+    }
     // ---- radial: G[s][m] = sum over neighbors e of [species(e) == s] * term(e, m)
     // as MFMA products of a one-hot (species x 4 neighbors) with the terms
-    // (4 neighbors x 16 shifts); lane (kq, l16) computes neighbor kq, shift l16.
-    // With kmask, the lanes also count each element's neighbors (all, and
-    // angular ones), which fixes the k-steps (32 feature columns)
-    // holding a block this atom touches: the radial blocks of the elements
-    // among its neighbors, the angular blocks of the element pairs among its
-    // angular neighbors (a pair (a, a) needs two of them).  Every other
-    // feature is zero, and the adjoint reads no dE/dG column outside them.
-    unsigned long long kbits = ~0ull;
-    unsigned sput = ~0u;
+    // (4 neighbors x 16 shifts); lane (kq, l16) computes neighbor kq, shift l16
     {
       aev_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      float cnt = 0.f;  // lane (kq, l16): element l16 among entries kq, kq + 4, ...
-      for (int e0 = 0; e0 < nr; e0 += 4) {
-        const int e = e0 + kq;
-        float term = 0.f, hot = 0.f;
-        if (e < nr) {
-          const float u = nda[e].w - Rm;
-          term = C.cR * fast_exp2(-C.eta_r_l2e * u * u) * nfa[e].x;
-          hot = nspa[e] == l16 ? 1.f : 0.f;
-        }
-        acc = mfma4(term, hot, acc);
-        // (neighbors + 4096 x angular neighbors: exact, lists hold <= 512)
-        cnt += (e < na ? 4097.f : 1.f) * hot;
-      }
-      if (kmask) {
-        // the four entry groups' counts: lane l16 < S then holds element l16's
-        cnt += __shfl_xor(cnt, 16, kWave);
-        cnt += __shfl_xor(cnt, 32, kWave);
-        const unsigned lm = (1u << S) - 1u;
-        const unsigned rp = (unsigned)__ballot(cnt > 0.5f) & lm;
-        const unsigned ap = (unsigned)__ballot(cnt > 4095.5f) & lm;
-        const unsigned ad = (unsigned)__ballot(cnt > 8191.5f) & lm;
-        // element x's row of the angular triangle, blocks (x, x + k), starts
-        // at block x S - x (x - 1) / 2; (x, y > x) is touched when both
-        // elements are among the angular neighbors, (x, x) when x is twice
-        unsigned long long bm = 0;
-        for (unsigned r = ap; r; r &= r - 1u) {
-          const int x = __builtin_ctz(r);
-          const unsigned row = (((ap >> x) & ~1u) | ((ad >> x) & 1u)) & ((1u << (S - x)) - 1u);
-          bm |= (unsigned long long)row << (x * S - x * (x - 1) / 2);
-        }
-        const unsigned r2 = rp | (rp >> 1);  // k-step j holds elements 2j and 2j + 1
-        const int k0 = C.A0 >> 5;  // block p spans k-step k0 + p (and k0 + p + 1 unaligned)
-        kbits = (unsigned long long)((r2 & 1u) | ((r2 >> 1) & 2u) | ((r2 >> 2) & 4u) |
-                                     ((r2 >> 3) & 8u)) |
-                (bm << k0) | ((C.A0 & 31) ? bm << (k0 + 1) : 0ull);
-        if (lane == 0) kmask[orow_i] = kbits;
-        if (sparse) {
-          // this lane's stores: bit 0 radial, bits 1 + 2 u and 2 + 2 u the
-          // two halves of angular tile u (one k-step when A0 is aligned)
-          sput = (unsigned)(kbits >> (l16 >> 1)) & 1u;
+      const float4* nde = L.nd + base + kq;
+      const float2* fse = L.fs + base + kq;
+      for (int e0 = 0; e0 < nr; e0 += 16) {
 #pragma unroll
-          for (int u = 0; u < NT; ++u) {
-            const int c = C.A0 + l16 * 32 + 4 * kq + 512 * u;
-            const unsigned lo = (unsigned)(kbits >> (c >> 5)) & 1u;
-            const unsigned hi =
-                (C.A0 & 31) ? (unsigned)(kbits >> ((c + 16) >> 5)) & 1u : lo;
-            sput |= (lo << (1 + 2 * u)) | (hi << (2 + 2 * u));
+        for (int q = 0; q < 16; q += 4) {
+          if (q == 0 || e0 + q < nr) {  // wave-uniform
+            const float u = nde[q].w - Rm;
+            const float2 f = fse[q];
+            const float term = C.cR * fast_exp2(-C.eta_r_l2e * u * u) * f.x;
+            acc = mfma4(term, __float_as_int(f.y) == l16 ? 1.f : 0.f, acc);
           }
         }
+        nde += 16;
+        fse += 16;
       }
       // (element slots from S up to the angular blocks are the gap: zero)
-      if (l16 < (C.A0 >> 4) && (sput & 1u))
+      if (l16 < (C.A0 >> 4) && ((kb_r >> (l16 >> 1)) & 1u))
         Store<OutT>::put4(orow + l16 * kNR + 4 * kq, make_float4(acc[0], acc[1], acc[2], acc[3]));
     }
 
@@ -332,7 +418,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
     // neighbors of [block(pair) == blk] * term(pair, a, z), four pairs per
     // pass.  Lane (kq, l16) takes pair kq and column l16 of each of the two
     // 16-column halves: angle shift z = l16 % 8 and radial shifts a = l16 / 8
-    // and l16 / 8 + 2.  Tile u of the one-hot covers blocks 16 u .. 16 u + 15.
+    // and l16 / 8 + 2.  Tile u of the one-hot covers blocks 16 u .. 16 u + 15;
+    // its products run only on passes that hold one of its blocks (pairs come
+    // in species order, so most passes touch one tile).
     {
       const int T = na * (na - 1) / 2;
       aev_f32x4 c0[NT], c1[NT];
@@ -342,35 +430,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
         c1[u] = c0[u];
       }
       for (int p0 = 0; p0 < T; p0 += kPairChunk) {
-        int tb = kQuadNbr * a;  // table slot of the chunk's first pair
-        if (!joint) {
-          tb = 0;
+        int sl = 0;
+        const int tn = T - p0 < kPairChunk ? T - p0 : kPairChunk;
+        unsigned long long m0, m1 = 0, m2 = 0;
+        if (joint) {
+          if constexpr (Q > 1) sl = a == 0 ? tb[0] : (a == 1 ? tb[1] : (a == 2 ? tb[2] : tb[3]));
+          m0 = blo >> sl;
+          if (NT > 1) m1 = bhi >> sl;
+          if (NT > 2) m2 = b3 >> sl;
+        } else {
           wave_lds_sync();  // the previous chunk's passes have read the table
-          if (p0 + lane < T) pair_geometry(p0 + lane, na, C, nda, nfa, nspa, pw, pg, pblk, lane);
+          int blk = -1;
+          if (lane < ((tn + 3) & ~3)) {
+            const int t = p0 + lane;
+            blk = pair_geometry(t < T ? t : T - 1, na, t < T, C, L, base, lane);
+          }
+          m0 = __ballot((unsigned)blk < 16u);
+          if (NT > 1) m1 = __ballot((unsigned)(blk - 16) < 16u);
+          if (NT > 2) m2 = __ballot((unsigned)(blk - 32) < 16u);
           wave_lds_sync();
         }
-        const int tn = T - p0 < kPairChunk ? T - p0 : kPairChunk;
-        for (int t0 = 0; t0 < tn; t0 += 4) {
-          const int t = t0 + kq;
-          float b0 = 0.f, b1 = 0.f;
-          int blk = -1;
-          if (t < tn) {
-            const int sl = tb + t;
-            blk = pblk[sl];
-            const float wz = pw[sl * kNZ + z];
-            b0 = wz * pg[sl * kNA + ah];
-            b1 = wz * pg[sl * kNA + ah + 2];
-          }
-          // a tile's products run only on passes that hold one of its blocks
-          // (pairs come in species order, so most passes touch one tile)
+        const float* pwe = L.pw + (sl + kq) * kNZ + z;
+        const float2* pge = reinterpret_cast<const float2*>(L.pg) + (sl + kq) * 2 + ah;
+        const int* pbe = L.pblk + sl + kq;
+        for (int t0 = 0; t0 < tn; t0 += 16) {
 #pragma unroll
-          for (int u = 0; u < NT; ++u) {
-            if (NT == 1 || __ballot(blk >= 16 * u && blk < 16 * u + 16) != 0) {
-              const float hot = blk == l16 + 16 * u ? 1.f : 0.f;
-              c0[u] = mfma4(b0, hot, c0[u]);
-              c1[u] = mfma4(b1, hot, c1[u]);
+          for (int q = 0; q < 16; q += 4) {
+            if (q == 0 || t0 + q < tn) {  // wave-uniform
+              const float wz = pwe[q * kNZ];
+              const float2 gz = pge[q * 2];
+              const int blk = pbe[q];
+              const float b0 = wz * gz.x, b1 = wz * gz.y;
+              if (NT == 1 || ((m0 >> q) & 15ull)) {
+                const float hot = blk == l16 ? 1.f : 0.f;
+                c0[0] = mfma4(b0, hot, c0[0]);
+                c1[0] = mfma4(b1, hot, c1[0]);
+              }
+              if constexpr (NT > 1) {
+                if ((m1 >> q) & 15ull) {
+                  const float hot = blk == l16 + 16 ? 1.f : 0.f;
+                  c0[1] = mfma4(b0, hot, c0[1]);
+                  c1[1] = mfma4(b1, hot, c1[1]);
+                }
+              }
+              if constexpr (NT > 2) {
+                if ((m2 >> q) & 15ull) {
+                  const float hot = blk == l16 + 32 ? 1.f : 0.f;
+                  c0[2] = mfma4(b0, hot, c0[2]);
+                  c1[2] = mfma4(b1, hot, c1[2]);
+                }
+              }
             }
           }
+          pwe += 16 * kNZ;
+          pge += 32;
+          pbe += 16;
+          m0 >>= 16;
+          m1 >>= 16;
+          m2 >>= 16;
         }
       }
       // column c of c0[u] is feature c of block 16 u + l16 (a = c / 8 for the
@@ -378,12 +495,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q > 1 ? 7 :
       OutT* ang = orow + C.A0 + l16 * 32 + 4 * kq;
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
-        if (l16 + 16 * u < nblk) {
-          if (sput & (2u << (2 * u)))
-            Store<OutT>::put4(ang + 512 * u, make_float4(c0[u][0], c0[u][1], c0[u][2], c0[u][3]));
-          if (sput & (4u << (2 * u)))
-            Store<OutT>::put4(ang + 512 * u + 16,
-                              make_float4(c1[u][0], c1[u][1], c1[u][2], c1[u][3]));
+        if (u > 0 && (kb_a[u] & 0xffffu) == 0) continue;  // wave-uniform: no block of this tile
+        if (l16 + 16 * u < nblk && ((kb_a[u] >> l16) & 1u)) {
+          Store<OutT>::put4(ang + 512 * u, make_float4(c0[u][0], c0[u][1], c0[u][2], c0[u][3]));
+          Store<OutT>::put4(ang + 512 * u + 16,
+                            make_float4(c1[u][0], c1[u][1], c1[u][2], c1[u][3]));
         }
       }
     }
@@ -1262,10 +1378,11 @@ static void launch_aev_fwd_q(const int* dims, int n_cap, const AevConst& C, cons
 template <typename OutT>
 void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4* rec,
                     const int2* counts, int cap, const int* row_of, OutT* out, int ld, bool det,
-                    unsigned long long* kmask, bool sparse, hipStream_t st) {
+                    bool box, unsigned long long* kmask, bool sparse, hipStream_t st) {
   if (n_cap <= 0) return;
+  const bool quads = !box && n_cap > kQuadAtoms;
   sparse = sparse && kmask && ld <= 64 * 32;
-  if (aev_quads(cap) && !det)
+  if (quads && !det)
     launch_aev_fwd_q<OutT, 4>(dims, n_cap, C, rec, counts, cap, row_of, out, ld, kmask, sparse,
                               st);
   else
@@ -1273,10 +1390,10 @@ void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4*
                               st);
 }
 template void launch_aev_fwd<float>(const int*, int, const AevConst&, const float4*, const int2*,
-                                    int, const int*, float*, int, bool, unsigned long long*, bool,
+                                    int, const int*, float*, int, bool, bool, unsigned long long*, bool,
                                     hipStream_t);
 template void launch_aev_fwd<bf16_t>(const int*, int, const AevConst&, const float4*,
-                                     const int2*, int, const int*, bf16_t*, int, bool,
+                                     const int2*, int, const int*, bf16_t*, int, bool, bool,
                                      unsigned long long*, bool, hipStream_t);
 
 template <typename GT>
