@@ -39,7 +39,6 @@ struct nnp_handle {
   size_t n_params = 0;                  // all members
   long param_off[kMaxModels * kMaxS][kLayers] = {};  // flat offset of W for (slot, layer)
   char* dmem = nullptr;
-  float* flat = nullptr;
   bool net = false;            // the fused network takes these widths (net_widths)
   // weight copies, those that the precision's kernels read (null otherwise)
   float* Wf[kLayers] = {};     // row-major W and W^T (LDS-staged kernels)
@@ -734,7 +733,6 @@ nnp_status nnp_create_ensemble(const nnp_aev_params* aev, const nnp_mlp_params* 
     bytes = align_up(bytes + b, 256);
     return a;
   };
-  const size_t o_flat = take(o * 4);
   // the copies of W and W^T that the handle's kernels read: fragment order
   // (the fused network; BF16 layer kernels, whose head also reads W
   // row-major), or row-major (FP32 layer kernels)
@@ -763,7 +761,6 @@ nnp_status nnp_create_ensemble(const nnp_aev_params* aev, const nnp_mlp_params* 
     delete h;
     return NNP_E_OOM;
   }
-  h->flat = reinterpret_cast<float*>(h->dmem + o_flat);
   for (int l = 0; l < kLayers - 1; ++l) {
     if (bf) {
       if (rows) h->Wb[l] = reinterpret_cast<bf16_t*>(h->dmem + o_w[l]);
@@ -800,16 +797,23 @@ nnp_status nnp_create_ensemble(const nnp_aev_params* aev, const nnp_mlp_params* 
   std::vector<long> po((size_t)kLayers * S);
   for (int l = 0; l < kLayers; ++l)
     for (int s = 0; s < S; ++s) po[(size_t)l * S + s] = h->param_off[s][l];
-  bool ok = true;
+  float* flat = nullptr;  // the parameters on the device while they are packed
+  bool ok = hip_ok(hipMalloc(&flat, h->n_params * 4));
+  if (!ok) {
+    (void)hipGetLastError();
+    (void)hipFree(h->dmem);
+    delete h;
+    return NNP_E_OOM;
+  }
   for (int k = 0; k < n_models && ok; ++k)
-    ok = hip_ok(hipMemcpy(h->flat + k * per_model, mlps[k].params, per_model * 4,
+    ok = hip_ok(hipMemcpy(flat + k * per_model, mlps[k].params, per_model * 4,
                           hipMemcpyHostToDevice));
   ok = ok && hip_ok(hipMemcpy(h->eself, es, sizeof(es), hipMemcpyHostToDevice)) &&
             hip_ok(hipMemcpy(h->param_off_dev, po.data(), po.size() * 8, hipMemcpyHostToDevice)) &&
             hip_ok(hipMemcpy(const_cast<float*>(C.lane_tab), lane_host, sizeof(lane_host),
                              hipMemcpyHostToDevice));
-  if (ok) ok = nnp_set_params_device(h, h->flat, nullptr) == NNP_OK &&
-               hip_ok(hipDeviceSynchronize());
+  if (ok) ok = nnp_set_params_device(h, flat, nullptr) == NNP_OK && hip_ok(hipDeviceSynchronize());
+  (void)hipFree(flat);
   if (!ok) {
     (void)hipFree(h->dmem);
     delete h;
@@ -832,12 +836,8 @@ size_t nnp_param_count(const nnp_handle* h) { return h ? h->n_params : 0; }
 nnp_status nnp_set_params_device(nnp_handle* h, const float* params_dev, void* stream) {
   if (!h || !params_dev) return NNP_E_INVALID;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (params_dev != h->flat &&
-      hipMemcpyAsync(h->flat, params_dev, h->n_params * 4, hipMemcpyDeviceToDevice, st) !=
-          hipSuccess)
-    return NNP_E_HIP;
   PackArgs p{};
-  p.flat = h->flat;
+  p.flat = params_dev;
   const int Q = h->n_models * h->S;
   for (int q = 0; q < Q; ++q)
     for (int l = 0; l < kLayers; ++l) p.off[q * kLayers + l] = h->param_off[q][l];

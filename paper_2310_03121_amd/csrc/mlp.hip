@@ -1236,21 +1236,71 @@ template void launch_wgrad_net<bf16_t>(const GroupTable*, int, int, int, const W
 // W_l^T [S][in_pad][out] row-major (float), the LDS-staged kernels' operands;
 // W_l and W_l^T in MFMA fragment order (bf16 or float), the fused network's
 // and the register-streamed kernels' operands; biases [S][out], output
-// weights [S][w3] and output biases [S].  One thread per (species, layer, out, in_pad).
+// weights [S][w3] and output biases [S].
 //
 // Fragment order of a [N][K] operand: 16-row tiles, then k-steps of KS, then
 // the 64 lanes of the wave, then the EL elements of a lane; lane l of k-step
 // ks in tile nt holds row nt*16 + l % 16, columns ks*KS + (l / 16)*EL + e.
-// A wave's fragment is then one contiguous 1 KB block.
-template <typename T>
-__device__ __forceinline__ size_t frag_off(int n, int k, int K) {
-  constexpr int KS = Frag<T>::KS, EL = Frag<T>::EL;
-  const int kk = k % KS;
-  const int lane = (kk / EL) * 16 + n % 16;
-  return (((size_t)(n / 16) * (K / KS) + k / KS) * 64 + lane) * EL + kk % EL;
+// A wave's fragment is then one contiguous 1 KB block.  One thread packs one
+// lane's 16 bytes of a fragment (so a wave writes whole fragments; one thread
+// per weight scattered 2- and 4-byte stores: 22 us for the 2.4 M weights of
+// seven elements in one precision and both orders, now 12 us).
+
+// Layer 1: inputs from r0 on sit at columns from a0 on (zero between).
+__device__ __forceinline__ float packed_weight(const float* __restrict__ W, int o, int c, int in,
+                                               int r0, int a0) {
+  const int i = c >= r0 ? c - (a0 - r0) : c;
+  return (c < r0 || c >= a0) && i < in ? W[(size_t)o * in + i] : 0.f;
 }
 
-__global__ __launch_bounds__(256) void k_pack(PackArgs p) {
+// blockIdx.y: layer and operand (2 l: W_l, 2 l + 1: W_l^T; then the output
+// layer, and of an ensemble the member-concatenated W_0^T); z: weight slot.
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack_frag(PackArgs p) {
+  constexpr int KS = Frag<T>::KS, EL = Frag<T>::EL;
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  const int s = blockIdx.z, what = blockIdx.y;
+  const bool cat = what == 2 * (kLayers - 1) + 1;
+  const int l = cat ? 0 : what >> 1;
+  const float* src = p.flat + p.off[s * kLayers + l];
+  const int in = p.width[l], out = p.width[l + 1];
+  if (l == kLayers - 1) {
+    if (t < in) p.wout[(size_t)s * in + t] = src[t];
+    if (t == 0) p.bout[s] = src[in];
+    return;
+  }
+  const int inp = l == 0 ? p.Fp : in, r0 = l == 0 ? p.r0 : in, a0 = l == 0 ? p.a0 : in;
+  const bool tr = (what & 1) != 0;  // W^T (rows are inputs)
+  const int N = tr ? inp : out, K = tr ? out : inp;
+  if (!tr && t < out) p.bias[l][(size_t)s * out + t] = src[(size_t)out * in + t];
+  if (t >= N * K / EL) return;
+  const int lane = t & 63, f = t >> 6, ks = f % (K / KS), nt = f / (K / KS);
+  const int n = nt * 16 + (lane & 15), k = ks * KS + (lane >> 4) * EL;
+  float v[EL];
+#pragma unroll
+  for (int e = 0; e < EL; ++e)
+    v[e] = tr ? packed_weight(src, k + e, n, in, r0, a0) : packed_weight(src, n, k + e, in, r0, a0);
+  uint4 u;
+  T* dst;
+  if constexpr (sizeof(T) == 2) {
+    u = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+    dst = cat ? p.WT0cq : (tr ? p.WTqb[l] : p.Wqb[l]);
+  } else {
+    u = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
+                   __float_as_uint(v[3]));
+    dst = cat ? p.WT0cqf : (tr ? p.WTqf[l] : p.Wqf[l]);
+  }
+  size_t at = (size_t)s * N * K + (size_t)t * EL;
+  if (cat) {
+    // member k's W_0^T as columns [k out, (k + 1) out) of one K = M out operand
+    const int m = s / p.S, e = s % p.S, kc = K / KS;
+    at = ((((size_t)e * (N / 16) + nt) * (p.n_models * kc) + m * kc + ks) * 64 + lane) * EL;
+  }
+  *reinterpret_cast<uint4*>(dst + at) = u;
+}
+
+// Row-major copies (layer kernels): one thread per (slot, layer, out, in_pad).
+__global__ __launch_bounds__(256) void k_pack_rows(PackArgs p) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int l = blockIdx.y, s = blockIdx.z;  // s: weight slot (member * S + element)
   const int in = p.width[l], out = p.width[l + 1];
@@ -1259,30 +1309,15 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs p) {
   if (l < kLayers - 1) {
     if (t >= (long)out * inp) return;
     const int o = (int)(t / inp), i = (int)(t % inp);
-    // layer 1: inputs from r0 on sit at columns from a0 on (zero between)
-    const int pi = l == 0 && i >= p.r0 ? i - (p.a0 - p.r0) : i;
-    const bool on = pi < in && (l != 0 || i < p.r0 || i >= p.a0);
-    const float v = on ? src[(size_t)o * in + pi] : 0.f;
+    const float v = packed_weight(src, o, i, in, l == 0 ? p.r0 : in, l == 0 ? p.a0 : in);
     const size_t ws = (size_t)s * out * inp;
     if (p.Wf[l]) p.Wf[l][ws + (size_t)o * inp + i] = v;
     if (p.Wb[l]) p.Wb[l][ws + (size_t)o * inp + i] = f2bf(v);
     if (p.WTf[l]) p.WTf[l][ws + (size_t)i * out + o] = v;
-    if (p.Wqb[l]) {
-      p.Wqb[l][ws + frag_off<bf16_t>(o, i, inp)] = f2bf(v);
-      p.WTqb[l][ws + frag_off<bf16_t>(i, o, out)] = f2bf(v);
-    }
-    if (p.Wqf[l]) {
-      p.Wqf[l][ws + frag_off<float>(o, i, inp)] = v;
-      p.WTqf[l][ws + frag_off<float>(i, o, out)] = v;
-    }
     if (i == 0) p.bias[l][(size_t)s * out + o] = src[(size_t)out * in + o];
-    if (l == 0 && p.n_models > 1) {
-      // member k's W_0^T as columns [k out, (k + 1) out) of one K = M out operand
+    if (l == 0 && p.WT0cf) {
       const int k = s / p.S, e = s % p.S, KM = p.n_models * out;
-      const size_t wc = (size_t)e * inp * KM;
-      if (p.WT0cf) p.WT0cf[wc + (size_t)i * KM + (size_t)k * out + o] = v;
-      if (p.WT0cq) p.WT0cq[wc + frag_off<bf16_t>(i, k * out + o, KM)] = f2bf(v);
-      if (p.WT0cqf) p.WT0cqf[wc + frag_off<float>(i, k * out + o, KM)] = v;
+      p.WT0cf[(size_t)e * inp * KM + (size_t)i * KM + (size_t)k * out + o] = v;
     }
   } else {
     if (t >= in) return;
@@ -1298,8 +1333,17 @@ void launch_pack(const PackArgs& p, int slots, hipStream_t st) {
     const long el = (long)p.width[l + 1] * inp;
     maxel = el > maxel ? el : maxel;
   }
-  dim3 grid((unsigned)((maxel + 255) / 256), kLayers, slots);
-  hipLaunchKernelGGL(k_pack, grid, dim3(256), 0, st, p);
+  if (p.Wf[0] || p.Wb[0])
+    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((maxel + 255) / 256), kLayers, slots),
+                       dim3(256), 0, st, p);
+  const bool cat = p.WT0cq || p.WT0cqf;
+  const unsigned ny = 2 * (kLayers - 1) + 1 + (cat ? 1 : 0);
+  if (p.Wqb[0])
+    hipLaunchKernelGGL(k_pack_frag<bf16_t>, dim3((unsigned)((maxel / 8 + 255) / 256), ny, slots),
+                       dim3(256), 0, st, p);
+  if (p.Wqf[0])
+    hipLaunchKernelGGL(k_pack_frag<float>, dim3((unsigned)((maxel / 4 + 255) / 256), ny, slots),
+                       dim3(256), 0, st, p);
 }
 
 }  // namespace nnp
