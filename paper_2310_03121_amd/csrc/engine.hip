@@ -75,7 +75,12 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
-constexpr int kWChunk = 1024;  // rows per weight-gradient partial
+// Rows per weight-gradient partial: 1,024, or fewer for small systems so that
+// about 24 chunks spread over the GPU (8,192 atoms in FP32: 87 us for the
+// weight gradients in chunks of 1,024 rows, 46 us in chunks of 384).
+int wgrad_chunk_rows(int n) {
+  return std::min(1024, std::max(128, (n / 24 + 127) / 128 * 128));
+}
 
 // Device address of `scratch` on device `dev`: looked up once per device
 // (with that device current) by hipGetSymbolAddress, then cached.  Returns
@@ -156,13 +161,13 @@ struct StageTimer {
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Plan {
-  int n = 0, nmol = 0, rows_cap = 0, cap = 0, nblk = 0, nwchunks = 0;
+  int n = 0, nmol = 0, rows_cap = 0, cap = 0, nblk = 0, nwchunks = 0, wchunk = 0;
   BoxConst B{};
   int ncell = 0;
   size_t total = 0;
   size_t status, dims, gt, xyzs, mol, mrange, row, perm, hist, nbr, counts, rec;
   size_t cell_of, cell_cnt, cell_start, cursor, cell_atoms, cell_xyzs;
-  size_t X, H1, H2, H3, D3, D2, D1, G, erow, uprow, wpart, pos32;
+  size_t X, H1, H2, H3, D3, D2, D1, G, erow, uprow, wpart, wact, pos32;
   size_t kmask;  // per feature row: the k-steps that may be nonzero
   size_t pgrad;  // deterministic mode: per-entry adjoint rows [n][cap]
   size_t grp;    // owned/ghost evaluation: group offsets (3 int) and upstream (2 double)
@@ -243,7 +248,8 @@ Plan make_plan(const nnp_handle* h, int n, int nmol, const BoxConst& B, bool wgr
   P.ncell = B.periodic ? B.nc[0] * B.nc[1] * B.nc[2] : 0;
   P.rows_cap = (int)align_up((size_t)std::max(n, 1), kPad) + h->S * kPad;
   P.nblk = stage_blocks(n);
-  P.nwchunks = (n + kWChunk - 1) / kWChunk + h->S;
+  P.wchunk = wgrad_chunk_rows(n);
+  P.nwchunks = (n + P.wchunk - 1) / P.wchunk + h->S;
   const size_t esz = h->prec == NNP_MLP_BF16 ? 2 : 4;
   const size_t R = (size_t)P.rows_cap;
   const size_t N = (size_t)std::max(n, 1);
@@ -295,7 +301,8 @@ Plan make_plan(const nnp_handle* h, int n, int nmol, const BoxConst& B, bool wgr
     const size_t in = l == 0 ? h->F : h->width[l];
     plen += (size_t)h->width[l + 1] * in + h->width[l + 1];
   }
-  P.wpart = wgrad ? take((size_t)P.nwchunks * plen * 4) : 0;
+  P.wpart = wgrad ? take((size_t)P.nwchunks * wgrad_part_pitch((long)plen) * 4) : 0;
+  P.wact = wgrad ? take((size_t)P.nwchunks * 64) : 0;
   P.pos32 = take(N * 12);
   P.total = o;
   return P;
@@ -361,10 +368,10 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
                  status, !io.keep_status, P.B.periodic ? at<int>(ws, P.cell_cnt) : nullptr,
                  P.B.periodic ? cell_zero_ints(P.ncell) : 0, st);
     if (P.nblk > kFusedSortBlocks) {
-      launch_groups(dims, P.n, S, hist, gt, perm, P.rows_cap, io.off, kWChunk, status, st);
+      launch_groups(dims, P.n, S, hist, gt, perm, P.rows_cap, io.off, P.wchunk, status, st);
       launch_scatter(dims, P.n, S, xyzs, hist, row, perm, st);
     } else if (P.B.periodic) {
-      launch_sort_scatter(dims, P.n, S, xyzs, hist, gt, row, perm, P.rows_cap, io.off, kWChunk,
+      launch_sort_scatter(dims, P.n, S, xyzs, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
                           status, st);
     }
   }
@@ -372,7 +379,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     StageTimer t(h, io.timed, ST_PAIRS, st);
     if (!P.B.periodic && P.nblk <= kFusedSortBlocks) {
       // molecules: the sort and the pair scan share one launch
-      launch_sort_pairs_mol(dims, P.n, S, hist, gt, row, perm, P.rows_cap, io.off, kWChunk,
+      launch_sort_pairs_mol(dims, P.n, S, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
                             h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
     } else if (P.B.periodic) {
       launch_pairs_cell(dims, P.n, h->C, P.B, xyzs, at<int>(ws, P.cell_of),
@@ -385,12 +392,13 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
   }
   T* X = at<T>(ws, P.X);
   unsigned long long* kmask = at<unsigned long long>(ws, P.kmask);
+  const bool wsparse = wgrad_sparse_fits(w1, Fp, h->F, S * kNR);
   {
     StageTimer t(h, io.timed, ST_AEV, st);
-    // the fused network reads each row's own k-steps only; the weight
-    // gradients and the layer kernels read whole rows
+    // the fused network and layer 1's weight gradients by k-steps read each
+    // row's own k-steps only; the other kernels read whole rows
     launch_aev_fwd<T>(dims, P.n, h->C, rec, counts, P.cap, row, X, Fp, h->deterministic,
-                      P.B.periodic != 0, kmask, h->net && !io.dparams, st);
+                      P.B.periodic != 0, kmask, h->net && (!io.dparams || wsparse), st);
   }
 
   T* H1 = at<T>(ws, P.H1);
@@ -588,8 +596,8 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
         {D3, H2, w3, w2, w3, w2, false},
         {up, H3, 1, w3, 1, w3, true},
     };
-    launch_wgrad_net<T>(gt, S, P.nwchunks, kWChunk, layers, kLayers, part, io.dparams,
-                        h->param_off_dev, st);
+    launch_wgrad_net<T>(gt, S, P.nwchunks, P.wchunk, layers, kLayers, wsparse ? kmask : nullptr,
+                        at<unsigned char>(ws, P.wact), part, io.dparams, h->param_off_dev, st);
   }
   if (!ok) return NNP_E_INVALID;
   return launches_ok() ? NNP_OK : NNP_E_HIP;
@@ -1086,7 +1094,7 @@ nnp_status nnp_debug_aev(nnp_handle* h, int32_t n, int32_t nmol, const float* po
                P.B.periodic ? at<int>(ws, P.cell_cnt) : nullptr, P.B.periodic ? cell_zero_ints(P.ncell) : 0,
                st);
   launch_groups(dims, P.n, h->S, at<int>(ws, P.hist), at<GroupTable>(ws, P.gt),
-                at<int>(ws, P.perm), P.rows_cap, off, kWChunk, status, st);
+                at<int>(ws, P.perm), P.rows_cap, off, P.wchunk, status, st);
   if (P.B.periodic)
     launch_pairs_cell(dims, P.n, h->C, P.B, xyzs, at<int>(ws, P.cell_of), at<int>(ws, P.cell_cnt),
                       at<int>(ws, P.cell_start), at<int>(ws, P.cursor), at<int>(ws, P.cell_atoms),

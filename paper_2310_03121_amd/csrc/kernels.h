@@ -215,7 +215,9 @@ bool launch_gemm(int epi, const GemmArgs& a, int rows_cap, hipStream_t st);
 // one launch (plus one per layer whose widths the MFMA tiles do not take),
 // then the chunk-ordered sum into dparams[param_off_dev[s] + e], e over the
 // element's whole flat parameter vector.  partial holds n_chunks_cap times
-// that vector's length in floats.
+// wgrad_part_pitch of that vector's length in floats.  kmask (null unless
+// wgrad_sparse_fits and chunk <= 1,024): the feature rows' k-steps; layer 1
+// reads only those (act: n_chunks_cap * 64 bytes).
 struct WgradLayer {
   const void* D;  // [rows][ldd] adjoint of the layer's output
   const void* H;  // [rows][ldh] the layer's input
@@ -225,9 +227,13 @@ struct WgradLayer {
   // i + hgap from hgap0 on (the feature rows' gap before the angular blocks)
   int hgap0 = 1 << 30, hgap = 0;
 };
+// Floats from one chunk's partial to the next (16-byte aligned).
+inline long wgrad_part_pitch(long len) { return (len + 3) / 4 * 4; }
+bool wgrad_sparse_fits(int Nout, int ldx, int Nin, int gap0);
 template <typename T>
 void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
-                      const WgradLayer* layers, int n_layers, float* partial, float* dparams,
+                      const WgradLayer* layers, int n_layers, const unsigned long long* kmask,
+                      unsigned char* act, float* partial, float* dparams,
                       const long* param_off_dev, hipStream_t st);
 void launch_pack(const PackArgs& p, int slots, hipStream_t st);
 

@@ -689,13 +689,24 @@ struct WgLayerArgs {
   int ldd, ldh, Nout, Nin;
   int hgap0, hgap;  // input i >= hgap0 is column i + hgap of H
   int n_o, n_i;   // 128-wide output and input tiles
-  int block0;     // first block of the layer after the output layer's
+  int tile0;      // its first tile among a chunk's blocks
   long part_off;  // the layer's W inside a chunk's partial vector
 };
 struct WgVecArgs {
   const void* H;
   int ldh, Nin;
   long part_off;
+};
+// Layer 1 over the feature rows' k-steps (wgrad_sparse).
+struct WgSparseArgs {
+  const void* D;
+  const void* X;
+  const unsigned long long* kmask;
+  int ldd, ldx, Nout, Nin;
+  int r0, gap;       // column c >= r0 + gap is input c - gap
+  int on;
+  long part_off;
+  unsigned char* act;  // [chunks][64]: the k-steps some row of the chunk has
 };
 struct WgNetArgs {
   const GroupTable* gt;
@@ -704,9 +715,9 @@ struct WgNetArgs {
   long part_len;  // floats per chunk
   const float* up;
   WgVecArgs vec;
-  int vec_blocks;    // a multiple of 8
-  int tiled_blocks;  // MFMA tiles of all layers
-  int n_tiled;
+  int n_tiled, n_tiles;  // layers of MFMA tiles, and their tiles per chunk
+  int n_sp, has_vec, per;  // blocks per chunk: tiles, layer 1's k-steps, output layer, layer 1's db
+  WgSparseArgs sp;
   WgLayerArgs L[kLayers];
 };
 
@@ -933,7 +944,10 @@ __device__ __forceinline__ void wgrad_tile(const T* __restrict__ D, int ldd, int
   };
   f32x4_t acc[4][4];
   zero_acc(acc);
+  // (a wave past the layer's widths only loads)
+  const bool on = o0 + wo * 64 < Nout && i0 + wi * 64 < Nin;
   auto compute = [&](int buf) __attribute__((always_inline)) {
+    if (!on) return;
     const T* dt = lds + (size_t)buf * 2 * L::TILE;
     const T* ht = dt + L::TILE;
     if constexpr (BF) {
@@ -1036,8 +1050,8 @@ __device__ __forceinline__ void wgrad_tile(const T* __restrict__ D, int ldd, int
 }
 
 // The output layer's partials (one output): dW[i] = sum_r up[r] H[r][i],
-// db = sum_r up[r].  Lane l takes columns 4l..4l+3 of every row (one 8- or
-// 16-byte load), the workgroup's four waves take 16-row blocks in turn, and
+// db = sum_r up[r] (up null: ones, and no db).  Lane l takes columns
+// 4l..4l+3 of every row (one 8- or 16-byte load), the workgroup's four waves take 16-row blocks in turn, and
 // the 16 rows' loads are issued together through buffer resources spanning
 // the chunk (rows past it and columns past Nin load as zeros, so no load is
 // behind a branch).  The waves' sums are added in wave order.
@@ -1052,7 +1066,7 @@ __device__ __forceinline__ void wgrad_vec(const float* __restrict__ up,
       const_cast<TH*>(H + (size_t)r0 * ldh), (short)0, nrow * ldh * (int)sizeof(TH),
       kBufferRsrcWord3);
   const __amdgpu_buffer_rsrc_t us = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(up + r0), (short)0, nrow * 4, kBufferRsrcWord3);
+      const_cast<float*>(up ? up + r0 : nullptr), (short)0, up ? nrow * 4 : 0, kBufferRsrcWord3);
   const int c0 = 4 * lane;
   const bool cok = c0 < Nin;
   float acc[4] = {0.f, 0.f, 0.f, 0.f}, bacc = 0.f;
@@ -1061,7 +1075,7 @@ __device__ __forceinline__ void wgrad_vec(const float* __restrict__ up,
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int r = rb + u;
-      d[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(us, r * 4, 0, 0));
+      d[u] = up ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(us, r * 4, 0, 0)) : 1.f;
       const unsigned off = cok ? (unsigned)((r * ldh + c0) * (int)sizeof(TH)) : kOutOfRange;
       if constexpr (sizeof(TH) == 2) {
         const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(hs, off, 0, 0);
@@ -1087,9 +1101,208 @@ __device__ __forceinline__ void wgrad_vec(const float* __restrict__ up,
   for (int e = 0; e < 4; ++e) red[w * RS + c0 + e] = acc[e];
   if (lane == 0) red[w * RS + kWgVecMaxIn] = bacc;
   __syncthreads();
-  for (int i = threadIdx.x; i <= Nin; i += 256) {
+  for (int i = threadIdx.x; i < Nin + (up ? 1 : 0); i += 256) {
     const int src = i < Nin ? i : kWgVecMaxIn;
     out[i] = ((red[src] + red[RS + src]) + red[2 * RS + src]) + red[3 * RS + src];
+  }
+}
+
+// Layer 1's partials over the feature rows' k-steps (32 columns of X): block j
+// of a chunk takes the chunk's j-th active k-step and every kWgSpBlocks-th
+// after it, dW[o][i] = sum of D[r][o] X[r][i] over the rows r that have it, up
+// to 256 outputs by 32 inputs (four waves of 64 x 32).  An atom's row has 4 to
+// 6 of the 32 k-steps of seven elements, so this is a sixth of the dense
+// product and of its reads, and rows need not hold their other columns.  The
+// rows' list (in row order, so the sums have one order) comes from the masks by
+// ballots; a stage of BK rows is gathered into registers while the two before
+// it are multiplied.  LDS layouts are wgrad_tile's (D's tile has 256 rows; FP32
+// row pitches of 272 and 48 floats put a fragment's four K rows in different
+// banks).  k-steps that no row has are not written: act says which are.
+// (Dense tiles over all rows: 136 us for the weight gradients of 8,192 atoms
+// in FP32, 58 us for 32,768 in BF16; now 46 and 40.)
+constexpr int kWgMaxChunk = 1024;
+constexpr int kWgSpBlocks = 12;  // about as many k-steps as a chunk has
+constexpr int kWgSpD = 272, kWgSpX = 48;  // FP32 row pitches (floats)
+template <typename T> constexpr int kWgSpTile = WgLayout<float>::BK * kWgSpD;  // D's tile
+template <> constexpr int kWgSpTile<bf16_t> = 256 * WgLayout<bf16_t>::P;
+template <typename T>
+__device__ __forceinline__ void wgrad_sparse(const WgSparseArgs& a, int j, int r0, int r1,
+                                             unsigned char* act, float* __restrict__ out, T* lds) {
+  using L = WgLayout<T>;
+  constexpr bool BF = sizeof(T) == 2;
+  constexpr int BK = L::BK;
+  __shared__ unsigned short list[kWgMaxChunk + 4 * BK];
+  __shared__ unsigned long long wor[4];
+  __shared__ int wcnt[4];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nrow = __builtin_amdgcn_readfirstlane(r1 - r0);
+  // wave w has the masks of rows [256 w, 256 w + 256) of the chunk
+  unsigned long long m[4], U = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = 256 * w + 64 * k + lane;
+    m[k] = r < nrow ? a.kmask[r0 + r] : 0ull;
+    U |= m[k];
+  }
+  U = ((unsigned long long)wave_or((unsigned)(U >> 32)) << 32) | wave_or((unsigned)U);
+  if (lane == 0) wor[w] = U;
+  __syncthreads();
+  const int nks = a.ldx / 32;
+  U = (wor[0] | wor[1] | wor[2] | wor[3]) & (nks >= 64 ? ~0ull : (1ull << nks) - 1ull);
+  if (j == 0 && tid < 64) act[tid] = (unsigned char)((U >> tid) & 1ull);
+  const T* D = static_cast<const T*>(a.D);
+  const T* X = static_cast<const T*>(a.X);
+  const __amdgpu_buffer_rsrc_t dsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(D + (size_t)r0 * a.ldd), (short)0, nrow * a.ldd * (int)sizeof(T),
+      kBufferRsrcWord3);
+  const __amdgpu_buffer_rsrc_t xsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(X + (size_t)r0 * a.ldx), (short)0, nrow * a.ldx * (int)sizeof(T),
+      kBufferRsrcWord3);
+  // BF16: this thread's 8 x 8 block of D (rows 8 db.., columns 8 dg..); of X,
+  // 16 bytes of a row (row xr, columns xc..)
+  const int dg = tid & 31, db = tid >> 5;
+  const int xr = tid / (BF ? 4 : 8), xc = (BF ? 8 : 4) * (tid % (BF ? 4 : 8));
+  const bool don = (BF ? 8 * dg : 4 * lane) < a.Nout;
+  auto row_off = [&](int k, int ld) -> unsigned {
+    const int r = list[k];
+    return r < nrow ? (unsigned)(r * ld * (int)sizeof(T)) : kOutOfRange;
+  };
+  auto gload = [&](int q, int st, uint4 (&rd)[8], uint4& rx) __attribute__((always_inline)) {
+    const int k0 = st * BK;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const unsigned off = !don ? kOutOfRange
+                           : BF ? row_off(k0 + 8 * db + e, a.ldd) + 16 * dg
+                                : row_off(k0 + w + 4 * e, a.ldd) + 16 * lane;
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(dsrc, off, 0, 0);
+      rd[e] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(
+        xsrc, row_off(k0 + xr, a.ldx) + xc * (int)sizeof(T), q * 32 * (int)sizeof(T), 0);
+    rx = make_uint4(v[0], v[1], v[2], v[3]);
+  };
+  T* dt = lds;
+  T* xt = lds + kWgSpTile<T>;
+  auto lstore = [&](const uint4 (&rd)[8], const uint4& rx) __attribute__((always_inline)) {
+    const unsigned ux4[4] = {rx.x, rx.y, rx.z, rx.w};
+    if constexpr (BF) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const unsigned sel = (c & 1) ? 0x07060302u : 0x05040100u;
+        unsigned u[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          const uint4 x = rd[2 * h], y = rd[2 * h + 1];
+          const unsigned ux[4] = {x.x, x.y, x.z, x.w}, uy[4] = {y.x, y.y, y.z, y.w};
+          u[h] = __builtin_amdgcn_perm(uy[c >> 1], ux[c >> 1], sel);
+        }
+        *reinterpret_cast<uint4*>(dt + L::off(8 * dg + c, 8 * db)) =
+            make_uint4(u[0], u[1], u[2], u[3]);
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        xt[L::off(xc + c, xr)] = (bf16_t)((c & 1) ? ux4[c >> 1] >> 16 : ux4[c >> 1]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        *reinterpret_cast<uint4*>(dt + (w + 4 * e) * kWgSpD + 4 * lane) = rd[e];
+      *reinterpret_cast<uint4*>(xt + xr * kWgSpX + xc) = rx;
+    }
+  };
+  f32x4_t acc[2][4];
+  const int l16 = lane & 15;
+  // one stage's products, with the loads of the stage after next behind them
+  auto stage = [&](int q, int st, uint4 (&rd)[8], uint4& rx) __attribute__((always_inline)) {
+    lstore(rd, rx);
+    __syncthreads();
+    gload(q, st + 2, rd, rx);
+    if constexpr (BF) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const int j = kk * 4 + (lane >> 4);
+        uint4 fa[2], fb[4];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          fa[x] = *reinterpret_cast<const uint4*>(xt + L::off(x * 16 + l16, 8 * j));
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          fb[y] = *reinterpret_cast<const uint4*>(dt + L::off(w * 64 + y * 16 + l16, 8 * j));
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) Mfma<bf16_t>::mma(fa[x], fb[y], acc[x][y]);
+      }
+    } else {
+#pragma unroll 4
+      for (int ks = 0; ks < BK / 4; ++ks) {
+        const int kr = ks * 4 + (lane >> 4);
+        float fa[2], fb[4];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) fa[x] = xt[kr * kWgSpX + x * 16 + l16];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) fb[y] = dt[kr * kWgSpD + w * 64 + y * 16 + l16];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[x], fb[y], acc[x][y], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  };
+  // this block's k-steps: the j-th active one and every kWgSpBlocks-th after it
+  int skip = j;
+  for (; U; U &= U - 1) {
+    if (skip-- > 0) continue;
+    skip = kWgSpBlocks - 1;
+    const int q = __builtin_amdgcn_readfirstlane(__ffsll((long long)U) - 1);
+    // the rows that have k-step q, in row order
+    unsigned long long bal[4];
+    int mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      bal[k] = __ballot((m[k] >> q) & 1ull);
+      mine += __popcll(bal[k]);
+    }
+    if (lane == 0) wcnt[w] = mine;
+    __syncthreads();
+    const int c0 = wcnt[0], c1 = c0 + wcnt[1], c2 = c1 + wcnt[2];
+    const int cnt = __builtin_amdgcn_readfirstlane(c2 + wcnt[3]);
+    int at = w == 0 ? 0 : (w == 1 ? c0 : (w == 2 ? c1 : c2));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if ((bal[k] >> lane) & 1ull)
+        list[at + popc_below(bal[k])] = (unsigned short)(256 * w + 64 * k + lane);
+      at += __popcll(bal[k]);
+    }
+    // (entries past the list: a row past the chunk, which loads as zero)
+    if (tid < 4 * BK) list[cnt + tid] = (unsigned short)0xffffu;
+    __syncthreads();
+    zero_acc(acc);
+    const int nst = (cnt + BK - 1) / BK;
+    uint4 rd0[8], rd1[8], rx0, rx1;
+    gload(q, 0, rd0, rx0);
+    gload(q, 1, rd1, rx1);
+    for (int st = 0;;) {
+      stage(q, st, rd0, rx0);
+      if (++st >= nst) break;
+      stage(q, st, rd1, rx1);
+      if (++st >= nst) break;
+    }
+    // acc[x][y][e]: column q 32 + x 16 + 4 (lane / 16) + e, o = w 64 + y 16 + lane % 16
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int c = q * 32 + x * 16 + 4 * (lane >> 4);
+      const int i = c < a.r0 ? c : c - a.gap;
+      if ((c >= a.r0 && c < a.r0 + a.gap) || i >= a.Nin) continue;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int o = w * 64 + y * 16 + l16;
+        if (o >= a.Nout) continue;
+        *reinterpret_cast<float4*>(out + (size_t)o * a.Nin + i) =
+            make_float4(acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]);
+      }
+    }
   }
 }
 
@@ -1105,63 +1318,105 @@ __device__ __forceinline__ bool wgrad_chunk(const GroupTable* gt, int S, int chu
   return true;
 }
 
-// Blocks [0, vec_blocks) take the output layer's chunks; then, layer by
-// layer, (chunk, o-tile, i-tile) MFMA tiles, chunk-major.
+// Blocks in order of their length, each kind for all chunks: the MFMA tiles
+// layer by layer, layer 1's k-steps (the sparse form), the output layer, layer
+// 1's db.  Workgroups are dealt to the eight XCDs in turn.  BF16: XCD x takes
+// the chunks c = x mod 8, because what bounds it are reads past the L2, and the
+// blocks of one chunk read the same rows (32,768 atoms: 41 us, 50 us with the
+// chunks of a kind side by side over the XCDs).  FP32 is bound by its products:
+// a chunk goes to whatever XCD is free (8,192 atoms: 44 us, by XCD 50 us).
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_wgrad_net(
     WgNetArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  int b = blockIdx.x;
   int r0 = 0, r1 = 0;
-  if (b < a.vec_blocks) {
-    if (!wgrad_chunk(a.gt, a.S, a.chunk, b, r0, r1)) return;
-    wgrad_vec<T>(a.up, static_cast<const T*>(a.vec.H), a.vec.ldh, a.vec.Nin, r0, r1,
-                 a.partial + (size_t)b * a.part_len + a.vec.part_off,
-                 reinterpret_cast<float*>(smem));
+  const int nc = a.gt->n_wchunks, nc8 = (nc + 7) / 8, slot = blockIdx.x / 8;
+  constexpr bool XCD = sizeof(T) == 2;
+  int b = XCD ? slot / nc8 : blockIdx.x / nc;
+  const int c = XCD ? slot % nc8 * 8 + blockIdx.x % 8 : blockIdx.x % nc;
+  if (b >= a.per) return;
+  if (!wgrad_chunk(a.gt, a.S, a.chunk, c, r0, r1)) return;
+  float* part = a.partial + (size_t)c * a.part_len;
+  if (b < a.n_tiles) {
+    int l = 0;
+    for (int q = 1; q < a.n_tiled; ++q) l = b >= a.L[q].tile0 ? q : l;
+    const WgLayerArgs& Ly = a.L[l];
+    b -= Ly.tile0;
+    const int ot = b / Ly.n_i, it = b % Ly.n_i;
+    float* out = part + Ly.part_off;
+    wgrad_tile<T>(static_cast<const T*>(Ly.D), Ly.ldd, Ly.Nout, static_cast<const T*>(Ly.H),
+                  Ly.ldh, Ly.Nin, Ly.hgap0, Ly.hgap, r0, r1, ot * kWgBO, it * kWgBI, it == 0, out,
+                  out + (size_t)Ly.Nout * Ly.Nin, reinterpret_cast<T*>(smem));
     return;
   }
-  // Tiles in XCD-major order: workgroups are dealt to the eight XCDs in
-  // turn, so physical block b (after the 8-aligned output-layer blocks) is
-  // slot b / 8 on XCD b % 8; XCD x takes the contiguous range of tiles
-  // [x, x + 1) * T / 8, which keeps the tiles of one chunk (reading the same
-  // rows of D and H) on one XCD and its L2.
-  b -= a.vec_blocks;
-  {
-    const int per_xcd = (a.tiled_blocks + 7) / 8;
-    b = (b % 8) * per_xcd + b / 8;
-    if (b >= a.tiled_blocks) return;
+  b -= a.n_tiles;
+  float* out = part + a.sp.part_off;
+  if (b < a.n_sp) {
+    wgrad_sparse<T>(a.sp, b, r0, r1, a.sp.act + c * 64, out, reinterpret_cast<T*>(smem));
+    return;
   }
-  int l = 0;
-  for (int q = 1; q < a.n_tiled; ++q) l = b >= a.L[q].block0 ? q : l;
-  const WgLayerArgs& Ly = a.L[l];
-  b -= Ly.block0;
-  const int per = Ly.n_o * Ly.n_i;
-  const int c = b / per, t = b % per;
-  const int ot = t / Ly.n_i, it = t % Ly.n_i;
-  if (!wgrad_chunk(a.gt, a.S, a.chunk, c, r0, r1)) return;
-  float* out = a.partial + (size_t)c * a.part_len + Ly.part_off;
-  wgrad_tile<T>(static_cast<const T*>(Ly.D), Ly.ldd, Ly.Nout, static_cast<const T*>(Ly.H), Ly.ldh,
-                Ly.Nin, Ly.hgap0, Ly.hgap, r0, r1, ot * kWgBO, it * kWgBI, it == 0, out,
-                out + (size_t)Ly.Nout * Ly.Nin, reinterpret_cast<T*>(smem));
+  if (a.has_vec && b == a.n_sp)
+    wgrad_vec<T>(a.up, static_cast<const T*>(a.vec.H), a.vec.ldh, a.vec.Nin, r0, r1,
+                 part + a.vec.part_off, reinterpret_cast<float*>(smem));
+  else
+    wgrad_vec<T>(nullptr, static_cast<const T*>(a.sp.D), a.sp.ldd, a.sp.Nout, r0, r1,
+                 out + (size_t)a.sp.Nout * a.sp.Nin, reinterpret_cast<float*>(smem));
 }
 
-// out[s] (W then b, Nout*Nin + Nout floats at param_off[s]) = sum of partials.
+// out[s] (the element's whole parameter vector, at param_off[s]) = sum of the
+// chunks' partials, in chunk order, four entries per thread.  Layer 1's k-steps
+// that no row of a chunk has (act) were not written and add nothing.
 __global__ __launch_bounds__(256) void k_wgrad_reduce(const GroupTable* __restrict__ gt, int S,
                                                       const float* __restrict__ partial, long len,
-                                                      float* __restrict__ dparams,
-                                                      const long* __restrict__ param_off) {
+                                                      long pitch, float* __restrict__ dparams,
+                                                      const long* __restrict__ param_off,
+                                                      WgSparseArgs sp) {
   const int s = blockIdx.y;
   if (s >= S) return;
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long e = 4 * ((long)blockIdx.x * blockDim.x + threadIdx.x);
   if (e >= len) return;
-  float v = 0.f;
-  for (int c = gt->wchunk[s]; c < gt->wchunk[s + 1]; ++c) v += partial[(size_t)c * len + e];
-  dparams[param_off[s] + e] = v;
+  const int c0 = gt->wchunk[s], c1 = gt->wchunk[s + 1];
+  // (four entries are of one input group: Nin, r0 and part_off are multiples of 4)
+  const long w = e - sp.part_off;
+  const bool sparse = sp.on && w >= 0 && w < (long)sp.Nout * sp.Nin;
+  const int i = sparse ? (int)((unsigned)w % (unsigned)sp.Nin) : 0;
+  const unsigned char* act = sp.act + ((i < sp.r0 ? i : i + sp.gap) >> 5);
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr int U = 8;
+  for (int c = c0; c < c1; c += U) {
+    float4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c + u < c1 && (!sparse || act[(c + u) * 64]))
+        x[u] = *reinterpret_cast<const float4*>(partial + (size_t)(c + u) * pitch + e);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v.x += x[u].x;
+      v.y += x[u].y;
+      v.z += x[u].z;
+      v.w += x[u].w;
+    }
+  }
+  float* out = dparams + param_off[s] + e;
+  out[0] = v.x;
+  if (e + 1 < len) out[1] = v.y;
+  if (e + 2 < len) out[2] = v.z;
+  if (e + 3 < len) out[3] = v.w;
+}
+
+// Layer 1 by k-steps: up to 256 outputs (a workgroup's four waves), and rows
+// whose 32-column k-steps one 64-bit mask covers.
+bool wgrad_sparse_fits(int Nout, int ldx, int Nin, int gap0) {
+  return Nout % 16 == 0 && Nout <= 256 && ldx % 32 == 0 && ldx <= 64 * 32 && Nin % 4 == 0 &&
+         gap0 % 4 == 0;
 }
 
 template <typename T>
 void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
-                      const WgradLayer* layers, int n_layers, float* partial, float* dparams,
+                      const WgradLayer* layers, int n_layers, const unsigned long long* kmask,
+                      unsigned char* act, float* partial, float* dparams,
                       const long* param_off_dev, hipStream_t st) {
   if (n_chunks_cap <= 0 || n_layers <= 0) return;
   static const bool attr = (ensure_lds(k_wgrad_net<T>), true);
@@ -1176,8 +1431,8 @@ void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
   a.S = S;
   a.chunk = chunk;
   a.partial = partial;
-  a.part_len = part_len;
-  int blocks = 0;
+  const long pitch = wgrad_part_pitch(part_len);
+  a.part_len = pitch;
   // the output layer: the vector kernel when it has one output
   const WgradLayer& lo = layers[n_layers - 1];
   const bool vec = lo.Nout == 1 && lo.Nin <= kWgVecMaxIn && lo.Nin % 4 == 0 && lo.ldh % 4 == 0;
@@ -1187,11 +1442,18 @@ void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
     a.vec.ldh = lo.ldh;
     a.vec.Nin = lo.Nin;
     a.vec.part_off = off[n_layers - 1];
-    a.vec_blocks = (n_chunks_cap + 7) / 8 * 8;
+    a.has_vec = 1;
+  }
+  // layer 1 over the rows' k-steps
+  if (kmask) {
+    const WgradLayer& y = layers[0];
+    const int gap = y.hgap0 < y.Nin ? y.hgap : 0;
+    a.sp = WgSparseArgs{y.D, y.H, kmask, y.ldd, y.ldh, y.Nout, y.Nin, gap ? y.hgap0 : y.Nin, gap,
+                        1, off[0], act};
   }
   for (int l = 0; l < n_layers; ++l) {
     const WgradLayer& y = layers[l];
-    if (l == n_layers - 1 && vec) continue;
+    if ((l == n_layers - 1 && vec) || (l == 0 && a.sp.on)) continue;
     const bool tiled = y.Nout >= 16 && y.Nout % 4 == 0 && y.Nin % 4 == 0 && y.ldd % 8 == 0 &&
                        y.ldh % 8 == 0 && !y.d_fp32;
     if (tiled && a.n_tiled < kLayers) {
@@ -1200,33 +1462,36 @@ void launch_wgrad_net(const GroupTable* gt, int S, int n_chunks_cap, int chunk,
       t.hgap0 = y.hgap0; t.hgap = y.hgap;
       t.n_o = (y.Nout + kWgBO - 1) / kWgBO;
       t.n_i = (y.Nin + kWgBI - 1) / kWgBI;
-      t.block0 = blocks;
+      t.tile0 = a.n_tiles;
       t.part_off = off[l];
-      blocks += n_chunks_cap * t.n_o * t.n_i;
+      a.n_tiles += t.n_o * t.n_i;
     } else if (y.d_fp32) {
       dim3 grid(n_chunks_cap, (y.Nout + 63) / 64, (y.Nin + 63) / 64);
       hipLaunchKernelGGL((k_wgrad<float, T>), grid, dim3(256), 0, st, gt, S,
                          static_cast<const float*>(y.D), y.ldd, y.Nout,
-                         static_cast<const T*>(y.H), y.ldh, y.Nin, chunk, partial, part_len,
+                         static_cast<const T*>(y.H), y.ldh, y.Nin, chunk, partial, pitch,
                          off[l], y.hgap0, y.hgap);
     } else {
       dim3 grid(n_chunks_cap, (y.Nout + 63) / 64, (y.Nin + 63) / 64);
       hipLaunchKernelGGL((k_wgrad<T, T>), grid, dim3(256), 0, st, gt, S,
                          static_cast<const T*>(y.D), y.ldd, y.Nout, static_cast<const T*>(y.H),
-                         y.ldh, y.Nin, chunk, partial, part_len, off[l], y.hgap0, y.hgap);
+                         y.ldh, y.Nin, chunk, partial, pitch, off[l], y.hgap0, y.hgap);
     }
   }
-  a.tiled_blocks = blocks;
-  const int total = a.vec_blocks + (blocks + 7) / 8 * 8;
-  if (total > 0)
-    hipLaunchKernelGGL(k_wgrad_net<T>, dim3(total), dim3(256), wgrad_lds_bytes<T>(), st, a);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((part_len + 255) / 256), S), dim3(256), 0,
-                     st, gt, S, partial, part_len, dparams, param_off_dev);
+  a.n_sp = a.sp.on ? kWgSpBlocks : 0;
+  a.per = a.n_tiles + a.n_sp + a.has_vec + a.sp.on;
+  if (a.per > 0)
+    hipLaunchKernelGGL(k_wgrad_net<T>, dim3((n_chunks_cap + 7) / 8 * 8 * a.per), dim3(256),
+                       wgrad_lds_bytes<T>(), st, a);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((part_len + 1023) / 1024), S), dim3(256), 0,
+                     st, gt, S, partial, part_len, pitch, dparams, param_off_dev, a.sp);
 }
 template void launch_wgrad_net<float>(const GroupTable*, int, int, int, const WgradLayer*, int,
-                                      float*, float*, const long*, hipStream_t);
+                                      const unsigned long long*, unsigned char*, float*, float*,
+                                      const long*, hipStream_t);
 template void launch_wgrad_net<bf16_t>(const GroupTable*, int, int, int, const WgradLayer*, int,
-                                       float*, float*, const long*, hipStream_t);
+                                       const unsigned long long*, unsigned char*, float*, float*,
+                                       const long*, hipStream_t);
 
 // ------------------------------------------------------------ weight packing
 //
