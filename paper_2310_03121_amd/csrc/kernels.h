@@ -46,6 +46,16 @@ struct GemmArgs {
 
 // The fused network (mlp_net.h).  Weights in fragment order, weight slot
 // member * S + element; T is the operand type of the launch.
+// A feature row as the fused network takes it: its k-steps, row and atom.
+struct alignas(16) NetRow {
+  unsigned long long mask;
+  int row, atom;
+};
+constexpr int kNetWindow = 1024;
+// order[p] for p over each species group: its rows, in windows of kNetWindow
+// by their k-step masks.
+void launch_net_order(const GroupTable* gt, const unsigned long long* kmask, const int* perm,
+                      int ldx, int rows_cap, NetRow* order, hipStream_t st);
 struct NetArgs {
   const GroupTable* gt;
   int S;
@@ -68,6 +78,7 @@ struct NetArgs {
   float inv_alpha_l2e;            // log2(e) / alpha
   float escale;                   // factor on the upstream gradient (1 / ensemble size)
   const int* perm;                // sorted row -> atom
+  const NetRow* order;            // the rows in the order the tiles take them, or null
   const int* mol;                 // atom -> molecule
   const double* dLdE;             // per-molecule upstream gradient, or null for ones
   float* erow;                    // [members][erow_stride] atomic energies, input atom order
@@ -96,6 +107,7 @@ struct NetGradArgs {
   const unsigned long long* kmask;
   void* G;
   int ldx;
+  const NetRow* order;  // as the network took them (D1's rows lie in that order)
 };
 
 // Weight slots: member k of an ensemble, element s -> slot k * S + s.

@@ -192,6 +192,9 @@ struct NetLds {
   static constexpr int X1 = RA;                                  // H1, then D1
   static constexpr int MASKS = X1 + BM * S1;
   static constexpr size_t bytes = (size_t)MASKS + BM * 8;
+  // the tile's row numbers sit in the padding of X1's rows (64 BF16 rows fill
+  // half a CU's LDS to the byte)
+  static constexpr int ROWS = X1 + W1 * ES;
   static_assert(RA % 16 == 0 && D3 % 16 == 0 && MASKS % 8 == 0, "aligned regions");
 };
 
@@ -207,7 +210,7 @@ __device__ __forceinline__ float net_celu(float z, float alpha, float ial2e) {
 // D3, D2, D1 and the upstream gradients in global memory for the weight
 // gradients (H1's and D1's rows have W1 columns then).  blockIdx.y is the
 // ensemble member; with a.D1 (and not STORE) its D1 goes to columns
-// [member W1, ...) of a.D1's rows.
+// [member W1, ...) of a.D1's rows, which lie as the tiles take them.
 // HEAD: the order of the energy's sum over the last hidden layer's columns.
 //   false (BF16 with gradients): a lane adds its columns 16 j + 4 g + e of a
 //     half in order of j, then e; then the four g, then the halves.
@@ -226,6 +229,7 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
   unsigned char* D3s = smem + LL::D3;
   unsigned char* X1 = smem + LL::X1;
   unsigned long long* rmask = reinterpret_cast<unsigned long long*>(smem + LL::MASKS);
+  auto rrow = [&](int r) -> int& { return *reinterpret_cast<int*>(smem + LL::ROWS + r * S1); };
 
   const GroupTable* gt = a.gt;
   const int nt = gt->total_rows / BM;
@@ -246,14 +250,26 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
   // qlist (lane l: the l-th active k-step); rows past the group have none
   const int nks = K / 32;
   const unsigned long long all = nks >= 64 ? ~0ull : (1ull << nks) - 1ull;
-  auto row_mask = [&](int r) -> unsigned long long {
-    return row0 + r < row_end ? a.kmask[row0 + r] & all : 0ull;
+  // row r of the tile: by a.order, or the tile's rows as they lie
+  auto net_row = [&](int r) -> NetRow {
+    const int p = row0 + r;
+    if (p >= row_end) return NetRow{0ull, p, -1};
+    NetRow v = a.order ? a.order[p] : NetRow{a.kmask[p], p, a.perm[p]};
+    v.mask &= all;
+    return v;
   };
   static_assert(BM <= 64, "at most one row per lane");
   unsigned long long U;
   {
-    const unsigned long long m = lane < BM ? row_mask(lane) : 0ull;
-    if (tid < BM) rmask[tid] = m;
+    unsigned long long m = 0ull;
+    if (lane < BM) {
+      const NetRow v = net_row(lane);
+      m = v.mask;
+      if (tid < BM) {
+        rmask[tid] = m;
+        rrow(tid) = v.row;
+      }
+    }
     unsigned lo = (unsigned)m, hi = (unsigned)(m >> 32);
 #pragma unroll
     for (int d = 1; d < (BM < 64 ? BM : 64); d <<= 1) {
@@ -274,14 +290,13 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
   for (int i = 0; i < C3::TM; ++i) {
     up[i] = a.escale;
     if (BWD && a.dLdE) {
-      const int row = row0 + (wv / C3::WN) * C3::TM * 16 + i * 16 + rl;
-      up[i] = row < row_end ? (float)a.dLdE[a.mol[a.perm[row]]] * a.escale : 0.f;
+      const int atom = net_row((wv / C3::WN) * C3::TM * 16 + i * 16 + rl).atom;
+      up[i] = atom >= 0 ? (float)a.dLdE[a.mol[atom]] * a.escale : 0.f;
     }
   }
   const bool erow_on = tid < (C3::spread ? BM * 16 : BM);
   const int erow_r = C3::spread ? tid >> 4 : tid;
-  int eatom = -1;
-  if (erow_on && row0 + erow_r < row_end) eatom = a.perm[row0 + erow_r];
+  const int eatom = erow_on ? net_row(erow_r).atom : -1;
 
   // weight-ring depths: BF16 products are short, so all their fragments are
   // in flight over the previous product's epilogue; FP32 products are bound
@@ -300,24 +315,29 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     constexpr int PPM = 16 / MS;        // 16-byte pieces per mask step
     constexpr int RPV = NTH / 16;       // rows per round of loads
     constexpr int NVA = (BM + RPV - 1) / RPV;
+    // (an ordered tile's rows are of one window of its group)
+    const int g0 = gt->pstart[s], win = g0 + (row0 - g0) / kNetWindow * kNetWindow;
+    const int wrows = row_end - win < kNetWindow ? row_end - win : kNetWindow;
     const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(static_cast<const T*>(a.X) + (size_t)row0 * K), (short)0,
-        (row_end - row0) * K * ES, kBufferRsrcWord3);
+        const_cast<T*>(static_cast<const T*>(a.X) + (size_t)win * K), (short)0, wrows * K * ES,
+        kBufferRsrcWord3);
     const int mslot = (tid & 15) / PPM, piece = (tid & 15) % PPM;
     unsigned long long rm[NVA];
+    int xo[NVA];  // the row's offset in elements
 #pragma unroll
     for (int v = 0; v < NVA; ++v) {
       const int r = (tid >> 4) + RPV * v;
-      rm[v] = r < BM ? row_mask(r) : 0ull;
+      const NetRow w = r < BM ? net_row(r) : NetRow{0ull, win, -1};
+      rm[v] = w.mask;
+      xo[v] = (w.row - win) * K;
     }
     auto aload = [&](int c, uint4 (&ra)[NVA]) __attribute__((always_inline)) {
       const int pos = c * MS + mslot;
       const int q = __shfl(qlist, pos & 63, 64);
 #pragma unroll
       for (int v = 0; v < NVA; ++v) {
-        const int r = (tid >> 4) + RPV * v;
         const bool on = pos < nact && ((rm[v] >> q) & 1ull);
-        const unsigned off = on ? (unsigned)((r * K + q * 32) * ES + piece * 16) : kOutOfRange;
+        const unsigned off = on ? (unsigned)((xo[v] + q * 32) * ES + piece * 16) : kOutOfRange;
         const u32x4_t val = __builtin_amdgcn_raw_buffer_load_b128(arsrc, off, 0, 0);
         ra[v] = make_uint4(val[0], val[1], val[2], val[3]);
       }
@@ -379,7 +399,7 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
                                        net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
                                        net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
           LdsV<T>::put(X1 + r * S1 + c * ES, h);
-          if (STORE) Store<T>::put4(static_cast<T*>(a.H1) + (size_t)(row0 + r) * W1 + c, h);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.H1) + (size_t)rrow(r) * W1 + c, h);
         }
         br1.template fetch_share<W1 / KS, C1::TM * C1::TN>(i * C1::TN + j);
       }
@@ -417,7 +437,7 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
                                        net_celu(acc[i][j][2] + b[j].z, alpha, ial2e),
                                        net_celu(acc[i][j][3] + b[j].w, alpha, ial2e));
           LdsV<T>::put(X2 + r * S2 + c * ES, h);
-          if (STORE) Store<T>::put4(static_cast<T*>(a.H2) + (size_t)(row0 + r) * W2 + c, h);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.H2) + (size_t)rrow(r) * W2 + c, h);
         }
         br2.template fetch_share<W2 / KS, C2::TM * C2::TN>(i * C2::TN + j);
       }
@@ -473,13 +493,13 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
             *reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(epart) + r * LL::SH + c * 4) =
                 h4;
           if (STORE) {
-            Store<T>::put4(static_cast<T*>(a.H3) + (size_t)(row0 + r) * W3 + c, h4);
-            Store<T>::put4(static_cast<T*>(a.D3) + (size_t)(row0 + r) * W3 + c, d4);
+            Store<T>::put4(static_cast<T*>(a.H3) + (size_t)rrow(r) * W3 + c, h4);
+            Store<T>::put4(static_cast<T*>(a.D3) + (size_t)rrow(r) * W3 + c, d4);
           }
         }
         if (BWD) br3.template fetch_share<W3 / KS, C3::TM * C3::TN>(i * C3::TN + j);
       }
-      if (STORE && wn == 0 && lane < 16) a.uprow[row0 + r] = row0 + r < row_end ? up[i] : 0.f;
+      if (STORE && wn == 0 && lane < 16) a.uprow[rrow(r)] = row0 + r < row_end ? up[i] : 0.f;
       if constexpr (!C3::spread) {
         float e = HEAD ? (ep[0] + ep[1]) + (ep[2] + ep[3]) : ep[0];
         e += __shfl_xor(e, 16, 64);
@@ -553,7 +573,7 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
               make_float4(acc[i][j][0] * celu_slope(h.x, ia), acc[i][j][1] * celu_slope(h.y, ia),
                           acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
           LdsV<T>::put(X2 + r * S2 + c * ES, d);
-          if (STORE) Store<T>::put4(static_cast<T*>(a.D2) + (size_t)(row0 + r) * W2 + c, d);
+          if (STORE) Store<T>::put4(static_cast<T*>(a.D2) + (size_t)rrow(r) * W2 + c, d);
         }
         br4.template fetch_share<W2 / KS, C2::TM * C2::TN>(i * C2::TN + j);
       }
@@ -593,7 +613,8 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
                           acc[i][j][2] * celu_slope(h.z, ia), acc[i][j][3] * celu_slope(h.w, ia));
           LdsV<T>::put(X1 + r * S1 + c * ES, d);
           if (STORE || a.D1)
-            Store<T>::put4(static_cast<T*>(a.D1) + (size_t)(row0 + r) * a.ld_d1 + member * W1 + c, d);
+            Store<T>::put4(static_cast<T*>(a.D1) + (size_t)(STORE ? rrow(r) : row0 + r) * a.ld_d1 +
+                               member * W1 + c, d);
         }
         if (a.G) br5.template fetch_share<W1 / KS, C1::TM * C1::TN>(i * C1::TN + j);
       }
@@ -616,7 +637,7 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
     for (int i = 0; i < GM; ++i) {
       const int r = i * 16 + rl;
       if (row0 + r < row_end && ((rmask[r] >> q) & 1ull)) {
-        T* g = static_cast<T*>(a.G) + (size_t)(row0 + r) * K + q * 32 + cq;
+        T* g = static_cast<T*>(a.G) + (size_t)rrow(r) * K + q * 32 + cq;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           Store<T>::put4(g + j * 16,

@@ -24,6 +24,78 @@ bool launch_mlp_net(const int* width, const NetArgs& a, int n_rows, int rows_cap
 template bool launch_mlp_net<bf16_t>(const int*, const NetArgs&, int, int, int, hipStream_t);
 template bool launch_mlp_net<float>(const int*, const NetArgs&, int, int, int, hipStream_t);
 
+// ------------------------------------------------------------ the rows' order
+//
+// Layer 1 and dE/dG run over the union of a tile's k-steps.  Neighboring rows
+// of a group belong to unlike atoms: 32 rows of one element in 512 conformers
+// of 64 atoms have 13 k-steps together, a row alone 4.4.  Sorted by their masks
+// as numbers (the k-steps of the rarest elements come last and lead the order)
+// within windows of 1,024 rows they have 5.3; 64 rows of random molecules 10
+// for 22.  A row's rank in its window is the number of smaller masks (equal
+// ones: of earlier rows), so the order follows from the rows alone.  One
+// workgroup ranks 64 rows, each wave against an eighth of the window from LDS
+// (6 us for 8,192 rows, 7 for 32,768, 12 for 77,163: latencies, then the
+// comparisons; four waves 8 / 8 / 11, sixteen 5 / 8 / 18, 128 rows at a time 10 /
+// 10 / 14).
+constexpr int kOrderWaves = 8;
+template <typename K>
+__global__ __launch_bounds__(64 * kOrderWaves) void k_net_order(
+    const GroupTable* __restrict__ gt, const unsigned long long* __restrict__ kmask,
+    const int* __restrict__ perm, NetRow* __restrict__ order) {
+  constexpr int W = kNetWindow, SL = W / kOrderWaves;  // keys per wave
+  static_assert(SL % 64 == 0, "64 keys are the rows' own or none of them");
+  __shared__ __attribute__((aligned(16))) K key[W];
+  __shared__ int part[kOrderWaves][64];
+  const int row0 = blockIdx.x * 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (row0 >= gt->total_rows) return;
+  const int s = tile_species(gt, row0);
+  const int g0 = gt->pstart[s], g1 = g0 + gt->cnt[s];
+  if (row0 >= g1) return;
+  const int w0 = g0 + (row0 - g0) / W * W;
+  const int cnt = g1 - w0 < W ? g1 - w0 : W;
+  const int row = row0 + lane;
+  const unsigned long long m = row < g1 ? kmask[row] : 0ull;
+  const int atom = wv == 0 && row < g1 ? perm[row] : -1;
+#pragma unroll
+  for (int i = tid; i < W; i += 64 * kOrderWaves) key[i] = i < cnt ? (K)kmask[w0 + i] : (K)~(K)0;
+  __syncthreads();
+  const K mine = (K)m;
+  const int own = row0 - w0;
+  int n = 0;
+  for (int k0 = wv * SL; k0 < (wv + 1) * SL && k0 < cnt; k0 += 64) {
+    const K* k = key + k0;
+    if (k0 < own) {
+#pragma unroll 32
+      for (int j = 0; j < 64; ++j) n += k[j] <= mine;
+    } else if (k0 > own) {
+#pragma unroll 32
+      for (int j = 0; j < 64; ++j) n += k[j] < mine;
+    } else {
+#pragma unroll 32
+      for (int j = 0; j < 64; ++j) n += k[j] < mine || (k[j] == mine && j < lane);
+    }
+  }
+  part[wv][lane] = n;
+  __syncthreads();
+  if (wv == 0 && row < g1) {
+    int at = 0;
+#pragma unroll
+    for (int w = 0; w < kOrderWaves; ++w) at += part[w][lane];
+    order[w0 + at] = NetRow{m, row, atom};
+  }
+}
+
+void launch_net_order(const GroupTable* gt, const unsigned long long* kmask, const int* perm,
+                      int ldx, int rows_cap, NetRow* order, hipStream_t st) {
+  const dim3 grid(rows_cap / 64), block(64 * kOrderWaves);
+  if (ldx <= 32 * 32)
+    hipLaunchKernelGGL(k_net_order<unsigned>, grid, block, 0, st, gt, kmask, perm, order);
+  else
+    hipLaunchKernelGGL(k_net_order<unsigned long long>, grid, block, 0, st, gt, kmask, perm,
+                       order);
+}
+
 // ------------------------------------------------------- dE/dG of an ensemble
 //
 // One workgroup per 64-row tile and group of 4 UN active k-steps of the
@@ -68,6 +140,7 @@ __global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
   constexpr int BM = 64, NTH = 256, ES = sizeof(T), TM = BM / 16;
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BM * kNetChunkStride];
   __shared__ unsigned long long rmask[BM];
+  __shared__ int rrow[BM];
   const GroupTable* gt = a.gt;
   const int nt = gt->total_rows / BM;
   if ((int)blockIdx.x >= nt) return;
@@ -81,8 +154,16 @@ __global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
   const int K = a.K, ldx = a.ldx;
   const int nks = ldx / 32;
   const unsigned long long all = nks >= 64 ? ~0ull : (1ull << nks) - 1ull;
-  const unsigned long long m = row0 + lane < row_end ? a.kmask[row0 + lane] & all : 0ull;
-  if (tid < BM) rmask[tid] = m;
+  unsigned long long m = 0ull;
+  int row = row0 + lane;
+  if (row < row_end) {
+    m = (a.order ? a.order[row].mask : a.kmask[row]) & all;
+    if (a.order) row = a.order[row].row;
+  }
+  if (tid < BM) {
+    rmask[tid] = m;
+    rrow[tid] = row;
+  }
   unsigned lo = (unsigned)m, hi = (unsigned)(m >> 32);
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -154,7 +235,7 @@ __global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
     for (int i = 0; i < TM; ++i) {
       const int r = i * 16 + rl;
       if (row0 + r < row_end && ((rmask[r] >> q[u]) & 1ull)) {
-        T* g = static_cast<T*>(a.G) + (size_t)(row0 + r) * ldx + q[u] * 32 + cq;
+        T* g = static_cast<T*>(a.G) + (size_t)rrow[r] * ldx + q[u] * 32 + cq;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const f32x4_t v = acc[i][2 * u + j];
