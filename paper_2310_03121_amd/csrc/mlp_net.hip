@@ -101,7 +101,10 @@ void launch_net_order(const GroupTable* gt, const unsigned long long* kmask, con
 // One workgroup per 64-row tile and group of 4 UN active k-steps of the
 // tile's rows (32 columns of G each, UN per wave): the members' delta1 stream
 // through two LDS chunk buffers, the weights through the register ring.  The
-// members are summed inside the FP32 accumulator, in member order.
+// members are summed inside the FP32 accumulator, in member order.  Held to two
+// waves per SIMD: left alone the compiler takes 278 registers for BF16 with two
+// k-steps per wave and one wave per SIMD (eight members, 32,768 rows: 64 us,
+// now 54; with unsorted rows 91 and 72).
 template <typename T, int UN, int P>
 struct GradRing {
   static constexpr int FB = 64 * 16;
@@ -136,7 +139,7 @@ struct GradRing {
 };
 
 template <typename T, int UN>
-__global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_net_grad(NetGradArgs a) {
   constexpr int BM = 64, NTH = 256, ES = sizeof(T), TM = BM / 16;
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BM * kNetChunkStride];
   __shared__ unsigned long long rmask[BM];
