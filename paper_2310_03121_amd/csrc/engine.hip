@@ -324,15 +324,15 @@ bool launches_ok() {
 }
 
 // Whether the fused network's tiles take the rows sorted by k-steps (a launch
-// of 5 to 11 us): where fewer k-steps per tile save more than that, which asks
+// of 5 to 12 us): where fewer k-steps per tile save more than that, which asks
 // for many k-steps and for more tiles than run at once.  Networks in us,
 // unsorted / sorted, without that launch: FP32 forces of seven elements 3,072
-// atoms 43 / 40, 4,096: 74 / 52, 32,768: 242 / 194, energies 8,192: 44 / 34; of
-// four elements 8,192: 37 / 35, 32,768: 128 / 107.  BF16 forces of seven
-// elements 32,768 atoms: 40 / 39, 51,200: 83 / 60, 77,163 of all sizes: 112 / 96,
-// eight members of 4,096: 68 / 61, of 32,768: 287 / 250; energies 64,000: 43 /
-// 35; four elements 77,163: 61 / 58.  A box of a liquid has few elements and
-// every row the same k-steps (23,001 atoms of water: 29 / 28).
+// atoms 43 / 40, 4,096: 74 / 52, 8,192: 60 / 48, 32,768: 243 / 163; of four
+// elements 8,192: 37 / 35, 32,768: 128 / 97.  BF16 forces of seven elements
+// 25,600 atoms 41 / 33, 32,768: 40 / 33, 51,200: 83 / 57, 77,163 of all sizes:
+// 109 / 81, eight members of 4,096: 68 / 61, of 32,768: 287 / 241; energies
+// 64,000: 43 / 34; four elements 77,163: 60 / 54.  A box of a liquid has few
+// elements and every row the same k-steps (23,001 atoms of water: 29 / 28).
 bool net_ordered(const nnp_handle* h, const Plan& P, bool grad) {
   if (P.B.periodic) return false;
   const bool many = h->Fp > 512;
@@ -476,8 +476,11 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
       if (net_ordered(h, P, need_bwd)) {
         // (a region that this call's network leaves alone)
         NetRow* order = at<NetRow>(ws, io.dparams ? P.wpart : P.H2);
-        launch_net_order(gt, kmask, perm, Fp, P.rows_cap, order, st);
+        int* tiles = reinterpret_cast<int*>(order + P.rows_cap);
+        launch_net_order(gt, kmask, perm, Fp, P.rows_cap, net_tile<T>(P.n, M, true), order, tiles,
+                         st);
         na.order = order;
+        na.tiles = tiles;
       }
       // (the feature rows may be stored sparse: no other kernel may take over)
       ok &= launch_mlp_net<T>(h->width, na, P.n, P.rows_cap, M, st);

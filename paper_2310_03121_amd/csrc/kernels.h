@@ -53,9 +53,14 @@ struct alignas(16) NetRow {
 };
 constexpr int kNetWindow = 1024;
 // order[p] for p over each species group: its rows, in windows of kNetWindow
-// by their k-step masks.
+// by their k-step masks; tiles: the tiles of tile_rows rows in the order the
+// workgroups take them.
 void launch_net_order(const GroupTable* gt, const unsigned long long* kmask, const int* perm,
-                      int ldx, int rows_cap, NetRow* order, hipStream_t st);
+                      int ldx, int rows_cap, int tile_rows, NetRow* order, int* tiles,
+                      hipStream_t st);
+// Rows per tile of the fused network.
+template <typename T>
+int net_tile(int n_rows, int members, bool ordered);
 struct NetArgs {
   const GroupTable* gt;
   int S;
@@ -79,6 +84,7 @@ struct NetArgs {
   float escale;                   // factor on the upstream gradient (1 / ensemble size)
   const int* perm;                // sorted row -> atom
   const NetRow* order;            // the rows in the order the tiles take them, or null
+  const int* tiles;               // with order: the tiles as the workgroups take them
   const int* mol;                 // atom -> molecule
   const double* dLdE;             // per-molecule upstream gradient, or null for ones
   float* erow;                    // [members][erow_stride] atomic energies, input atom order

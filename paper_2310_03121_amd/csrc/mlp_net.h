@@ -234,7 +234,9 @@ __global__ __launch_bounds__(64 * kNetWaves) __attribute__((amdgpu_waves_per_eu(
   const GroupTable* gt = a.gt;
   const int nt = gt->total_rows / BM;
   if ((int)blockIdx.x >= nt) return;
-  const int row0 = xcd_tile(blockIdx.x, nt) * BM;
+  int tile = xcd_tile(blockIdx.x, nt);
+  if (a.order) tile = a.tiles[tile];
+  const int row0 = tile * BM;
   const int s = tile_species(gt, row0);
   const int row_end = gt->pstart[s] + gt->cnt[s];
   if (row0 >= row_end) return;
@@ -666,27 +668,9 @@ static void launch_net_m(const NetArgs& a, int rows_cap, int members, hipStream_
     launch_net_t<T, W1, W2, W3, BM, true, true>(a, rows_cap, members, st);
 }
 
-// Rows per tile.  A tile's chain of products takes about the same time
-// whatever its rows (28 us with 64 rows, 15 us with 16 for BF16 in the idle
-// GPU), so small systems spread over small tiles and large ones, whose tiles
-// fill the 512 places on the GPU anyway, share the weight stream among more
-// rows.  Measured, whole evaluation of 64-atom molecules of seven elements
-// (rows: us with 16 / 32 / 64): BF16 2,048: 61.5 / 63.9 / 70.7; 8,192: 75.6 /
-// 71.2 / 78.5; 12,288: 94.8 / 82.5 / 81.8; 32,768: 152 / 126 / 114.  FP32
-// 2,048: 79.8 / 100.1 / 145.6; 6,144: 117.3 / 112.0 / 165.6; 32,768: 325 /
-// 308 / 307 (64 rows of FP32 activations leave one workgroup per CU, and at
-// 24,576 take 328 against 270: no use).  Ensembles: the members' tiles count
-// for BF16; FP32 eight members 2,048: 229 / 244, 4,096: 384 / 399.
-template <typename T>
-inline int net_tile(int n_rows, int members) {
-  if (sizeof(T) == 4) return n_rows <= 4096 ? 16 : 32;
-  const long rows = (long)n_rows * members;
-  return rows <= 3072 ? 16 : (rows <= 10240 ? 32 : 64);
-}
-
 template <typename T, int W1, int W2, int W3>
 static void launch_net_w(const NetArgs& a, int n_rows, int rows_cap, int members, hipStream_t st) {
-  switch (net_tile<T>(n_rows, members)) {
+  switch (net_tile<T>(n_rows, members, a.order != nullptr)) {
     case 16: launch_net_m<T, W1, W2, W3, 16>(a, rows_cap, members, st); return;
     case 32: launch_net_m<T, W1, W2, W3, 32>(a, rows_cap, members, st); return;
     default:

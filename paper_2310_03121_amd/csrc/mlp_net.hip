@@ -24,6 +24,29 @@ bool launch_mlp_net(const int* width, const NetArgs& a, int n_rows, int rows_cap
 template bool launch_mlp_net<bf16_t>(const int*, const NetArgs&, int, int, int, hipStream_t);
 template bool launch_mlp_net<float>(const int*, const NetArgs&, int, int, int, hipStream_t);
 
+// Rows per tile.  A tile's chain of products takes about the same time
+// whatever its rows (28 us with 64 rows, 15 us with 16 for BF16 in the idle
+// GPU), so small systems spread over small tiles and large ones, whose tiles
+// fill the 512 places on the GPU anyway, share the weight stream among more
+// rows.  Measured, whole evaluation of 64-atom molecules of seven elements
+// (rows: us with 16 / 32 / 64): BF16 2,048: 61.5 / 63.9 / 70.7; 8,192: 75.6 /
+// 71.2 / 78.5; 12,288: 94.8 / 82.5 / 81.8; 32,768: 152 / 126 / 114.  FP32
+// 2,048: 79.8 / 100.1 / 145.6; 6,144: 117.3 / 112.0 / 165.6; 32,768: 325 /
+// 308 / 307 (64 rows of FP32 activations leave one workgroup per CU, and at
+// 24,576 take 328 against 270: no use).  Ensembles: the members' tiles count
+// for BF16; FP32 eight members 2,048: 229 / 244, 4,096: 384 / 399.  Rows sorted
+// by k-steps make small FP32 tiles cheaper (network of seven elements, 16 / 32:
+// 8,192: 48 / 52, 12,160: 85 / 97, 16,000: 105 / 105, 32,768: 178 / 163; BF16
+// 32 / 64: 19,200: 29 / 29, 32,768: 40 / 33, as without).
+template <typename T>
+int net_tile(int n_rows, int members, bool ordered) {
+  const long rows = (long)n_rows * members;
+  if (sizeof(T) == 4) return n_rows <= 4096 || (ordered && rows <= 14336) ? 16 : 32;
+  return rows <= 3072 ? 16 : (rows <= 10240 ? 32 : 64);
+}
+template int net_tile<float>(int, int, bool);
+template int net_tile<bf16_t>(int, int, bool);
+
 // ------------------------------------------------------------ the rows' order
 //
 // Layer 1 and dE/dG run over the union of a tile's k-steps.  Neighboring rows
@@ -37,15 +60,59 @@ template bool launch_mlp_net<float>(const int*, const NetArgs&, int, int, int, h
 // (6 us for 8,192 rows, 7 for 32,768, 12 for 77,163: latencies, then the
 // comparisons; four waves 8 / 8 / 11, sixteen 5 / 8 / 18, 128 rows at a time 10 /
 // 10 / 14).
+//
+// The last rows of a window have the k-steps of rare elements and the most
+// unlike masks: their tiles take up to twice the time of the others.  Eight
+// more workgroups list the tiles of each XCD's range with the ends of all
+// windows first, so that no long tile starts last (512 x 64 conformers in FP32,
+// two rounds of tiles: 194 us with the tiles in order, now 163; 77,163 rows in
+// BF16 96, now 80).
 constexpr int kOrderWaves = 8;
+__device__ __forceinline__ void order_tiles(const GroupTable* __restrict__ gt, int xcd,
+                                            int tile_rows, int* __restrict__ tiles, int* bin) {
+  // bin[p]: tiles p places before the end of their window
+  const int per = kNetWindow / tile_rows, tid = threadIdx.x;
+  const int nt = gt->total_rows / tile_rows;
+  const int lo = xcd < nt ? xcd_tile(xcd, nt) : 0, m = xcd < nt ? (nt - xcd + 7) / 8 : 0;
+  auto place = [&](int t) {
+    const int row0 = t * tile_rows, s = tile_species(gt, row0), g0 = gt->pstart[s];
+    const int len = (gt->cnt[s] + tile_rows - 1) / tile_rows, i = row0 / tile_rows - g0 / tile_rows;
+    const int end = (i / per + 1) * per;
+    const int p = (end < len ? end : len) - 1 - i;
+    return p < 0 ? per - 1 : p;  // (tiles of padding only)
+  };
+  for (int p = tid; p < per; p += 64 * kOrderWaves) bin[p] = 0;
+  __syncthreads();
+  for (int j = tid; j < m; j += 64 * kOrderWaves) atomicAdd(&bin[place(lo + j)], 1);
+  __syncthreads();
+  if (tid < 64) {  // per <= 64: exclusive sums in place
+    const int v = tid < per ? bin[tid] : 0;
+    int x = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int u = __shfl_up(x, d, 64);
+      if (tid >= d) x += u;
+    }
+    if (tid < per) bin[tid] = x - v;
+  }
+  __syncthreads();
+  for (int j = tid; j < m; j += 64 * kOrderWaves)
+    tiles[lo + atomicAdd(&bin[place(lo + j)], 1)] = lo + j;
+}
+
 template <typename K>
 __global__ __launch_bounds__(64 * kOrderWaves) void k_net_order(
     const GroupTable* __restrict__ gt, const unsigned long long* __restrict__ kmask,
-    const int* __restrict__ perm, NetRow* __restrict__ order) {
+    const int* __restrict__ perm, int nrank, int tile_rows, NetRow* __restrict__ order,
+    int* __restrict__ tiles) {
   constexpr int W = kNetWindow, SL = W / kOrderWaves;  // keys per wave
   static_assert(SL % 64 == 0, "64 keys are the rows' own or none of them");
   __shared__ __attribute__((aligned(16))) K key[W];
   __shared__ int part[kOrderWaves][64];
+  if ((int)blockIdx.x >= nrank) {
+    order_tiles(gt, blockIdx.x - nrank, tile_rows, tiles, &part[0][0]);
+    return;
+  }
   const int row0 = blockIdx.x * 64;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (row0 >= gt->total_rows) return;
@@ -87,13 +154,16 @@ __global__ __launch_bounds__(64 * kOrderWaves) void k_net_order(
 }
 
 void launch_net_order(const GroupTable* gt, const unsigned long long* kmask, const int* perm,
-                      int ldx, int rows_cap, NetRow* order, hipStream_t st) {
-  const dim3 grid(rows_cap / 64), block(64 * kOrderWaves);
+                      int ldx, int rows_cap, int tile_rows, NetRow* order, int* tiles,
+                      hipStream_t st) {
+  const int nrank = rows_cap / 64;
+  const dim3 grid(nrank + 8), block(64 * kOrderWaves);
   if (ldx <= 32 * 32)
-    hipLaunchKernelGGL(k_net_order<unsigned>, grid, block, 0, st, gt, kmask, perm, order);
+    hipLaunchKernelGGL(k_net_order<unsigned>, grid, block, 0, st, gt, kmask, perm, nrank,
+                       tile_rows, order, tiles);
   else
-    hipLaunchKernelGGL(k_net_order<unsigned long long>, grid, block, 0, st, gt, kmask, perm,
-                       order);
+    hipLaunchKernelGGL(k_net_order<unsigned long long>, grid, block, 0, st, gt, kmask, perm, nrank,
+                       tile_rows, order, tiles);
 }
 
 // ------------------------------------------------------- dE/dG of an ensemble
