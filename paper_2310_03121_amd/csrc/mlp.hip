@@ -1518,13 +1518,42 @@ __device__ __forceinline__ float packed_weight(const float* __restrict__ W, int 
   return (c < r0 || c >= a0) && i < in ? W[(size_t)o * in + i] : 0.f;
 }
 
-// blockIdx.y: layer and operand (2 l: W_l, 2 l + 1: W_l^T; then the output
-// layer, and of an ensemble the member-concatenated W_0^T); z: weight slot.
+// EL columns c, c + 1, .. of row o, in 16-byte loads: widths are multiples of
+// 32 and layer 1's radial and angular blocks of 16, so a lane's 4 or 8 columns
+// are all of the gap or none.  (The parameters of an element start at any
+// multiple of 4 bytes.)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int EL>
+__device__ __forceinline__ void packed_row(const float* __restrict__ W, int o, int c, int in, int r0,
+                                           int a0, float (&v)[EL]) {
+  const int i = c >= r0 ? c - (a0 - r0) : c;
+  const bool on = (c < r0 || c >= a0) && i < in;
+#pragma unroll
+  for (int e = 0; e < EL; e += 4) {
+    const f32x4_any x =
+        on ? *reinterpret_cast<const f32x4_any*>(W + (size_t)o * in + i + e) : f32x4_any(0.f);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[e + k] = x[k];
+  }
+}
+
+// The operands that one launch packs, in blocks of 256 threads: what = 2 l:
+// W_l, 2 l + 1: W_l^T; then the output layer, and of an ensemble the
+// member-concatenated W_0^T.
+constexpr int kPackWhat = 2 * (kLayers - 1) + 2;
+struct PackBlocks {
+  int first[kPackWhat + 1];
+};
+
+// blockIdx.y: weight slot.
 template <typename T>
-__global__ __launch_bounds__(256) void k_pack_frag(PackArgs p) {
+__global__ __launch_bounds__(256) void k_pack_frag(PackArgs p, PackBlocks pb) {
   constexpr int KS = Frag<T>::KS, EL = Frag<T>::EL;
-  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  const int s = blockIdx.z, what = blockIdx.y;
+  const int s = blockIdx.y;
+  int what = 0;
+#pragma unroll
+  for (int q = 1; q < kPackWhat; ++q) what = (int)blockIdx.x >= pb.first[q] ? q : what;
+  const int t = ((int)blockIdx.x - pb.first[what]) * 256 + (int)threadIdx.x;
   const bool cat = what == 2 * (kLayers - 1) + 1;
   const int l = cat ? 0 : what >> 1;
   const float* src = p.flat + p.off[s * kLayers + l];
@@ -1542,9 +1571,12 @@ __global__ __launch_bounds__(256) void k_pack_frag(PackArgs p) {
   const int lane = t & 63, f = t >> 6, ks = f % (K / KS), nt = f / (K / KS);
   const int n = nt * 16 + (lane & 15), k = ks * KS + (lane >> 4) * EL;
   float v[EL];
+  if (tr) {
 #pragma unroll
-  for (int e = 0; e < EL; ++e)
-    v[e] = tr ? packed_weight(src, k + e, n, in, r0, a0) : packed_weight(src, n, k + e, in, r0, a0);
+    for (int e = 0; e < EL; ++e) v[e] = packed_weight(src, k + e, n, in, r0, a0);
+  } else {
+    packed_row<EL>(src, n, k, in, r0, a0, v);
+  }
   uint4 u;
   T* dst;
   if constexpr (sizeof(T) == 2) {
@@ -1602,13 +1634,27 @@ void launch_pack(const PackArgs& p, int slots, hipStream_t st) {
     hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((maxel + 255) / 256), kLayers, slots),
                        dim3(256), 0, st, p);
   const bool cat = p.WT0cq || p.WT0cqf;
-  const unsigned ny = 2 * (kLayers - 1) + 1 + (cat ? 1 : 0);
-  if (p.Wqb[0])
-    hipLaunchKernelGGL(k_pack_frag<bf16_t>, dim3((unsigned)((maxel / 8 + 255) / 256), ny, slots),
-                       dim3(256), 0, st, p);
-  if (p.Wqf[0])
-    hipLaunchKernelGGL(k_pack_frag<float>, dim3((unsigned)((maxel / 4 + 255) / 256), ny, slots),
-                       dim3(256), 0, st, p);
+  auto blocks = [&](int EL) {
+    PackBlocks pb{};
+    for (int q = 0; q < kPackWhat; ++q) {
+      const int l = q == kPackWhat - 1 ? 0 : q >> 1;
+      const int inp = l == 0 ? p.Fp : p.width[l];
+      int threads = l == kLayers - 1 ? p.width[l] : std::max(inp * p.width[l + 1] / EL, p.width[l + 1]);
+      if (q == kPackWhat - 1 && !cat) threads = 0;
+      pb.first[q + 1] = pb.first[q] + (threads + 255) / 256;
+    }
+    return pb;
+  };
+  if (p.Wqb[0]) {
+    const PackBlocks pb = blocks(8);
+    hipLaunchKernelGGL(k_pack_frag<bf16_t>, dim3(pb.first[kPackWhat], slots), dim3(256), 0, st, p,
+                       pb);
+  }
+  if (p.Wqf[0]) {
+    const PackBlocks pb = blocks(4);
+    hipLaunchKernelGGL(k_pack_frag<float>, dim3(pb.first[kPackWhat], slots), dim3(256), 0, st, p,
+                       pb);
+  }
 }
 
 }  // namespace nnp
