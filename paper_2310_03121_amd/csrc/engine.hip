@@ -387,22 +387,22 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     if (P.nblk > kFusedSortBlocks) {
       launch_groups(dims, P.n, S, hist, gt, perm, P.rows_cap, io.off, P.wchunk, status, st);
       launch_scatter(dims, P.n, S, xyzs, hist, row, perm, st);
-    } else if (P.B.periodic) {
-      launch_sort_scatter(dims, P.n, S, xyzs, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
-                          status, st);
     }
   }
   {
     StageTimer t(h, io.timed, ST_PAIRS, st);
     if (!P.B.periodic && P.nblk <= kFusedSortBlocks) {
-      // molecules: the sort and the pair scan share one launch
+      // molecules: the sort and the pair scan share one launch (boxes: the
+      // sort and the binning)
       launch_sort_pairs_mol(dims, P.n, S, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
                             h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
     } else if (P.B.periodic) {
       launch_pairs_cell(dims, P.n, h->C, P.B, xyzs, at<int>(ws, P.cell_of),
                         at<int>(ws, P.cell_cnt), at<int>(ws, P.cell_start),
                         at<int>(ws, P.cursor), at<int>(ws, P.cell_atoms),
-                        at<float4>(ws, P.cell_xyzs), P.cap, nbr, rec, counts, status, st);
+                        at<float4>(ws, P.cell_xyzs), P.cap, nbr, rec, counts, status, S, hist,
+                        P.nblk <= kFusedSortBlocks ? gt : nullptr, row, perm, P.rows_cap, io.off,
+                        P.wchunk, st);
     } else {
       launch_pairs_mol(dims, P.n, h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
     }
@@ -1126,7 +1126,8 @@ nnp_status nnp_debug_aev(nnp_handle* h, int32_t n, int32_t nmol, const float* po
     launch_pairs_cell(dims, P.n, h->C, P.B, xyzs, at<int>(ws, P.cell_of), at<int>(ws, P.cell_cnt),
                       at<int>(ws, P.cell_start), at<int>(ws, P.cursor), at<int>(ws, P.cell_atoms),
                       at<float4>(ws, P.cell_xyzs), P.cap, at<int>(ws, P.nbr),
-                      at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, st);
+                      at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, h->S, nullptr,
+                      nullptr, nullptr, nullptr, P.rows_cap, off, P.wchunk, st);
   else
     launch_pairs_mol(dims, P.n, h->C, xyzs, mrange, P.cap, at<int>(ws, P.nbr),
                      at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, st);

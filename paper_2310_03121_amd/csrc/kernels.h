@@ -188,16 +188,19 @@ void launch_sort_pairs_mol(const int* dims, int n_cap, int S, const int* hist, G
                            int* nbr, float4* rec, int2* counts, uint32_t* status,
                            hipStream_t st);
 // Periodic boxes: cell_cnt holds cell_zero_ints(ncell) ints that staging
-// zeroed: the per-cell counts, then (up to kCellScanLds cells) the fill
-// counters, or (more cells) the counting launch's done counter.
+// zeroed: the per-cell counts, then (more than kCellScanLds cells) the counting
+// launch's done counter.  With gt, the species sort as well
+// (n_cap <= 256 * kFusedSortBlocks).
 constexpr int kCellScanLds = 8192;
 inline size_t cell_zero_ints(int ncell) {
-  return ncell <= kCellScanLds ? 2 * (size_t)ncell : (size_t)ncell + 1;
+  return (size_t)ncell + (ncell > kCellScanLds ? 1 : 0);
 }
 void launch_pairs_cell(const int* dims, int n_cap, const AevConst& C, const BoxConst& B,
                        const float4* xyzs, int* cell_of, int* cell_cnt, int* cell_start,
                        int* cursor, int* cell_atoms, float4* cell_xyzs, int cap, int* nbr,
-                       float4* rec, int2* counts, uint32_t* status, hipStream_t st);
+                       float4* rec, int2* counts, uint32_t* status, int S, const int* hist,
+                       GroupTable* gt, int* row, int* perm, int rows_cap, const int* off,
+                       int wchunk_rows, hipStream_t st);
 // Deterministic forces from the adjoint's per-entry rows pgrad ([n][cap],
 // dE_i/d(displacement of entry e)): atom a's row out[gidx ? gidx[a] : a] +=
 // sign * sum over a's entries e, in list order, of pgrad[a][e] -
