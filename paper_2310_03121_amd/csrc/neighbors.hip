@@ -36,7 +36,10 @@ __device__ __forceinline__ int make_key(int j, int s, bool ang) {
 // row: indices to nbr, the matching displacement records to rec.  Lists of at
 // most 64 keep one key per lane and count smaller keys with lane reads (no
 // LDS round trip per comparison), in groups of 16 up to nr; longer lists
-// compare against the LDS copy.
+// compare against the LDS copy.  Ascending: the keys come in the order of
+// their atoms, so that a key's rank follows from its place among those of its
+// kind (angular or not, species): one ballot per bit of the kind.
+template <bool Ascending>
 __device__ __forceinline__ void finish_list(const int* key, const float4* lrec, int nr, int na,
                                             int i, int cap, int* __restrict__ nbr,
                                             float4* __restrict__ rec, int2* __restrict__ counts) {
@@ -44,9 +47,30 @@ __device__ __forceinline__ void finish_list(const int* key, const float4* lrec, 
   if (nr <= kWave) {
     const int k = lane < nr ? key[lane] : 0x7fffffff;
     int rank = 0;
-    for (int g = 0; g < nr; g += 16) {
+    if constexpr (Ascending) {
+      // bit by bit: eq, the lanes of this lane's kind; lt, those of smaller ones
+      const int kind = k >> kKeyJBits;
+      static_assert(kMaxS <= 8, "kinds of 4 bits");
+      const uint64_t valid = ballot(lane < nr);
+      unsigned eq[2] = {(unsigned)valid, (unsigned)(valid >> 32)}, lt[2] = {0u, 0u};
 #pragma unroll
-      for (int q = 0; q < 16; ++q) rank += __builtin_amdgcn_readlane(k, g + q) < k ? 1 : 0;
+      for (int bit = 3; bit >= 0; --bit) {
+        const uint64_t B = ballot((kind >> bit) & 1);
+        const unsigned mine = (unsigned)__builtin_amdgcn_sbfe(kind, bit, 1);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const unsigned Bh = (unsigned)(B >> (32 * h));
+          lt[h] |= eq[h] & ~Bh & mine;
+          eq[h] &= ~(Bh ^ mine);
+        }
+      }
+      rank = (int)__builtin_amdgcn_mbcnt_hi(eq[1], __builtin_amdgcn_mbcnt_lo(eq[0], 0u)) +
+             __popc(lt[0]) + __popc(lt[1]);
+    } else {
+      for (int g = 0; g < nr; g += 16) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) rank += __builtin_amdgcn_readlane(k, g + q) < k ? 1 : 0;
+      }
     }
     if (lane < nr) {
       nbr[(size_t)i * cap + rank] = k & kKeyJMask;
@@ -64,9 +88,18 @@ __device__ __forceinline__ void finish_list(const int* key, const float4* lrec, 
   if (lane == 0) counts[i] = make_int2(nr, na);
 }
 
-// Wave w of a block scans for atom i: the candidates are the atoms of its
-// molecule, [mrange[i].x, mrange[i].y), read as contiguous records.
-__device__ __forceinline__ void pairs_mol_wave(int i, int w, float4* lds, const AevConst& C,
+// Wave w of a block scans for atoms [i0, i0 + A): an atom's candidates are the
+// atoms of its molecule, [mrange[i].x, mrange[i].y), read as contiguous records
+// and kept from one atom to the next of the same molecule (up to kMolKeep
+// batches of 64).  Bound by instructions, vector and scalar alike (118 and 67
+// per atom when ranks came from a lane read and a comparison per neighbor, now
+// 103 and 54: 49,152 atoms in molecules of 24 with the sort 16.4 -> 13.6 us).
+constexpr int kMolKeep = 3;
+__device__ __forceinline__ float readlane_f(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+template <int A>
+__device__ __forceinline__ void pairs_mol_wave(int i0, int n, int w, float4* lds, const AevConst& C,
                                                const float4* __restrict__ xyzs,
                                                const int2* __restrict__ mrange, int cap,
                                                int* __restrict__ nbr, float4* __restrict__ rec,
@@ -75,43 +108,61 @@ __device__ __forceinline__ void pairs_mol_wave(int i, int w, float4* lds, const 
   const int lane = lane_id();
   float4* lrec = lds + (size_t)w * cap;
   int* key = reinterpret_cast<int*>(lds + (size_t)4 * cap) + w * cap;
-  const float4 pi = xyzs[i];
-  const int2 ab = mrange[i];  // clamped to [0, n] by staging
-  const int a = ab.x, b = ab.y;
-  int nr = 0, na = 0;
-  for (int base = a; base < b; base += kWave) {
-    const int j = base + lane;
-    bool inR = false, inA = false;
-    int sj = 0;
-    float dx = 0.f, dy = 0.f, dz = 0.f;
-    if (j < b && j != i) {
-      const float4 pj = xyzs[j];
-      dx = __fsub_rn(pj.x, pi.x);
-      dy = __fsub_rn(pj.y, pi.y);
-      dz = __fsub_rn(pj.z, pi.z);
+  // lane k: atom i0 + k
+  const int il = lane < A && i0 + lane < n ? i0 + lane : i0;
+  const float4 pl = xyzs[il];
+  const int2 abl = mrange[il];  // clamped to [0, n] by staging
+  int a = -1, b = -1;
+  float4 pk[kMolKeep];
+#pragma unroll 1
+  for (int k = 0; k < A; ++k) {
+    const int i = i0 + k;
+    if (i >= n) break;
+    const int ak = __builtin_amdgcn_readlane(abl.x, k), bk = __builtin_amdgcn_readlane(abl.y, k);
+    const float pix = readlane_f(pl.x, k), piy = readlane_f(pl.y, k), piz = readlane_f(pl.z, k);
+    if (ak != a || bk != b) {  // wave-uniform
+      a = ak;
+      b = bk;
+#pragma unroll
+      for (int q = 0; q < kMolKeep; ++q) {
+        const int j = a + q * kWave + lane;
+        pk[q] = j < b ? xyzs[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+    int nr = 0, na = 0;
+    auto batch = [&](int base, const float4& pj) __attribute__((always_inline)) {
+      const int j = base + lane;
+      const float dx = __fsub_rn(pj.x, pix), dy = __fsub_rn(pj.y, piy), dz = __fsub_rn(pj.z, piz);
       const float d2 = dist2(dx, dy, dz);
-      inR = d2 < C.rc2_r;
-      inA = d2 < C.rc2_a;
-      sj = species_of(pj);
+      const bool on = j < b && j != i;
+      const bool inR = on && d2 < C.rc2_r, inA = on && d2 < C.rc2_a;
+      const int sj = species_of(pj);
+      const uint64_t mr = ballot(inR);
+      const int p = nr + popc_below(mr);
+      if (inR && p < cap) {
+        key[p] = make_key(j, sj, inA);
+        lrec[p] = make_float4(dx, dy, dz, __int_as_float(sj));
+      }
+      nr += __popcll(mr);
+      na += __popcll(ballot(inA));
+    };
+#pragma unroll
+    for (int q = 0; q < kMolKeep; ++q)
+      if (a + q * kWave < b) batch(a + q * kWave, pk[q]);
+    for (int base = a + kMolKeep * kWave; base < b; base += kWave)
+      batch(base, base + lane < b ? xyzs[base + lane] : make_float4(0.f, 0.f, 0.f, 0.f));
+    if (nr > cap) {
+      if (lane == 0) atomicOr(status, kStCapacity);
+      nr = cap;
+      na = na < nr ? na : nr;
     }
-    const uint64_t mr = ballot(inR);
-    const int p = nr + popc_below(mr);
-    if (inR && p < cap) {
-      key[p] = make_key(j, sj, inA);
-      lrec[p] = make_float4(dx, dy, dz, __int_as_float(sj));
-    }
-    nr += __popcll(mr);
-    na += __popcll(ballot(inA));
+    wave_lds_sync();
+    finish_list<true>(key, lrec, nr, na, i, cap, nbr, rec, counts);
+    if (A > 1) wave_lds_sync();
   }
-  if (nr > cap) {
-    if (lane == 0) atomicOr(status, kStCapacity);
-    nr = cap;
-    na = na < nr ? na : nr;
-  }
-  wave_lds_sync();
-  finish_list(key, lrec, nr, na, i, cap, nbr, rec, counts);
 }
 
+template <int A>
 __global__ __launch_bounds__(256) void k_pairs_mol(const int* __restrict__ dims, AevConst C,
                                                    const float4* __restrict__ xyzs,
                                                    const int2* __restrict__ mrange, int cap,
@@ -119,15 +170,16 @@ __global__ __launch_bounds__(256) void k_pairs_mol(const int* __restrict__ dims,
                                                    int2* __restrict__ counts,
                                                    uint32_t* __restrict__ status) {
   extern __shared__ float4 lds_mol[];
-  const int w = threadIdx.x >> 6;
-  const int i = blockIdx.x * 4 + w;
-  if (i >= dims[0]) return;
-  pairs_mol_wave(i, w, lds_mol, C, xyzs, mrange, cap, nbr, rec, counts, status);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = (blockIdx.x * 4 + w) * A, n = dims[0];
+  if (i0 >= n) return;
+  pairs_mol_wave<A>(i0, n, w, lds_mol, C, xyzs, mrange, cap, nbr, rec, counts, status);
 }
 
 // The species sort (blocks [0, nsort)) and the molecule neighbor search (the
 // blocks after them) in one launch: both read only what staging wrote, and
 // the pair scan no longer waits behind the sort's tail.
+template <int A>
 __global__ __launch_bounds__(256) void k_sort_pairs_mol(
     const int* __restrict__ dims, int nsort, int S, const int* __restrict__ hist,
     GroupTable* __restrict__ gt, int* __restrict__ row, int* __restrict__ perm, int rows_cap,
@@ -140,10 +192,10 @@ __global__ __launch_bounds__(256) void k_sort_pairs_mol(
                        wchunk_rows, status);
     return;
   }
-  const int w = threadIdx.x >> 6;
-  const int i = ((int)blockIdx.x - nsort) * 4 + w;
-  if (i >= dims[0]) return;
-  pairs_mol_wave(i, w, lds_mol, C, xyzs, mrange, cap, nbr, rec, counts, status);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = (((int)blockIdx.x - nsort) * 4 + w) * A, n = dims[0];
+  if (i0 >= n) return;
+  pairs_mol_wave<A>(i0, n, w, lds_mol, C, xyzs, mrange, cap, nbr, rec, counts, status);
 }
 
 // ---------------------------------------------------------------- cell list
@@ -471,7 +523,7 @@ __global__ __launch_bounds__(1024) void k_pairs_cell_lds(
       na = na < nr ? na : nr;
     }
     wave_lds_sync();
-    if (i >= 0 && i < n) finish_list(key, lrec, nr, na, i, cap, nbr, rec, counts);
+    if (i >= 0 && i < n) finish_list<false>(key, lrec, nr, na, i, cap, nbr, rec, counts);
     wave_lds_sync();  // the next atom reuses the wave's list
   }
 }
@@ -547,13 +599,20 @@ void launch_force_gather(const int* dims, int n_cap, const float4* xyzs, const f
 
 // ----------------------------------------------------------------- launchers
 
+// Atoms per wave of the molecule pair scan: four where that still leaves the
+// GPU its waves, since an atom's own loads and its molecule's are then waited
+// for once per four (32,768 atoms with the sort, one / four: 13 / 11.5 us,
+// 77,163 of all sizes 27 / 21; 8,192: 6 / 7).
+static int mol_atoms_per_wave(int n) { return n >= 16384 ? 4 : 1; }
+
 void launch_pairs_mol(const int* dims, int n_cap, const AevConst& C, const float4* xyzs,
                       const int2* mrange, int cap, int* nbr, float4* rec, int2* counts,
                       uint32_t* status, hipStream_t st) {
   if (n_cap <= 0) return;
-  hipLaunchKernelGGL(k_pairs_mol, dim3((n_cap + 3) / 4), dim3(256),
-                     4 * cap * (sizeof(float4) + sizeof(int)), st, dims, C, xyzs, mrange, cap, nbr,
-                     rec, counts, status);
+  const int A = mol_atoms_per_wave(n_cap);
+  hipLaunchKernelGGL(A == 4 ? k_pairs_mol<4> : k_pairs_mol<1>, dim3((n_cap + 4 * A - 1) / (4 * A)),
+                     dim3(256), 4 * cap * (sizeof(float4) + sizeof(int)), st, dims, C, xyzs, mrange,
+                     cap, nbr, rec, counts, status);
 }
 
 void launch_sort_pairs_mol(const int* dims, int n_cap, int S, const int* hist, GroupTable* gt,
@@ -561,12 +620,12 @@ void launch_sort_pairs_mol(const int* dims, int n_cap, int S, const int* hist, G
                            const AevConst& C, const float4* xyzs, const int2* mrange, int cap,
                            int* nbr, float4* rec, int2* counts, uint32_t* status,
                            hipStream_t st) {
-  const int nsort = stage_blocks(n_cap);
-  const int npair = n_cap > 0 ? (n_cap + 3) / 4 : 0;
-  hipLaunchKernelGGL(k_sort_pairs_mol, dim3(nsort + npair), dim3(256),
-                     4 * cap * (sizeof(float4) + sizeof(int)), st, dims, nsort, S, hist, gt, row,
-                     perm, rows_cap, off, wchunk_rows, C, xyzs, mrange, cap, nbr, rec, counts,
-                     status);
+  const int nsort = stage_blocks(n_cap), A = mol_atoms_per_wave(n_cap);
+  const int npair = n_cap > 0 ? (n_cap + 4 * A - 1) / (4 * A) : 0;
+  hipLaunchKernelGGL(A == 4 ? k_sort_pairs_mol<4> : k_sort_pairs_mol<1>, dim3(nsort + npair),
+                     dim3(256), 4 * cap * (sizeof(float4) + sizeof(int)), st, dims, nsort, S, hist,
+                     gt, row, perm, rows_cap, off, wchunk_rows, C, xyzs, mrange, cap, nbr, rec,
+                     counts, status);
 }
 
 void launch_pairs_cell(const int* dims, int n_cap, const AevConst& C, const BoxConst& B,
