@@ -161,7 +161,9 @@ void launch_groups(const int* dims, int n_cap, int S, int* hist, GroupTable* gt,
                    int rows_cap, const int* off, int wchunk_rows, uint32_t* status,
                    hipStream_t st);
 // k_groups + k_scatter in one launch; for n_cap <= 256 * kFusedSortBlocks
-constexpr int kFusedSortBlocks = 256;
+// (each block adds up all blocks' counts: beside the pair scan of 77,163 atoms
+// that hides, while the two launches took 12 us)
+constexpr int kFusedSortBlocks = 512;
 void launch_sort_scatter(const int* dims, int n_cap, int S, const float4* xyzs, const int* hist,
                          GroupTable* gt, int* row, int* perm, int rows_cap, const int* off,
                          int wchunk_rows, uint32_t* status, hipStream_t st);
