@@ -45,20 +45,12 @@ __global__ __launch_bounds__(256) void k_stage(int n_arg, int nmol_arg, int clea
   }
   if (threadIdx.x < kMaxS) h[threadIdx.x] = 0;
   if (threadIdx.x == 0) bits = 0;
-  // every step-th molecule offset, step chosen so that at most kOffSamples
-  // intervals remain: the molecule search runs in LDS and ends with at most
-  // log2(step) dependent global loads (none for up to kOffSamples molecules)
-  const int step = nmol > 0 ? (nmol + kOffSamples - 1) / kOffSamples : 1;
-  const int K = nmol > 0 ? (nmol + step - 1) / step : 0;
-  for (int k = threadIdx.x; k <= K; k += blockDim.x) {
-    const int m = k * step;
-    smp[k] = off[m < nmol ? m : nmol];
-  }
-  __syncthreads();
+  // the atom's inputs, in flight while the offsets are sampled
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  float x = 0.f, y = 0.f, z = 0.f;
+  int s = 0;
+  uint32_t st = 0;
   if (i < n) {
-    float x, y, z;
-    uint32_t st = 0;
     int g = i;  // row of the position arrays
     if (gidx) {  // subset of a larger system: gather by index
       g = gidx[i];
@@ -76,7 +68,19 @@ __global__ __launch_bounds__(256) void k_stage(int n_arg, int nmol_arg, int clea
       y = pos[3 * g + 1];
       z = pos[3 * g + 2];
     }
-    int s = species[i];
+    s = species[i];
+  }
+  // every step-th molecule offset, step chosen so that at most kOffSamples
+  // intervals remain: the molecule search runs in LDS and ends with at most
+  // log2(step) dependent global loads (none for up to kOffSamples molecules)
+  const int step = nmol > 0 ? (nmol + kOffSamples - 1) / kOffSamples : 1;
+  const int K = nmol > 0 ? (nmol + step - 1) / step : 0;
+  for (int k = threadIdx.x; k <= K; k += blockDim.x) {
+    const int m = k * step;
+    smp[k] = off[m < nmol ? m : nmol];
+  }
+  __syncthreads();
+  if (i < n) {
     if (s < 0 || s >= S) {
       st |= kStSpecies;
       s = clampi(s, S);
