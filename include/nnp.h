@@ -110,9 +110,9 @@ typedef struct {
 } nnp_mlp_params;
 
 /* Creates a potential on the current HIP device: validates the parameters,
- * uploads the symmetry-function constants and packs the weights (FP32 master
- * copy, BF16 copy and transposed copies for the adjoint).  This is the only
- * call that copies weights from the host.  Returns NNP_E_INVALID for an
+ * uploads the symmetry-function constants and packs the weights (the copies of
+ * W and W^T that the precision and widths need; the parameters themselves are
+ * not kept).  This is the only call that copies weights from the host.  Returns NNP_E_INVALID for an
  * unsupported layout, NNP_E_OOM / NNP_E_HIP on device failures. */
 nnp_status nnp_create(const nnp_aev_params* aev, const nnp_mlp_params* mlp,
                       nnp_precision precision, nnp_handle** out);

@@ -103,7 +103,9 @@ __device__ __forceinline__ int pair_block(int p, int q, int S) {
 // accumulated in registers and stored block by block, so no LDS row is needed.
 constexpr int kPairChunk = 64;
 constexpr int kFwdBytesPerNbr = 16 + 8 + 4;
-constexpr int kFwdPairBytes = 32 + 16 + 4;
+// (the block is a byte: lists of 128 entries then leave LDS for six waves per
+// SIMD, an int for five: 80 -> 78 us on the 23,001-atom water box)
+constexpr int kFwdPairBytes = 32 + 16 + 1;
 
 typedef float aev_f32x4 __attribute__((ext_vector_type(4)));
 
@@ -143,7 +145,7 @@ struct FwdLds {
   float* fa;    // angular cutoff value
   float* pw;    // [kPairChunk][8]
   float* pg;    // [kPairChunk][4]: distance shifts 0, 2, 1, 3
-  int* pblk;    // [kPairChunk]: block, -1 past the last pair
+  unsigned char* pblk;  // [kPairChunk]: block, 255 past the last pair
 };
 
 // The angular pair t of the na angular neighbors at entry `base`, to table
@@ -181,7 +183,7 @@ __device__ __forceinline__ int pair_geometry(int t, int na, bool valid, const Ae
   reinterpret_cast<float4*>(L.pw)[2 * slot + 1] = make_float4(w[4], w[5], w[6], w[7]);
   reinterpret_cast<float4*>(L.pg)[slot] = make_float4(g[0], g[2], g[1], g[3]);
   const int blk = valid ? pair_block(__float_as_int(L.fs[a].y), __float_as_int(L.fs[b].y), C.S) : -1;
-  L.pblk[slot] = blk;
+  L.pblk[slot] = (unsigned char)blk;
   return blk;
 }
 
@@ -231,7 +233,7 @@ __device__ __forceinline__ unsigned seen_bits(int e, int nr, int na, const float
 // one-hot row is zero (no lane is switched off), table reads have constant
 // offsets, which tiles a pass touches is read from two wave-wide masks, and
 // the row's k-steps come from one bitwise or over the entries and are formed
-// for four atoms at once.  Measured: 23,001-atom water box 99 -> 80 us (1,456
+// for four atoms at once.  Measured: 23,001-atom water box 99 -> 78 us (1,456
 // -> 977 vector instructions per atom), 4,500 atoms in FP32 32 -> 27 us, the
 // 32,768-atom batch 23.9 -> 21.7 us, 77,163 mixed atoms 50.5 -> 45.2 us, 1,645
 // atoms (a wave per atom now) 14.6 -> 6.3 us.
@@ -257,7 +259,7 @@ k_aev_fwd(const int* __restrict__ dims, AevConst C, const float4* __restrict__ r
   L.pw = pw0 + w * kPairChunk * kNZ;
   float* pg0 = pw0 + 4 * kPairChunk * kNZ;
   L.pg = pg0 + w * kPairChunk * kNA;
-  L.pblk = reinterpret_cast<int*>(pg0 + 4 * kPairChunk * kNA) + w * kPairChunk;
+  L.pblk = reinterpret_cast<unsigned char*>(pg0 + 4 * kPairChunk * kNA) + w * kPairChunk;
 
   // entry `slot`; past the list (not `in`): a species no one-hot row has
   auto setup = [&](int slot, const float4 q, bool in, bool ang) __attribute__((always_inline)) {
@@ -452,7 +454,7 @@ k_aev_fwd(const int* __restrict__ dims, AevConst C, const float4* __restrict__ r
         }
         const float* pwe = L.pw + (sl + kq) * kNZ + z;
         const float2* pge = reinterpret_cast<const float2*>(L.pg) + (sl + kq) * 2 + ah;
-        const int* pbe = L.pblk + sl + kq;
+        const unsigned char* pbe = L.pblk + sl + kq;
         for (int t0 = 0; t0 < tn; t0 += 16) {
 #pragma unroll
           for (int q = 0; q < 16; q += 4) {

@@ -57,7 +57,7 @@ template <> struct Frag<float> {
 // k-step s with s % P == u.  Loads are unconditional (a step past the end
 // re-reads the last step, which keeps every access inside B), so the wait
 // before a step's MFMAs is an exact count of the loads issued after it.
-// B is stored in fragment order (see k_pack): tile nt, k-step ks, lane l at
+// B is stored in fragment order (see k_pack_frag): tile nt, k-step ks, lane l at
 // ((nt * (K/KS) + ks) * 64 + l) * EL, so each fragment load is one contiguous
 // 1 KB block per wave.  Steps are counted per pass over [0, nsp), nsp = ns
 // rounded up to the ring depth: steps in [ns, nsp) re-read the last step
