@@ -167,7 +167,7 @@ struct Plan {
   size_t total = 0;
   size_t status, dims, gt, xyzs, mol, mrange, row, perm, hist, nbr, counts, rec;
   size_t cell_of, cell_cnt, cell_start, cursor, cell_atoms, cell_xyzs;
-  size_t X, H1, H2, H3, D3, D2, D1, G, erow, uprow, wpart, wact, pos32;
+  size_t X, H1, H2, H3, D3, D2, D1, G, erow, uprow, wpart, part, wact, pos32;
   size_t kmask;  // per feature row: the k-steps that may be nonzero
   size_t pgrad;  // deterministic mode: per-entry adjoint rows [n][cap]
   size_t grp;    // owned/ghost evaluation: group offsets (3 int) and upstream (2 double)
@@ -248,8 +248,6 @@ Plan make_plan(const nnp_handle* h, int n, int nmol, const BoxConst& B, bool wgr
   P.ncell = B.periodic ? B.nc[0] * B.nc[1] * B.nc[2] : 0;
   P.rows_cap = (int)align_up((size_t)std::max(n, 1), kPad) + h->S * kPad;
   P.nblk = stage_blocks(n);
-  P.wchunk = wgrad_chunk_rows(n);
-  P.nwchunks = (n + P.wchunk - 1) / P.wchunk + h->S;
   const size_t esz = h->prec == NNP_MLP_BF16 ? 2 : 4;
   const size_t R = (size_t)P.rows_cap;
   const size_t N = (size_t)std::max(n, 1);
@@ -293,16 +291,26 @@ Plan make_plan(const nnp_handle* h, int n, int nmol, const BoxConst& B, bool wgr
   P.D3 = take(R * w3 * esz);
   P.D2 = take(R * w2 * esz);
   P.D1 = take(R * w1 * h->n_models * esz);  // members side by side in each row
-  P.G = take(R * h->Fp * esz);
-  P.erow = take(R * 4 * h->n_models);
-  P.uprow = take(R * 4);
   size_t plen = 0;  // one element's parameters
   for (int l = 0; l < kLayers; ++l) {
     const size_t in = l == 0 ? h->F : h->width[l];
     plen += (size_t)h->width[l + 1] * in + h->width[l + 1];
   }
-  P.wpart = wgrad ? take((size_t)P.nwchunks * wgrad_part_pitch((long)plen) * 4) : 0;
-  P.wact = wgrad ? take((size_t)P.nwchunks * 64) : 0;
+  P.G = take(R * h->Fp * esz);
+  // weight-gradient partials: room for chunks of 1,024 rows and, the adjoint
+  // having read it by then, dE/dG's before it; chunks as small as fit there
+  const size_t wpart = wgrad ? ((size_t)(n + 1023) / 1024 + h->S) * plen * 4 : 0;
+  P.wpart = wgrad ? take(wpart) : 0;
+  const size_t room = wgrad ? P.wpart + wpart - P.G : 0;
+  const size_t chunk_bytes = (size_t)wgrad_part_pitch((long)plen) * 4 + 64;
+  for (P.wchunk = wgrad_chunk_rows(n);; P.wchunk += 128) {
+    P.nwchunks = (n + P.wchunk - 1) / P.wchunk + h->S;
+    if (P.wchunk >= 1024 || P.nwchunks * chunk_bytes <= room) break;
+  }
+  P.part = P.G;
+  P.wact = P.part + P.nwchunks * (chunk_bytes - 64);
+  P.erow = take(R * 4 * h->n_models);
+  P.uprow = take(R * 4);
   P.pos32 = take(N * 12);
   P.total = o;
   return P;
@@ -615,7 +623,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
   }
   if (io.dparams) {
     StageTimer t(h, io.timed, ST_WGRAD, st);
-    float* part = at<float>(ws, P.wpart);
+    float* part = at<float>(ws, P.part);
     const float* up = at<float>(ws, P.uprow);
     const WgradLayer layers[kLayers] = {
         {D1, X, w1, Fp, w1, h->F, false, S * kNR, h->C.A0 - S * kNR},
