@@ -497,7 +497,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
       NetGradArgs ga{gt, D1, ldd1, bf ? (const void*)h->WT0cq : h->WT0cqf, kmask, G, Fp,
                      na.order};
       StageTimer t(h, io.timed, ST_GRADG, st);
-      launch_net_grad<T>(ga, P.rows_cap, st);
+      launch_net_grad<T>(ga, P.n, P.rows_cap, st);
     }
   }
   // other widths, layer by layer.  B operands: row-major W (both precisions)

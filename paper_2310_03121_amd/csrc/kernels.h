@@ -273,7 +273,7 @@ template <typename T>
 bool launch_mlp_net(const int* width, const NetArgs& a, int n_rows, int rows_cap, int members,
                     hipStream_t st);
 template <typename T>
-void launch_net_grad(const NetGradArgs& a, int rows_cap, hipStream_t st);
+void launch_net_grad(const NetGradArgs& a, int n_rows, int rows_cap, hipStream_t st);
 
 // md.hip
 void launch_vv_kick_drift(const int* dims, int n_cap, double* x, double* v, const float* F,

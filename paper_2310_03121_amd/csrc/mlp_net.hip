@@ -319,9 +319,128 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
+// Small FP32 calls: one workgroup per 16-row tile and four active k-steps of
+// it.  The tile's deltas all lie in LDS (16 rows of up to 8 KB), so the loop has
+// no barriers, a ring of 16 steps keeps the weights' latency out of it, and no
+// products run for 48 absent rows; the sums are those of the large form, step
+// by step.  Eight members, 128 / 1,024 atoms: 71 / 72 us in the large form, 27 /
+// 53 here.  BF16, half the bytes and an eighth of the matrix time, is faster in
+// the large form, which multiplies while it loads (53 / 1,024 atoms 12 / 13 us,
+// 14 / 15 here).
+constexpr int kGradSmallRing = 16;
+constexpr int kGradSmallRows = 1024;
+template <typename T, int S = 0>
+__device__ __forceinline__ void grad_steps(const unsigned char* ap, GradRing<T, 1, kGradSmallRing>& br,
+                                           int s0, f32x4_t (&acc)[1][2], uint4 (&fe)[1],
+                                           uint4 (&fo)[1]) {
+  constexpr int P = kGradSmallRing, SB = Frag<T>::KS * sizeof(T);
+  if constexpr (S < P) {
+    if constexpr (S % 2 == 0)
+      kstep<T, 1, 2, P, S, true, (S + 1 < P)>(ap + (S + 1) * SB, 0, br, s0 + S + P, acc, fe, fo);
+    else
+      kstep<T, 1, 2, P, S, true, (S + 1 < P)>(ap + (S + 1) * SB, 0, br, s0 + S + P, acc, fo, fe);
+    grad_steps<T, S + 1>(ap, br, s0, acc, fe, fo);
+  }
+}
+
 template <typename T>
-void launch_net_grad(const NetGradArgs& a, int rows_cap, hipStream_t st) {
+constexpr int grad_small_steps(int K) {  // K in steps, whole rings
+  return (K / Frag<T>::KS + kGradSmallRing - 1) / kGradSmallRing * kGradSmallRing;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_net_grad_small(NetGradArgs a) {
+  constexpr int BM = 16, ES = sizeof(T), SB = Frag<T>::KS * ES;
+  static_assert(SB == 64, "a step is four 16-byte pieces of a row");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ unsigned long long rmask[BM];
+  __shared__ int rrow[BM];
+  const GroupTable* gt = a.gt;
+  const int nt = gt->total_rows / BM;
+  if ((int)blockIdx.x >= nt) return;
+  const int row0 = xcd_tile(blockIdx.x, nt) * BM;
+  const int s = tile_species(gt, row0);
+  const int row_end = gt->pstart[s] + gt->cnt[s];
+  if (row0 >= row_end) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rl = lane & 15, cq = (lane >> 4) * 4;
+  const int K = a.K, ldx = a.ldx, nks = ldx / 32;
+  const unsigned long long all = nks >= 64 ? ~0ull : (1ull << nks) - 1ull;
+  unsigned long long m = 0ull;
+  int row = row0 + rl;
+  if (row < row_end) {
+    m = (a.order ? a.order[row].mask : a.kmask[row]) & all;
+    if (a.order) row = a.order[row].row;
+  }
+  if (tid < BM) {
+    rmask[tid] = m;
+    rrow[tid] = row;
+  }
+  const unsigned long long U =
+      ((unsigned long long)wave_or((unsigned)(m >> 32)) << 32) | wave_or((unsigned)m);
+  const int nact = __popcll(U);
+  const int p = (int)blockIdx.y * 4 + wv;
+  if ((int)blockIdx.y * 4 >= nact) return;  // block-uniform
+  int q[1];
+  q[0] = __builtin_amdgcn_readlane(nth_set_bit(U, lane), p < nact ? p : nact - 1);
+  GradRing<T, 1, kGradSmallRing> br;
+  br.init(static_cast<const T*>(a.Wc) + (size_t)s * ldx * K, K, lane, q);
+  br.prologue();
+  const int nsp = grad_small_steps<T>(K), stride = nsp * SB + 16;
+  const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(static_cast<const T*>(a.D1) + (size_t)row0 * K), (short)0,
+      (row_end - row0) * K * ES, kBufferRsrcWord3);
+  constexpr int NL = 8;
+  const int pieces = nsp * 4;  // per row
+  for (int c0 = tid; c0 < BM * pieces; c0 += 256 * NL) {
+    u32x4_t v[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int c = c0 + 256 * k, r = c / pieces, at = (c - r * pieces) * 16;
+      v[k] = __builtin_amdgcn_raw_buffer_load_b128(
+          src, r < BM && at < K * ES ? (unsigned)(r * K * ES + at) : kOutOfRange, 0, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int c = c0 + 256 * k, r = c / pieces, at = (c - r * pieces) * 16;
+      if (r < BM)
+        *reinterpret_cast<uint4*>(smem + r * stride + at) =
+            make_uint4(v[k][0], v[k][1], v[k][2], v[k][3]);
+    }
+  }
+  __syncthreads();
+  f32x4_t acc[1][2];
+  zero_acc(acc);
+  const unsigned char* ap = smem + rl * stride + (lane >> 4) * 16;
+  for (int s0 = 0; s0 < nsp; s0 += kGradSmallRing) {
+    uint4 fe[1], fo[1];
+    load_a<1>(ap, 0, fe);
+    grad_steps<T>(ap, br, s0, acc, fe, fo);
+    ap += kGradSmallRing * SB;
+  }
+  if (p >= nact) return;  // wave-uniform, no barrier after
+  if (row0 + rl < row_end && ((rmask[rl] >> q[0]) & 1ull)) {
+    T* g = static_cast<T*>(a.G) + (size_t)rrow[rl] * ldx + q[0] * 32 + cq;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      Store<T>::put4(g + j * 16, make_float4(acc[0][j][0], acc[0][j][1], acc[0][j][2], acc[0][j][3]));
+  }
+}
+
+template <typename T>
+void launch_net_grad(const NetGradArgs& a, int n_rows, int rows_cap, hipStream_t st) {
   const int tiles = rows_cap / 64, nks = a.ldx / 32;
+  if constexpr (sizeof(T) == 4) {
+    if (n_rows <= kGradSmallRows) {
+      static const bool attr = (ensure_lds(k_net_grad_small<T>), true);
+      (void)attr;
+      const size_t lds = 16 * ((size_t)grad_small_steps<T>(a.K) * 64 + 16);
+      hipLaunchKernelGGL(k_net_grad_small<T>, dim3(rows_cap / 16, (nks + 3) / 4), dim3(256), lds,
+                         st, a);
+      return;
+    }
+  }
   // two k-steps per wave where the tiles alone fill the GPU (the deltas are
   // read once per eight k-steps then), else one
   if (tiles >= 256)
@@ -329,7 +448,7 @@ void launch_net_grad(const NetGradArgs& a, int rows_cap, hipStream_t st) {
   else
     hipLaunchKernelGGL((k_net_grad<T, 1>), dim3(tiles, (nks + 3) / 4), dim3(256), 0, st, a);
 }
-template void launch_net_grad<bf16_t>(const NetGradArgs&, int, hipStream_t);
-template void launch_net_grad<float>(const NetGradArgs&, int, hipStream_t);
+template void launch_net_grad<bf16_t>(const NetGradArgs&, int, int, hipStream_t);
+template void launch_net_grad<float>(const NetGradArgs&, int, int, hipStream_t);
 
 }  // namespace nnp
