@@ -634,7 +634,12 @@ void launch_pairs_cell(const int* dims, int n_cap, const AevConst& C, const BoxC
                        float4* rec, int2* counts, uint32_t* status, int S, const int* hist,
                        GroupTable* gt, int* row, int* perm, int rows_cap, const int* off,
                        int wchunk_rows, hipStream_t st) {
-  if (n_cap <= 0) return;
+  if (n_cap <= 0) {  // nothing to bin; the group table is wanted all the same
+    if (gt)
+      launch_sort_scatter(dims, n_cap, S, xyzs, hist, gt, row, perm, rows_cap, off, wchunk_rows,
+                          status, st);
+    return;
+  }
   const int ncell = B.nc[0] * B.nc[1] * B.nc[2];
   // staging zeroed cell_cnt[0 .. cell_zero_ints(ncell))
   const dim3 grid((n_cap + 255) / 256);
