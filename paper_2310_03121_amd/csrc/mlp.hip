@@ -1331,6 +1331,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   int r0 = 0, r1 = 0;
   const int nc = a.gt->n_wchunks, nc8 = (nc + 7) / 8, slot = blockIdx.x / 8;
+  if (nc <= 0) return;  // a system of no atoms (and the block index is divided by nc)
   constexpr bool XCD = sizeof(T) == 2;
   int b = XCD ? slot / nc8 : blockIdx.x / nc;
   const int c = XCD ? slot % nc8 * 8 + blockIdx.x % 8 : blockIdx.x % nc;

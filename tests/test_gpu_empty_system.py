@@ -41,3 +41,15 @@ def test_energy_and_forces(prec, box):
     pot.energy_forces(pos, sp, off, b, out=(E, F))
     pot.check()
     assert E.tolist() == [0.0] and bool((F == 2.0).all())
+
+
+@pytest.mark.parametrize("box", ["no box", "box"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_weight_gradients(prec, box):
+    print(f"\n[case] weight gradients of no atoms, {prec}, {box}", flush=True)
+    pot, pos, sp, off, b = empty_call(prec, box)
+    up = torch.full((1,), 2.0, dtype=torch.float64, device="cuda")
+    _, gw, E = pot.backward(pos, sp, off, up, b)
+    pot.check()
+    assert E.tolist() == [0.0]
+    assert gw.numel() == pot.n_params and bool((gw == 0.0).all())
