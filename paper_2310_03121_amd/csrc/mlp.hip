@@ -101,9 +101,10 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_rb(GemmArgs a) {
   // return zeros in hardware.  So no load sits behind a branch, which would
   // make the compiler assume it may not have been issued and let every later
   // wait for the weight ring also wait for one more ring slot.
+  const int rows = row_end - row0 < BM ? row_end - row0 : BM;
   const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<T*>(A + (size_t)row0 * a.lda), (short)0,
-      (row_end - row0) * a.lda * (int)sizeof(T), kBufferRsrcWord3);
+      const_cast<T*>(A + (size_t)row0 * a.lda), (short)0, rows * a.lda * (int)sizeof(T),
+      kBufferRsrcWord3);
   auto aload = [&](int c, uint4 (&ra)[NVA]) __attribute__((always_inline)) {
 #pragma unroll
     for (int v = 0; v < NVA; ++v) {

@@ -256,9 +256,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     q[u] = __builtin_amdgcn_readlane(qlist, p < nact ? p : nact - 1);
   }
 
+  // (the tile's rows only: an element's may be more bytes than a range can say)
+  const int rows = row_end - row0 < BM ? row_end - row0 : BM;
   const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<T*>(static_cast<const T*>(a.D1) + (size_t)row0 * K), (short)0,
-      (row_end - row0) * K * ES, kBufferRsrcWord3);
+      rows * K * ES, kBufferRsrcWord3);
   constexpr int RPV = NTH / 16, NVA = BM / RPV;
   auto aload = [&](int c, uint4 (&ra)[NVA]) __attribute__((always_inline)) {
     const int col = c * (kNetChunk / ES) + (tid & 15) * (16 / ES);
@@ -388,9 +390,10 @@ __global__ __launch_bounds__(256) void k_net_grad_small(NetGradArgs a) {
   br.init(static_cast<const T*>(a.Wc) + (size_t)s * ldx * K, K, lane, q);
   br.prologue();
   const int nsp = grad_small_steps<T>(K), stride = nsp * SB + 16;
+  const int rows = row_end - row0 < BM ? row_end - row0 : BM;
   const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<T*>(static_cast<const T*>(a.D1) + (size_t)row0 * K), (short)0,
-      (row_end - row0) * K * ES, kBufferRsrcWord3);
+      rows * K * ES, kBufferRsrcWord3);
   constexpr int NL = 8;
   const int pieces = nsp * 4;  // per row
   for (int c0 = tid; c0 < BM * pieces; c0 += 256 * NL) {
