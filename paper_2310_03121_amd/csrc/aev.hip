@@ -24,6 +24,8 @@
 // (read from the network backward pass, only the blocks the atom touches).
 // Its radial part is pulled from both sides of a pair, so only the angular
 // neighbors are scattered to.
+#include <type_traits>
+
 #include "kernels.h"
 #include "energy_sum.h"
 
@@ -781,20 +783,26 @@ struct AdjLds {
 // derivative, so an atom adds both to its own force and writes to no
 // neighbor.  Lists are symmetric (the predicate sees the negated
 // displacement, the same distance), so every pair comes up from both sides.
-// (PULL = false: dE_i's part alone, for the caller to scatter.)
-template <typename GT, bool PULL = true>
+// That fails only in a call whose status has a bit of kStAsym (`cut`): j's list
+// need not hold i then, nor need the network have written j's block of dE/dG,
+// so dE_i's part alone is returned, for the caller to scatter, as without PULL.
+// (The second block is i's own then, times zero: with a branch around its loads
+// the 23,001-atom box took 1.7 us more a call, so 0.9.)
+constexpr uint32_t kStAsym = kStCapacity | kStOffsets;
+template <typename GT, bool PULL>
 __device__ __forceinline__ float radial_pull(const AevConst& C, const GT* __restrict__ gi,
-                                             const GT* __restrict__ gj, float r) {
+                                             const GT* __restrict__ gj, bool cut, float r) {
   float gv[16], gw[16];
   Load16<GT>::get(gi, gv);
-  if constexpr (PULL) Load16<GT>::get(gj, gw);
+  if constexpr (PULL) Load16<GT>::get(cut ? gi : gj, gw);
+  const float pull = cut ? 0.f : 1.f;
   float dfr;
   const float fr = cutoff_val(r, C.inv_rc_r, dfr, C.pi_2rc_r);
   float acc = 0.f;
 #pragma unroll
   for (int m = 0; m < kNR; ++m) {
     const float u = r - C.shf_r[m];
-    const float gm = PULL ? gv[m] + gw[m] : gv[m];
+    const float gm = PULL ? __builtin_fmaf(gw[m], pull, gv[m]) : gv[m];
     acc += gm * fast_exp2(-C.eta_r_l2e * u * u) * (dfr - C.eta_r2 * u * fr);
   }
   return C.cR * acc * fast_rcp(r);
@@ -824,7 +832,7 @@ __device__ __forceinline__ void adjoint_one(int i, int n, const AevConst& C, int
                                             const int* __restrict__ nbr, int nr, int na, int cap,
                                             const int* __restrict__ row_of,
                                             const GT* __restrict__ grow, const GT* __restrict__ g,
-                                            int ldg, float sign, AdjLds& L, Put&& put) {
+                                            int ldg, float sign, bool cut, AdjLds& L, Put&& put) {
   const int lane = lane_id();
   const int S = C.S;
   const size_t at0 = (size_t)i * cap;
@@ -839,8 +847,8 @@ __device__ __forceinline__ void adjoint_one(int i, int n, const AevConst& C, int
     const int sp = species_of(v);
     const float r = fast_sqrt(dist2(v.x, v.y, v.z));
     const float sc = radial_pull<GT, PULL>(
-        C, grow + sp * kNR, PULL ? g + (size_t)row_of[j] * ldg + si * kNR : nullptr, r);
-    if (!PULL) {
+        C, grow + sp * kNR, PULL ? g + (size_t)row_of[j] * ldg + si * kNR : nullptr, cut, r);
+    if (!PULL || cut) {
       put(j, 0, -sign * v.x * sc);
       put(j, 1, -sign * v.y * sc);
       put(j, 2, -sign * v.z * sc);
@@ -1063,7 +1071,7 @@ __device__ __forceinline__ bool adjoint_quads(int i0, int n, const AevConst& C,
         const float r = fast_sqrt(dist2(v.x, v.y, v.z));
         const float sc = radial_pull<GT, PULL>(
             C, g + (size_t)row[h] * ldg + sp * kNR,
-            PULL ? g + (size_t)row_of[j] * ldg + si[h] * kNR : nullptr, r);
+            PULL ? g + (size_t)row_of[j] * ldg + si[h] * kNR : nullptr, false, r);
         if (!PULL) {
           if (e < na[h]) {  // (with the angular part)
             gx[h] = v.x * sc;
@@ -1179,14 +1187,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     const int* __restrict__ dims, AevConst C, const float4* __restrict__ xyzs,
     const float4* __restrict__ rec, const int* __restrict__ nbr, const int2* __restrict__ counts,
     int cap, const int* __restrict__ row_of, const GT* __restrict__ g, int ldg,
-    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total, int nb_adj,
-    EnergyArgs EA) {
+    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total,
+    const uint32_t* __restrict__ status, int nb_adj, EnergyArgs EA) {
   __shared__ AdjLds lds[4];
   if ((int)blockIdx.x >= nb_adj) {  // block-uniform: the molecular energy sums
     energy_block((int)blockIdx.x - nb_adj, dims, EA);
     return;
   }
   const int n = dims[0];
+  const bool cut = (*status & kStAsym) != 0;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int i = (int)blockIdx.x * 4 + w;
   if (i >= n) return;
@@ -1194,7 +1203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
   const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
   adjoint_one<GT, true>(i, n, C, species_of(xyzs[i]), rec, nbr, nr, na, cap, row_of,
-                        g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w],
+                        g + (size_t)row_of[i] * ldg, g, ldg, sign, cut, lds[w],
                         [&](int j, int c, float x) {
                           if (gidx) {
                             j = gidx[j];
@@ -1214,8 +1223,8 @@ __global__ __launch_bounds__(256) void k_aev_bwd_small(
     const int* __restrict__ dims, AevConst C, const float4* __restrict__ xyzs,
     const float4* __restrict__ rec, const int* __restrict__ nbr, const int2* __restrict__ counts,
     int cap, const int* __restrict__ row_of, const GT* __restrict__ g, int ldg,
-    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total, int nb_adj,
-    EnergyArgs EA) {
+    float* __restrict__ out, float sign, const int* __restrict__ gidx, int n_total,
+    const uint32_t* __restrict__, int nb_adj, EnergyArgs EA) {
   __shared__ union {
     QuadLds<1> quad;
     AdjLds one;
@@ -1244,7 +1253,7 @@ __global__ __launch_bounds__(256) void k_aev_bwd_small(
     const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
     const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
     adjoint_one<GT, false>(i, n, C, 0, rec, nbr, nr, na, cap, row_of,
-                           g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w].one, put);
+                           g + (size_t)row_of[i] * ldg, g, ldg, sign, false, lds[w].one, put);
     wave_lds_sync();  // the next atom reuses the LDS
   }
 }
@@ -1302,7 +1311,8 @@ k_aev_bwd_mol(const int* __restrict__ dims, AevConst C, const float4* __restrict
               const float4* __restrict__ rec, const int* __restrict__ nbr,
               const int2* __restrict__ counts, int cap, const int* __restrict__ row_of,
               const GT* __restrict__ g, int ldg, float* __restrict__ out, float sign,
-              const int2* __restrict__ mrange, int nb_adj, EnergyArgs EA) {
+              const int2* __restrict__ mrange, const uint32_t* __restrict__ status, int nb_adj,
+              EnergyArgs EA) {
   constexpr int kWin = 3 * kMolBlock;
   __shared__ union {
     QuadLds<2> quad;
@@ -1314,6 +1324,7 @@ k_aev_bwd_mol(const int* __restrict__ dims, AevConst C, const float4* __restrict
     return;
   }
   const int n = dims[0];
+  const bool cut = (*status & kStAsym) != 0;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int base = (int)blockIdx.x * kMolBlock, w0 = base - kMolBlock;
   for (int t = threadIdx.x; t < 3 * kWin; t += blockDim.x) win[t] = 0.f;
@@ -1327,18 +1338,23 @@ k_aev_bwd_mol(const int* __restrict__ dims, AevConst C, const float4* __restrict
   };
   static_assert(kMolBlock == 8 * kMolWaves, "eight atoms per wave");
   const int i0 = base + 8 * w;
-  if (i0 < n && !adjoint_quads<GT, 2, true>(i0, n, C, xyzs, rec, nbr, counts, cap, row_of, g, ldg,
-                                            sign, lds[w].quad, put)) {
+  auto one_by_one = [&](auto pull) __attribute__((always_inline)) {
     for (int a = 0; a < 8 && i0 + a < n; ++a) {
       const int i = i0 + a;
       const int2 cn = counts[i];
       const int nr = cn.x < 0 ? 0 : (cn.x > cap ? cap : cn.x);
       const int na = cn.y < 0 ? 0 : (cn.y > nr ? nr : cn.y);
-      adjoint_one<GT, true>(i, n, C, species_of(xyzs[i]), rec, nbr, nr, na, cap, row_of,
-                            g + (size_t)row_of[i] * ldg, g, ldg, sign, lds[w].one, put);
+      adjoint_one<GT, pull.value>(i, n, C, species_of(xyzs[i]), rec, nbr, nr, na, cap, row_of,
+                                  g + (size_t)row_of[i] * ldg, g, ldg, sign, false, lds[w].one,
+                                  put);
       wave_lds_sync();  // the next atom reuses the LDS
     }
-  }
+  };
+  if (__builtin_expect(cut, 0))
+    one_by_one(std::false_type{});
+  else if (i0 < n && !adjoint_quads<GT, 2, true>(i0, n, C, xyzs, rec, nbr, counts, cap, row_of, g,
+                                                 ldg, sign, lds[w].quad, put))
+    one_by_one(std::true_type{});
   __syncthreads();
   for (int t = threadIdx.x; t < kWin; t += blockDim.x) {
     const int j = w0 + t;
@@ -1402,8 +1418,8 @@ template <typename GT>
 void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4* xyzs,
                     const float4* rec, const int* nbr, const int2* counts, int cap, const int* row_of, const GT* g,
                     int ldg, float* out, float sign, const int* gidx, int n_total,
-                    const int2* mrange, const EnergyArgs* energy, int nmol_cap, float4* pgrad,
-                    hipStream_t st) {
+                    const int2* mrange, const uint32_t* status, const EnergyArgs* energy,
+                    int nmol_cap, float4* pgrad, hipStream_t st) {
   if (pgrad) {
     const int nb_e = energy && energy->E && nmol_cap > 0 ? nmol_cap : 0;
     const EnergyArgs ea = nb_e ? *energy : EnergyArgs{};
@@ -1431,20 +1447,20 @@ void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4*
   if (nb_adj + nb_e == 0) return;
   if (window)
     hipLaunchKernelGGL((k_aev_bwd_mol<GT>), dim3(nb_adj + nb_e), dim3(64 * kMolWaves), 0, st, dims,
-                       C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, out, sign, mrange, nb_adj,
-                       ea);
+                       C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, out, sign, mrange, status,
+                       nb_adj, ea);
   else
     hipLaunchKernelGGL(small ? k_aev_bwd_small<GT> : k_aev_bwd<GT>, dim3(nb_adj + nb_e), dim3(256),
                        0, st, dims, C, xyzs, rec, nbr, counts, cap, row_of, g, ldg, out, sign,
-                       gidx, n_total, nb_adj, ea);
+                       gidx, n_total, status, nb_adj, ea);
 }
 template void launch_aev_bwd<float>(const int*, int, const AevConst&, const float4*, const float4*, const int*,
                                     const int2*, int, const int*, const float*, int, float*, float,
-                                    const int*, int, const int2*, const EnergyArgs*, int, float4*,
-                                    hipStream_t);
+                                    const int*, int, const int2*, const uint32_t*, const EnergyArgs*,
+                                    int, float4*, hipStream_t);
 template void launch_aev_bwd<bf16_t>(const int*, int, const AevConst&, const float4*, const float4*, const int*,
                                      const int2*, int, const int*, const bf16_t*, int, float*,
-                                     float, const int*, int, const int2*, const EnergyArgs*, int,
-                                     float4*, hipStream_t);
+                                     float, const int*, int, const int2*, const uint32_t*,
+                                     const EnergyArgs*, int, float4*, hipStream_t);
 
 }  // namespace nnp

@@ -616,7 +616,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     StageTimer t(h, io.timed, ST_AEVBWD, st);
     float4* pgrad = h->deterministic ? at<float4>(ws, P.pgrad) : nullptr;
     launch_aev_bwd<T>(dims, P.n, h->C, xyzs, rec, nbr, counts, P.cap, row, G, Fp, io.out3, io.sign,
-                      io.gidx, io.n_total, mrange, &ea, P.nmol, pgrad, st);
+                      io.gidx, io.n_total, mrange, status, &ea, P.nmol, pgrad, st);
     if (pgrad)
       launch_force_gather(dims, P.n, xyzs, rec, nbr, counts, P.cap, pgrad, io.out3, io.sign,
                           io.gidx, io.n_total, st);

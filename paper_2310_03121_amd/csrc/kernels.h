@@ -222,14 +222,15 @@ template <typename OutT>
 void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4* rec,
                     const int2* counts, int cap, const int* row_of, OutT* out, int ld, bool det,
                     bool box, unsigned long long* kmask, bool sparse, hipStream_t st);
+// status: whether the lists are whole (the launches before have set its bits).
 // pgrad: the deterministic adjoint, writing per-entry rows to pgrad (the
 // caller then runs launch_force_gather) instead of scattering into out
 template <typename GT>
 void launch_aev_bwd(const int* dims, int n_cap, const AevConst& C, const float4* xyzs,
                     const float4* rec, const int* nbr, const int2* counts, int cap, const int* row_of, const GT* g,
                     int ldg, float* out, float sign, const int* gidx, int n_total,
-                    const int2* mrange, const EnergyArgs* energy, int nmol_cap, float4* pgrad,
-                    hipStream_t st);
+                    const int2* mrange, const uint32_t* status, const EnergyArgs* energy,
+                    int nmol_cap, float4* pgrad, hipStream_t st);
 
 // mlp.hip
 template <typename T>

@@ -32,6 +32,15 @@ __device__ __forceinline__ int make_key(int j, int s, bool ang) {
   return (ang ? 0 : (1 << 30)) | (s << kKeyJBits) | j;
 }
 
+// The angular neighbors in a list that was cut: `cap` keys, in LDS.
+__device__ __forceinline__ int angular_kept(const int* key, int cap) {
+  wave_lds_sync();
+  int na = 0;
+  for (int e = lane_id(); __ballot(e < cap) != 0; e += kWave)
+    na += __popcll(__ballot(e < cap && key[e] < 1 << 30));
+  return na;
+}
+
 // Sorts the wave's keys [0, nr) by rank (keys are distinct) and writes the
 // row: indices to nbr, the matching displacement records to rec.  Lists of at
 // most 64 keep one key per lane and count smaller keys with lane reads (no
@@ -154,7 +163,7 @@ __device__ __forceinline__ void pairs_mol_wave(int i0, int n, int w, float4* lds
     if (nr > cap) {
       if (lane == 0) atomicOr(status, kStCapacity);
       nr = cap;
-      na = na < nr ? na : nr;
+      na = angular_kept(key, cap);
     }
     wave_lds_sync();
     finish_list<true>(key, lrec, nr, na, i, cap, nbr, rec, counts);
@@ -520,7 +529,7 @@ __global__ __launch_bounds__(1024) void k_pairs_cell_lds(
     if (nr > cap) {
       if (lane == 0) atomicOr(status, kStCapacity);
       nr = cap;
-      na = na < nr ? na : nr;
+      na = angular_kept(key, cap);
     }
     wave_lds_sync();
     if (i >= 0 && i < n) finish_list<false>(key, lrec, nr, na, i, cap, nbr, rec, counts);

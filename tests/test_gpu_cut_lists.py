@@ -1,0 +1,89 @@
+"""Forces where neighbor lists were cut at the capacity.
+
+Such a call reports NNP_E_CAPACITY and its forces are not the system's, but
+they are those of the cut lists: finite, and nothing that an earlier call left
+in the workspace enters them.  The lists are no longer symmetric then, so an
+atom's dE/dG need not hold the block of a neighbor's element.  The calls run on
+a workspace whose every byte is set (NaN as float and as bfloat16) and are
+compared with the float64 oracle on the cut lists; molecules of up to 10,000
+atoms, larger batches and boxes take three kernels, and a capacity of 16 the
+four- and eight-atom waves of short lists, 32 the one-atom form as well.
+
+Bar: that of the crowded neighborhoods of the adjoint's tests, whose sums are
+as long (an atom is in up to a hundred lists).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as o
+import workloads as w
+from gpu_util import pair_set_from_ell, potential, rel_rms, to_dev
+from oracle.neighbors import pair_list
+from paper_2310_03121_amd import NNPError
+
+pytestmark = pytest.mark.gpu
+BAR = {"fp32": 5e-5, "bf16": 1e-2}
+
+
+def cluster(n, side, seed):
+    rng = np.random.default_rng(seed)
+    pos = w.random_molecule(n, side, 0.9, rng).astype(np.float32)
+    return w.System(pos, rng.integers(0, 7, n).astype(np.int32), np.array([0, n], np.int32), None,
+                    7, f"cluster{n}")
+
+
+def cut_call(s, prec, cap):
+    pot, at, mt = potential(7, prec, max_neighbors=cap)
+    pos, sp, off = to_dev(s)
+    pot.workspace(s.n_atoms, s.n_mol, s.box).fill_(255)
+    E, F = pot.energy_forces(pos, sp, off, s.box)
+    with pytest.raises(NNPError) as e:
+        pot.check()
+    assert e.value.code == 4
+    counts, nbr = pot.debug_neighbors(s.n_atoms)
+    return F.cpu().numpy(), counts, nbr, at, mt
+
+
+def check_cut(F, s, counts, nbr, at, mt, prec, label):
+    """F of system s against the oracle on the lists (counts, nbr)."""
+    I, J = pair_set_from_ell(counts, nbr)
+    Ia, Ja = pair_list(s.pos, s.mol_offsets, s.box, at.rc_ang)
+    n = s.n_atoms
+    ang = np.isin(I * n + J, Ia * n + Ja)
+    sym = np.isin(I * n + J, J * n + I)
+    assert not sym.all()  # some lists were cut
+    r = o.energy_forces(s, aev_table=at, mlp_table=mt, pairs=((I, J), (I[ang], J[ang])))
+    assert bool(np.isfinite(F).all())
+    err = rel_rms(F, r.F)
+    print(f"{label}: {err:.2e}, {100 * (1 - sym.mean()):.0f} % one-sided", flush=True)
+    assert err <= BAR[prec]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("cap", [16, 32])
+@pytest.mark.parametrize("fill", [0, 400])
+def test_molecules(fill, cap, prec):
+    dense = [cluster(60, 7.5, 2), cluster(110, 6.0, 4), cluster(150, 9.0, 5)]
+    small = [w.single_molecule(10 + k % 40, seed=3000 + k, n_species=7) for k in range(fill)]
+    mols = dense[:1] + small + dense[1:]
+    s = w.pack_molecules(mols, 7)
+    print(f"\n[case] cut lists, capacity {cap}, {prec} N={s.n_atoms}", flush=True)
+    assert (s.n_atoms > 10000) == (fill > 0)
+    F, counts, nbr, at, mt = cut_call(s, prec, cap)
+    assert bool(np.isfinite(F).all())
+    for m in (0, s.n_mol - 2, s.n_mol - 1):
+        a, b = s.mol_offsets[m], s.mol_offsets[m + 1]
+        check_cut(F[a:b], mols[m], counts[a:b], nbr[a:b] - int(a), at, mt, prec, f"molecule {m}")
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("cap", [16, 48])
+def test_box(cap, prec):
+    rng = np.random.default_rng(330)
+    pos = w.random_molecule(330, 9.5, 0.9, rng).astype(np.float32)
+    s = w.System(pos, rng.integers(0, 7, 330).astype(np.int32), np.array([0, 330], np.int32),
+                 np.full(3, 10.4, np.float32), 7, "crowded")
+    print(f"\n[case] cut lists in a box, capacity {cap}, {prec}", flush=True)
+    F, counts, nbr, at, mt = cut_call(s, prec, cap)
+    check_cut(F, s, counts, nbr, at, mt, prec, "box")
