@@ -146,8 +146,13 @@ class Potential:
         return self._ws
 
     def set_params(self, params: torch.Tensor):
-        """Replace the network weights from a float32 device vector."""
+        """Replace the network weights from a float32 vector (on another
+        device than the current one it is copied first: a kernel reads it)."""
+        if params.numel() < self.n_params:
+            raise ValueError(f"params have {params.numel()} entries, expected {self.n_params}")
         p = params.detach().to(torch.float32).contiguous()
+        if p.get_device() != torch.cuda.current_device():
+            p = p.cuda()
         capi.check(self._lib.nnp_set_params_device(self._h, _ptr(p), _stream()), "set_params")
 
     # --------------------------------------------------------------- calls
