@@ -22,9 +22,13 @@ def _ptr(t):
 
 
 def _stream():
-    # the current stream's handle, without a Stream object around it (3 us a
-    # call, two per call of a training step that the host bounds: now 0.3)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the current stream's handle, without a Stream object around it where torch
+    # offers that (3 us a call, two per call of a training step that the host
+    # bounds: now 0.3)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _f32p(a):
