@@ -402,7 +402,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     if (!P.B.periodic && P.nblk <= kFusedSortBlocks) {
       // molecules: the sort and the pair scan share one launch (boxes: the
       // sort and the binning)
-      launch_sort_pairs_mol(dims, P.n, S, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
+      launch_sort_pairs_mol(dims, P.n, P.nmol, S, hist, gt, row, perm, P.rows_cap, io.off, P.wchunk,
                             h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
     } else if (P.B.periodic) {
       launch_pairs_cell(dims, P.n, h->C, P.B, xyzs, at<int>(ws, P.cell_of),
@@ -412,7 +412,7 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
                         P.nblk <= kFusedSortBlocks ? gt : nullptr, row, perm, P.rows_cap, io.off,
                         P.wchunk, st);
     } else {
-      launch_pairs_mol(dims, P.n, h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
+      launch_pairs_mol(dims, P.n, P.nmol, h->C, xyzs, mrange, P.cap, nbr, rec, counts, status, st);
     }
   }
   T* X = at<T>(ws, P.X);
@@ -1137,7 +1137,7 @@ nnp_status nnp_debug_aev(nnp_handle* h, int32_t n, int32_t nmol, const float* po
                       at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, h->S, nullptr,
                       nullptr, nullptr, nullptr, P.rows_cap, off, P.wchunk, st);
   else
-    launch_pairs_mol(dims, P.n, h->C, xyzs, mrange, P.cap, at<int>(ws, P.nbr),
+    launch_pairs_mol(dims, P.n, P.nmol, h->C, xyzs, mrange, P.cap, at<int>(ws, P.nbr),
                      at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, st);
   AevConst Cp = h->C;  // rows in the published order: no gap before the angular blocks
   Cp.A0 = h->S * kNR;

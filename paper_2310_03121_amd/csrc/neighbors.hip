@@ -611,25 +611,31 @@ void launch_force_gather(const int* dims, int n_cap, const float4* xyzs, const f
 // Atoms per wave of the molecule pair scan: four where that still leaves the
 // GPU its waves, since an atom's own loads and its molecule's are then waited
 // for once per four (32,768 atoms with the sort, one / four: 13 / 11.5 us,
-// 77,163 of all sizes 27 / 21; 8,192: 6 / 7).
-static int mol_atoms_per_wave(int n) { return n >= 16384 ? 4 : 1; }
+// 77,163 of all sizes 27 / 21; 8,192: 6 / 7).  Not in large molecules: an
+// atom's scan is long then, few waves hide little of it, and the kept
+// candidates are a small part (molecules of 300 atoms, 78,000 in all: 39 / 35,
+// 900: 17,100 in all 26 / 32; 1,500: 18,000 in all 35 / 47; one of 23,001:
+// 356 / 452).
+static int mol_atoms_per_wave(int n, int nmol) {
+  return n >= 16384 && n / 512 <= nmol ? 4 : 1;
+}
 
-void launch_pairs_mol(const int* dims, int n_cap, const AevConst& C, const float4* xyzs,
-                      const int2* mrange, int cap, int* nbr, float4* rec, int2* counts,
+void launch_pairs_mol(const int* dims, int n_cap, int nmol_cap, const AevConst& C,
+                      const float4* xyzs, const int2* mrange, int cap, int* nbr, float4* rec, int2* counts,
                       uint32_t* status, hipStream_t st) {
   if (n_cap <= 0) return;
-  const int A = mol_atoms_per_wave(n_cap);
+  const int A = mol_atoms_per_wave(n_cap, nmol_cap);
   hipLaunchKernelGGL(A == 4 ? k_pairs_mol<4> : k_pairs_mol<1>, dim3((n_cap + 4 * A - 1) / (4 * A)),
                      dim3(256), 4 * cap * (sizeof(float4) + sizeof(int)), st, dims, C, xyzs, mrange,
                      cap, nbr, rec, counts, status);
 }
 
-void launch_sort_pairs_mol(const int* dims, int n_cap, int S, const int* hist, GroupTable* gt,
-                           int* row, int* perm, int rows_cap, const int* off, int wchunk_rows,
+void launch_sort_pairs_mol(const int* dims, int n_cap, int nmol_cap, int S, const int* hist,
+                           GroupTable* gt, int* row, int* perm, int rows_cap, const int* off, int wchunk_rows,
                            const AevConst& C, const float4* xyzs, const int2* mrange, int cap,
                            int* nbr, float4* rec, int2* counts, uint32_t* status,
                            hipStream_t st) {
-  const int nsort = stage_blocks(n_cap), A = mol_atoms_per_wave(n_cap);
+  const int nsort = stage_blocks(n_cap), A = mol_atoms_per_wave(n_cap, nmol_cap);
   const int npair = n_cap > 0 ? (n_cap + 4 * A - 1) / (4 * A) : 0;
   hipLaunchKernelGGL(A == 4 ? k_sort_pairs_mol<4> : k_sort_pairs_mol<1>, dim3(nsort + npair),
                      dim3(256), 4 * cap * (sizeof(float4) + sizeof(int)), st, dims, nsort, S, hist,
