@@ -131,13 +131,18 @@ __device__ __forceinline__ aev_f32x4 mfma4(float a, float b, aev_f32x4 acc) {
 //
 // Quads pay off where lists are short and waves are many; elsewhere a wave
 // per atom keeps four times as many waves in flight to hide the latency of the
-// per-atom passes.  Measured (us, one atom / four atoms per wave): molecules,
-// 1,024 atoms 5.5 / 13.1, 8,192: 10.1 / 15.0, 16,384: 16.6 / 17.8, 32,768: 28.2
-// / 20.1 to 28.3 (by how crowded the molecule is); so molecules of more than
-// 16,384 atoms take quads, boxes (about 55 neighbors) and smaller calls one
-// atom.
+// per-atom passes.  The host does not see the lists, but long ones take large
+// molecules: more than 16,384 atoms in molecules of at most 160 in the mean take
+// quads, the others (and boxes) one atom.  Measured (us, one atom / four atoms
+// per wave).  Molecules of 64 atoms, 8 neighbors per atom: 1,024 atoms 5.5 / 13.1,
+// 8,192: 10.1 / 15.0, 16,640: 18.4 / 17.0, 32,768: 27.6 / 22.9; of 10 to 150:
+// 77,163: 52 / 47; of 150: 18,000: 18.3 / 21.7, 75,000: 51 / 47.  Molecules three
+// times as dense, whose lists mostly miss the 64 entries: of 64: 16,640: 31 / 36,
+// 32,768: 51 / 51; of 10 to 150: 77,163: 90 / 104; of 150: 75,000: 104 / 113.
+// Drops of 300 atoms (35 neighbors): 17,400: 45 / 58, 78,000: 148 / 165; one of
+// 23,001: 74 / 99.
 constexpr int kQuadNbr = 16;   // lanes per atom of a quad wave
-constexpr int kQuadAtoms = 16384;
+constexpr int kQuadAtoms = 16384, kQuadMolecule = 160;
 
 __host__ __device__ constexpr int aev_region(int cap) { return cap > 64 ? cap : 64; }
 
@@ -1394,11 +1399,11 @@ static void launch_aev_fwd_q(const int* dims, int n_cap, const AevConst& C, cons
 }
 
 template <typename OutT>
-void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4* rec,
-                    const int2* counts, int cap, const int* row_of, OutT* out, int ld, bool det,
-                    bool box, unsigned long long* kmask, bool sparse, hipStream_t st) {
+void launch_aev_fwd(const int* dims, int n_cap, int nmol_cap, const AevConst& C,
+                    const float4* rec, const int2* counts, int cap, const int* row_of, OutT* out,
+                    int ld, bool det, unsigned long long* kmask, bool sparse, hipStream_t st) {
   if (n_cap <= 0) return;
-  const bool quads = !box && n_cap > kQuadAtoms;
+  const bool quads = n_cap > kQuadAtoms && n_cap / kQuadMolecule <= nmol_cap;
   sparse = sparse && kmask && ld <= 64 * 32;
   if (quads && !det)
     launch_aev_fwd_q<OutT, 4>(dims, n_cap, C, rec, counts, cap, row_of, out, ld, kmask, sparse,
@@ -1407,11 +1412,11 @@ void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4*
     launch_aev_fwd_q<OutT, 1>(dims, n_cap, C, rec, counts, cap, row_of, out, ld, kmask, sparse,
                               st);
 }
-template void launch_aev_fwd<float>(const int*, int, const AevConst&, const float4*, const int2*,
-                                    int, const int*, float*, int, bool, bool, unsigned long long*, bool,
-                                    hipStream_t);
-template void launch_aev_fwd<bf16_t>(const int*, int, const AevConst&, const float4*,
-                                     const int2*, int, const int*, bf16_t*, int, bool, bool,
+template void launch_aev_fwd<float>(const int*, int, int, const AevConst&, const float4*,
+                                    const int2*, int, const int*, float*, int, bool,
+                                    unsigned long long*, bool, hipStream_t);
+template void launch_aev_fwd<bf16_t>(const int*, int, int, const AevConst&, const float4*,
+                                     const int2*, int, const int*, bf16_t*, int, bool,
                                      unsigned long long*, bool, hipStream_t);
 
 template <typename GT>

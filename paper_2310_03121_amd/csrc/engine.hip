@@ -422,8 +422,8 @@ nnp_status run_path(nnp_handle* h, const Plan& P, void* ws, const EvalIO& io, hi
     StageTimer t(h, io.timed, ST_AEV, st);
     // the fused network and layer 1's weight gradients by k-steps read each
     // row's own k-steps only; the other kernels read whole rows
-    launch_aev_fwd<T>(dims, P.n, h->C, rec, counts, P.cap, row, X, Fp, h->deterministic,
-                      P.B.periodic != 0, kmask, h->net && (!io.dparams || wsparse), st);
+    launch_aev_fwd<T>(dims, P.n, P.nmol, h->C, rec, counts, P.cap, row, X, Fp, h->deterministic,
+                      kmask, h->net && (!io.dparams || wsparse), st);
   }
 
   T* H1 = at<T>(ws, P.H1);
@@ -1141,8 +1141,8 @@ nnp_status nnp_debug_aev(nnp_handle* h, int32_t n, int32_t nmol, const float* po
                      at<float4>(ws, P.rec), at<int2>(ws, P.counts), status, st);
   AevConst Cp = h->C;  // rows in the published order: no gap before the angular blocks
   Cp.A0 = h->S * kNR;
-  launch_aev_fwd<float>(dims, P.n, Cp, at<float4>(ws, P.rec), at<int2>(ws, P.counts), P.cap,
-                        nullptr, aev, h->F, h->deterministic, P.B.periodic != 0, nullptr, false, st);
+  launch_aev_fwd<float>(dims, P.n, P.nmol, Cp, at<float4>(ws, P.rec), at<int2>(ws, P.counts),
+                        P.cap, nullptr, aev, h->F, h->deterministic, nullptr, false, st);
   return launches_ok() ? NNP_OK : NNP_E_HIP;
 }
 

@@ -214,14 +214,14 @@ void launch_force_gather(const int* dims, int n_cap, const float4* xyzs, const f
                          float* out, float sign, const int* gidx, int n_total, hipStream_t st);
 
 // aev.hip
-// det: one atom per wave.  box: periodic (long lists).  kmask (optional, [rows]):
+// det: one atom per wave.  nmol_cap: molecules (1 or 2 for a box).  kmask (optional, [rows]):
 // per row, bit q set when k-step q (feature columns 32 q .. 32 q + 31) holds
 // a block the atom touches; sparse (needs kmask and ld <= 2048): only those
 // k-steps of the row are stored (the rest of the row is left as it was).
 template <typename OutT>
-void launch_aev_fwd(const int* dims, int n_cap, const AevConst& C, const float4* rec,
-                    const int2* counts, int cap, const int* row_of, OutT* out, int ld, bool det,
-                    bool box, unsigned long long* kmask, bool sparse, hipStream_t st);
+void launch_aev_fwd(const int* dims, int n_cap, int nmol_cap, const AevConst& C,
+                    const float4* rec, const int2* counts, int cap, const int* row_of, OutT* out,
+                    int ld, bool det, unsigned long long* kmask, bool sparse, hipStream_t st);
 // status: whether the lists are whole (the launches before have set its bits).
 // pgrad: the deterministic adjoint, writing per-entry rows to pgrad (the
 // caller then runs launch_force_gather) instead of scattering into out
