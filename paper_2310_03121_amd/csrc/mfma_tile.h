@@ -87,8 +87,10 @@ struct BRing {
   }
   template <int U>
   __device__ __forceinline__ void load(int s) {
-    const T* p = s < ns ? base + (size_t)s * FE
-                        : (s < nsp ? base + (size_t)(ns - 1) * FE : base_next + (size_t)(s - nsp) * FE);
+    // (a next pass of fewer steps than the ring: its last one again, inside B;
+    // A is zero there, but what lies behind B may be a NaN)
+    const int t = s < nsp ? s : s - nsp;
+    const T* p = (s < nsp ? base : base_next) + (size_t)(t < ns ? t : ns - 1) * FE;
 #pragma unroll
     for (int j = 0; j < TN; ++j) r[U][j] = *reinterpret_cast<const uint4*>(p + j * tile);
   }
