@@ -241,9 +241,9 @@ __device__ __forceinline__ unsigned seen_bits(int e, int nr, int na, const float
 // offsets, which tiles a pass touches is read from two wave-wide masks, and
 // the row's k-steps come from one bitwise or over the entries and are formed
 // for four atoms at once.  Measured: 23,001-atom water box 99 -> 78 us (1,456
-// -> 977 vector instructions per atom), 4,500 atoms in FP32 32 -> 27 us, the
-// 32,768-atom batch 23.9 -> 21.7 us, 77,163 mixed atoms 50.5 -> 45.2 us, 1,645
-// atoms (a wave per atom now) 14.6 -> 6.3 us.
+// -> 976 vector instructions per atom), 4,500 atoms in FP32 32 -> 27 us, the
+// 32,768-atom batch 23.9 -> 21.9 us, 77,163 mixed atoms 50.5 -> 46.4 us, 1,645
+// atoms (a wave per atom now) 14.6 -> 5.9 us.
 template <typename OutT, int NT, int Q>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT < 3 && Q == 1 ? 8 : 7, 8))) void
 k_aev_fwd(const int* __restrict__ dims, AevConst C, const float4* __restrict__ rec,
@@ -814,10 +814,10 @@ __device__ __forceinline__ float radial_pull(const AevConst& C, const GT* __rest
 }
 
 // The adjoint of one atom by one wave; put(j, c, x) adds x to component c of
-// atom j.  (23,001-atom water box, BF16: 148 -> 73 us against scattering every
+// atom j.  (23,001-atom water box, BF16: 148 -> 74 us against scattering every
 // entry and adding the pairs by lane scans and LDS atomics, 4,500 atoms in
-// FP32 38 -> 24 us; it is bound by vector instructions, about 1,250 per atom,
-// 50 us at the full issue rate.)
+// FP32 38 -> 24 us; it is bound by vector instructions, 1,380 per atom of which
+// 88 transcendental: 61 us at four and sixteen clocks each.)
 //
 // Radial part: pulled, one lane per entry.  Angular part: one lane per
 // unordered pair of angular neighbors.  A pair leaves three numbers in LDS
@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void adjoint_one(int i, int n, const AevConst& C, int
 // angular neighbors of all atoms form one list, one lane per pair, whose
 // results go through LDS as in adjoint_one.  Needs at most 16 angular
 // neighbors per atom; returns false (nothing done) otherwise.  (32,768-atom
-// batch 18.8 -> 15.3 us, 77,163 atoms of mixed molecules 73.5 -> 39.4 us against
+// batch 18.8 -> 15.6 us, 77,163 atoms of mixed molecules 73.5 -> 40.4 us against
 // eight lanes per pair, lists of at most 16 entries and LDS atomics: mixed
 // molecules have longer lists now and then, which took the slow path.)
 template <int H>

@@ -4,8 +4,8 @@
 // weights on one device.  An evaluation carves the caller's workspace,
 // enqueues the kernels of the path on the caller's stream and returns:
 //   stage + species sort -> neighbor search -> symmetry functions ->
-//   network layers (grouped GEMMs) -> FP64 energy sums ->
-//   adjoint layers -> symmetry-function adjoint + force scatter.
+//   networks and their adjoint (one fused launch; other widths: grouped
+//   GEMMs) -> symmetry-function adjoint + force scatter, FP64 energy sums.
 // Nothing here synchronises except nnp_check and the server's retire step.
 #include <hip/hip_runtime.h>
 
@@ -76,8 +76,13 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 // Rows per weight-gradient partial: 1,024, or fewer for small systems so that
-// about 24 chunks spread over the GPU (8,192 atoms in FP32: 87 us for the
-// weight gradients in chunks of 1,024 rows, 46 us in chunks of 384).
+// about 24 chunks spread over the GPU.  Weight gradients by events, us, in
+// chunks of 128 / 256 / 512 / 1,024 rows (* the rule's): FP32, 512 atoms of seven
+// elements 27* / 35 / 34 / 34, 2,048 of four 32* / 32 / 50 / 64, 4,500 of water
+// 35* / 35 / 52 / 88, 8,192 of seven 57 / 56 / 65 / 92 (384: 59*), 32,768 of seven
+// 178 / 178 / 143 / 159* (768: 137); BF16, 2,048 of seven 26* / 26 / 27 / 33, 8,192
+// 29 / 29 / 30 / 34 (384: 29*), 32,768: 62 / 63 / 63 / 54*.  (Chunks shorter than
+// the partials' room holds are lengthened to it.)
 int wgrad_chunk_rows(int n) {
   return std::min(1024, std::max(128, (n / 24 + 127) / 128 * 128));
 }
@@ -335,12 +340,15 @@ bool launches_ok() {
 // of 5 to 12 us): where fewer k-steps per tile save more than that, which asks
 // for many k-steps and for more tiles than run at once.  Networks in us,
 // unsorted / sorted, without that launch: FP32 forces of seven elements 3,072
-// atoms 43 / 40, 4,096: 74 / 52, 8,192: 60 / 48, 32,768: 243 / 163; of four
+// atoms 43 / 40, 4,096: 74 / 52, 8,192: 60 / 48, 32,768: 256 / 166; of four
 // elements 8,192: 37 / 35, 32,768: 128 / 97.  BF16 forces of seven elements
 // 25,600 atoms 41 / 33, 32,768: 40 / 33, 51,200: 83 / 57, 77,163 of all sizes:
-// 109 / 81, eight members of 4,096: 68 / 61, of 32,768: 287 / 241; energies
+// 109 / 81, eight members of 4,096: 68 / 61, of 32,768: 289 / 245; energies
 // 64,000: 43 / 34; four elements 77,163: 60 / 54.  A box of a liquid has few
-// elements and every row the same k-steps (23,001 atoms of water: 29 / 28).
+// elements and every row the same k-steps (water with the launch: FP32 4,500
+// atoms 44 / 53, 23,001: 115 / 122, BF16 31 / 37).  The host does not see which
+// elements a box holds; one of all seven would gain in FP32 (4,500 atoms 101 /
+// 91, 23,001: 329 / 256), not in BF16 (27 / 32, 52 / 55).
 bool net_ordered(const nnp_handle* h, const Plan& P, bool grad) {
   if (P.B.periodic) return false;
   const bool many = h->Fp > 512;

@@ -181,12 +181,12 @@ void launch_fill_f64(double* p, double v, int n, hipStream_t st);
 // matching records (dx, dy, dz, species bits) with d = x_j - x_i (minimum
 // image when periodic), computed by the cutoff predicate's own arithmetic.
 void launch_pairs_mol(const int* dims, int n_cap, int nmol_cap, const AevConst& C,
-                      const float4* xyzs, const int2* mrange, int cap, int* nbr, float4* rec, int2* counts,
-                      uint32_t* status, hipStream_t st);
+                      const float4* xyzs, const int2* mrange, int cap, int* nbr, float4* rec,
+                      int2* counts, uint32_t* status, hipStream_t st);
 // launch_sort_scatter and launch_pairs_mol in one launch (n_cap <= 256 * kFusedSortBlocks)
 void launch_sort_pairs_mol(const int* dims, int n_cap, int nmol_cap, int S, const int* hist,
-                           GroupTable* gt, int* row, int* perm, int rows_cap, const int* off, int wchunk_rows,
-                           const AevConst& C, const float4* xyzs, const int2* mrange, int cap,
+                           GroupTable* gt, int* row, int* perm, int rows_cap, const int* off,
+                           int wchunk_rows, const AevConst& C, const float4* xyzs, const int2* mrange, int cap,
                            int* nbr, float4* rec, int2* counts, uint32_t* status,
                            hipStream_t st);
 // Periodic boxes: cell_cnt holds cell_zero_ints(ncell) ints that staging

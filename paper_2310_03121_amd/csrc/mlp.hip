@@ -1120,7 +1120,7 @@ __device__ __forceinline__ void wgrad_vec(const float* __restrict__ up,
 // row pitches of 272 and 48 floats put a fragment's four K rows in different
 // banks).  k-steps that no row has are not written: act says which are.
 // (Dense tiles over all rows: 136 us for the weight gradients of 8,192 atoms
-// in FP32, 58 us for 32,768 in BF16; now 46 and 40.)
+// in FP32, 58 us for 32,768 in BF16; now 45 and 41.)
 constexpr int kWgMaxChunk = 1024;
 constexpr int kWgSpBlocks = 12;  // about as many k-steps as a chunk has
 constexpr int kWgSpD = 272, kWgSpX = 48;  // FP32 row pitches (floats)
@@ -1511,7 +1511,7 @@ template void launch_wgrad_net<bf16_t>(const GroupTable*, int, int, int, const W
 // A wave's fragment is then one contiguous 1 KB block.  One thread packs one
 // lane's 16 bytes of a fragment (so a wave writes whole fragments; one thread
 // per weight scattered 2- and 4-byte stores: 22 us for the 2.4 M weights of
-// seven elements in one precision and both orders, now 12 us).
+// seven elements in one precision and both orders, now 9 us).
 
 // Layer 1: inputs from r0 on sit at columns from a0 on (zero between).
 __device__ __forceinline__ float packed_weight(const float* __restrict__ W, int o, int c, int in,

@@ -31,17 +31,18 @@
 // before it they queue for 1.6 us behind each other, 64 bytes per clock and
 // CU, and the epilogue's arithmetic waits), biases, upstream gradients and
 // row indices before the products that need them, CELU has no branch, and
-// conversions to BF16 are packed.  Measured per evaluation,
-// BF16 batch: 42.3 -> 37.7 us; FP32 batch, which ran one GEMM per layer with
-// activations through HBM: 342 -> 233 us, and 163 with the rows sorted by
-// k-steps (its products at the rate a large FP32 product reaches, 154
-// TFLOP/s, take 101); one 24-atom molecule in FP32: 108 -> 20 us; an
-// eight-network ensemble, which ran two launches per member: 603 -> 279 us on
-// the batch, 241 with sorted rows, 403 -> 33 us on one 53-atom molecule.
+// conversions to BF16 are packed.  Kernel time per evaluation (from traces, as
+// all kernel times in these sources), BF16 batch: 42 -> 40 us; FP32 batch, which
+// ran one GEMM per layer with activations through HBM: 342 -> 256 us, and 166
+// with the rows sorted by k-steps (its products at the rate a large FP32 product
+// reaches, 154 TFLOP/s, take 101); one 24-atom molecule in FP32: 108 -> 21 us;
+// an eight-network ensemble with its dE/dG, which ran two launches per member:
+// 603 -> 289 us on the batch, 245 with sorted rows, 402 -> 31 us on one 53-atom
+// molecule.
 //
 // Every row's result is independent of the tile it sits in: the sums over K
 // run in the same order for every tile size, and the energy's sum over the
-// last hidden layer in one of two fixed orders (EnergyOrder).
+// last hidden layer in one of two fixed orders (HEAD).
 #pragma once
 #include "mfma_tile.h"
 

@@ -65,8 +65,8 @@ template int net_tile<bf16_t>(int, int, bool);
 // unlike masks: their tiles take up to twice the time of the others.  Eight
 // more workgroups list the tiles of each XCD's range with the ends of all
 // windows first, so that no long tile starts last (512 x 64 conformers in FP32,
-// two rounds of tiles: 194 us with the tiles in order, now 163; 77,163 rows in
-// BF16 96, now 80).
+// two rounds of tiles: 194 us with the tiles in order, now 166; 77,163 rows in
+// BF16 96, now 81).
 constexpr int kOrderWaves = 8;
 __device__ __forceinline__ void order_tiles(const GroupTable* __restrict__ gt, int xcd,
                                             int tile_rows, int* __restrict__ tiles, int* bin) {
@@ -325,8 +325,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // it.  The tile's deltas all lie in LDS (16 rows of up to 8 KB), so the loop has
 // no barriers, a ring of 16 steps keeps the weights' latency out of it, and no
 // products run for 48 absent rows; the sums are those of the large form, step
-// by step.  Eight members, 128 / 1,024 atoms: 71 / 72 us in the large form, 27 /
-// 53 here.  BF16, half the bytes and an eighth of the matrix time, is faster in
+// by step.  Eight members of 256 columns, 128 / 1,024 / 1,536 / 2,048 atoms: 71 /
+// 72 / 73 / 73 us in the large form, whose tiles then run side by side, 27 / 54 /
+// 77 / 102 here; eight of 160, 1,024 / 2,048 / 3,072: 48 / 48 / 48 and 36 / 38 /
+// 53; two of 256, 1,536 / 2,048: 23 / 24 and 17 / 27.  BF16, half the bytes and an eighth of the matrix time, is faster in
 // the large form, which multiplies while it loads (53 / 1,024 atoms 12 / 13 us,
 // 14 / 15 here).
 constexpr int kGradSmallRing = 16;

@@ -102,7 +102,7 @@ __device__ __forceinline__ void finish_list(const int* key, const float4* lrec, 
 // and kept from one atom to the next of the same molecule (up to kMolKeep
 // batches of 64).  Bound by instructions, vector and scalar alike (118 and 67
 // per atom when ranks came from a lane read and a comparison per neighbor, now
-// 103 and 54: 49,152 atoms in molecules of 24 with the sort 16.4 -> 13.6 us).
+// 104 and 55: 49,152 atoms in molecules of 24 with the sort 16.4 -> 12.9 us).
 constexpr int kMolKeep = 3;
 __device__ __forceinline__ float readlane_f(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
