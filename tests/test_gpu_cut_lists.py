@@ -87,3 +87,27 @@ def test_box(cap, prec):
     print(f"\n[case] cut lists in a box, capacity {cap}, {prec}", flush=True)
     F, counts, nbr, at, mt = cut_call(s, prec, cap)
     check_cut(F, s, counts, nbr, at, mt, prec, "box")
+
+
+@pytest.mark.parametrize("subset", [False, True])
+def test_overlapping_molecules(subset):
+    """Offsets that fall back: reported, and the lists are not symmetric
+    either (an atom's molecule may not list it)."""
+    s = w.pack_molecules([w.single_molecule(20, seed=k, n_species=7) for k in range(520)], 7)
+    off = s.mol_offsets.copy()
+    off[5::10] += 30
+    print(f"\n[case] overlapping molecules N={s.n_atoms} subset={subset}", flush=True)
+    pot, _, _ = potential(7, "fp32", max_neighbors=128)
+    pos, sp, _ = to_dev(s)
+    off = torch.from_numpy(off).cuda()
+    pot.workspace(s.n_atoms, s.n_mol, None).fill_(255)
+    if subset:
+        F = torch.zeros_like(pos)
+        idx = torch.arange(s.n_atoms, dtype=torch.int32, device="cuda")
+        pot.energy_forces_subset(idx, pos, sp, off, F)
+    else:
+        _, F = pot.energy_forces(pos, sp, off)
+    with pytest.raises(NNPError) as e:
+        pot.check()
+    assert e.value.code == 1
+    assert bool(torch.isfinite(F).all())
